@@ -6,6 +6,7 @@
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -13,6 +14,7 @@
 #include <mutex>
 #include <queue>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "slr.h"
@@ -547,7 +549,7 @@ bool b_lds_plan_sz(int32_t max_m, int32_t max_lev, int32_t max_level_bytes, int6
     const int64_t rest = ((int64_t)limit - fixed - xb) & ~int64_t(15);
     if (rest >= need) {
       R = r;
-      stage = (int32_t)std::min<int64_t>(rest, pad16h(data_bytes));
+      stage = (int32_t)std::min<int64_t>(rest, std::max<int64_t>(pad16h(data_bytes), 2 * pad16h(max_level_bytes)));
       return true;
     }
   }
@@ -577,6 +579,7 @@ int run_bsolve(slr_ctx *c, const BlockArrays<TS> &B, const BArgs &a0, hipStream_
   } else if (!b_lds_plan(c, a.nrhs, sizeof(TC), R, stage)) {
     return fail(SLR_ERR_ARG, "a subdomain does not fit the LDS of one workgroup");
   }
+  if (B.pack_K == 0) threads = bsolve_threads(0);   // its programs are laid out for that many waves
   a.R = R;
   a.stage_bytes = stage;
   const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)sizeof(TC) * (c->b_max_m * R + 1)) +
@@ -649,7 +652,7 @@ int c1solve(slr_ctx *c, BArgs a, int32_t sweeps, bool compute64, hipStream_t st)
   a.stage_bytes = stage;
   const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)tcb * ((int64_t)I.max_m * R + 1)) +
                      16 * (size_t)(I.max_lev + 1);
-  const int32_t threads = 256;
+  const int32_t threads = (c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K) > 0 ? 256 : bsolve_threads(0);
   if (c->fact_prec == SLR_FP64)
     launch_bsolve<double, double>(I.Bd, I.nb, a, threads, lds, st);
   else if (compute64)
@@ -1247,47 +1250,17 @@ int lanczos_inner(slr_ctx *c, const double *v0_host, hipStream_t st) {
 // Fixed-width sweeps: levels wider than 64 * rec_passes(K) rows are cut into
 // consecutive sub-levels of at most that many rows (the rows of a level are
 // independent, so the schedule stays valid and the arithmetic unchanged).
-// Bytes of one ELL level segment of L rows of width K (layout in pack_sweep).
-int64_t ell_segment_bytes(int64_t L, int64_t K, int64_t ts) {
-  return pad16h(kEllHeaderBytes + pad8h(2 * L) + pad8h(ts * L) + pad8h(2 * K * L) + ts * K * L);
-}
-
-// Rows of one level are independent, so any split of a level is a valid
-// schedule.  Fixed-width records: levels wider than 64 * rec_passes(K) rows
-// are split (one straight-line pass per lane).  ELL form: each level is cut
-// into consecutive pieces of at most kEllLevelBytes (or one row), each
-// padded only to its own widest row.
-Sweep split_levels(const Sweep &sw, int32_t Kfix, int64_t ts) {
+Sweep split_levels(const Sweep &sw, int32_t Kfix) {
   Sweep out = sw;
   out.levptr.assign(1, 0);
-  for (int32_t l = 0; l < sw.nlev; ++l) {
-    const int32_t a = sw.levptr[l], b = sw.levptr[l + 1];
-    if (Kfix > 0) {
-      const int32_t cap = 64 * rec_passes(Kfix);
-      for (int32_t t = a; t < b; t += cap) out.levptr.push_back(std::min(t + cap, b));
-      continue;
-    }
-    int32_t t0 = a, K = 0;
-    for (int32_t t = a; t < b; ++t) {
-      const int32_t Kt = std::max(K, sw.rp[t + 1] - sw.rp[t]);
-      if (t > t0 && ell_segment_bytes(t + 1 - t0, Kt, ts) > kEllLevelBytes) {
-        out.levptr.push_back(t);
-        t0 = t;
-        K = sw.rp[t + 1] - sw.rp[t];
-      } else {
-        K = Kt;
-      }
-    }
-    out.levptr.push_back(b);
-  }
+  const int32_t cap = 64 * rec_passes(Kfix);
+  for (int32_t l = 0; l < sw.nlev; ++l)
+    for (int32_t t = sw.levptr[l], b = sw.levptr[l + 1]; t < b; t += cap) out.levptr.push_back(std::min(t + cap, b));
   out.nlev = (int32_t)out.levptr.size() - 1;
   if (sw.levptr.empty()) out.levptr.clear();
   return out;
 }
 
-// Pack one sweep of one subdomain as the level-sliced byte stream the B
-// kernel stages into LDS (layouts documented with BlockDesc): row records
-// when every row has the fixed width Kfix > 0, else the ELL form.
 // Coefficient maps of a device refactorisation (built while packing).
 struct RfSweepMaps {
   std::vector<RfMap> sc, w, w2;
@@ -1308,70 +1281,35 @@ RfMap rf_weight(const Sweep &sw, int32_t t, int32_t e, int64_t off, int64_t ebas
   return RfMap{off, (int32_t)(ebase + sw.w_e[e]), 0, 0, RF_RAW};
 }
 
+// Pack one fixed-width sweep of one subdomain as the level-sliced byte
+// stream the B kernel stages into LDS (row records, layout with BlockDesc).
 template <typename TS>
-void pack_sweep(const Sweep &sw, int32_t Kfix, std::vector<uint8_t> &data, std::vector<int32_t> &lvb, int32_t &K,
+void pack_sweep(const Sweep &sw, int32_t K, std::vector<uint8_t> &data, std::vector<int32_t> &lvb,
                 int32_t &max_level_bytes, int64_t &offset, std::vector<RfMap> *map = nullptr, int64_t ebase = 0) {
-  K = 0;
-  for (int32_t t = 0; t < sw.nrows; ++t) K = std::max(K, sw.rp[t + 1] - sw.rp[t]);
-  if (Kfix > 0) K = Kfix;
   offset = (int64_t)data.size();
   int64_t pos = 0;
   lvb.push_back(0);
   const int32_t KR = rec_width(K);
   for (int32_t l = 0; l < sw.nlev; ++l) {
     const int32_t a = sw.levptr[l], L = sw.levptr[l + 1] - a;
-    int64_t size;
-    if (Kfix > 0) {
-      // row records: int32 [row, c_0 .. c_{K-1}, pad] then TS [sc, w_0 .. w_{K-1}, pad]
-      const int64_t o_w = 4 * (int64_t)KR * L;
-      size = o_w + (int64_t)sizeof(TS) * KR * L;
-      data.resize(offset + pos + size, 0);
-      uint8_t *base = data.data() + offset + pos;
-      int32_t *ix = reinterpret_cast<int32_t *>(base);
-      TS *wr = reinterpret_cast<TS *>(base + o_w);
-      const int64_t wbase = offset + pos + o_w;
-      for (int32_t j = 0; j < L; ++j) {
-        const int32_t t = a + j, row = sw.rows[t];
-        const int32_t e0 = sw.rp[t], cnt = sw.rp[t + 1] - e0;
-        ix[(int64_t)j * KR] = row;
-        wr[(int64_t)j * KR] = (TS)sw.sc[t];
-        if (map) map->push_back(rf_scale(sw, t, wbase + (int64_t)sizeof(TS) * j * KR, ebase));
-        for (int32_t e = 0; e + 1 < KR; ++e) {
-          ix[(int64_t)j * KR + 1 + e] = e < cnt ? sw.ci[e0 + e] : row;
-          wr[(int64_t)j * KR + 1 + e] = e < cnt ? (TS)sw.w[e0 + e] : (TS)0;
-          if (map && e < cnt)
-            map->push_back(rf_weight(sw, t, e0 + e, wbase + (int64_t)sizeof(TS) * ((int64_t)j * KR + 1 + e), ebase));
-        }
-      }
-    } else {
-      // this level's own width
-      int32_t Kl = 0;
-      for (int32_t j = 0; j < L; ++j) Kl = std::max(Kl, sw.rp[a + j + 1] - sw.rp[a + j]);
-      const int32_t K = Kl;
-      const int64_t o_rows = kEllHeaderBytes;
-      const int64_t o_sc = o_rows + pad8h(2 * L), o_ci = o_sc + pad8h((int64_t)sizeof(TS) * L);
-      const int64_t o_w = o_ci + pad8h(2 * (int64_t)K * L);
-      size = ell_segment_bytes(L, K, sizeof(TS));
-      data.resize(offset + pos + size, 0);
-      uint8_t *base = data.data() + offset + pos;
-      *reinterpret_cast<int32_t *>(base) = K;
-      uint16_t *rows = reinterpret_cast<uint16_t *>(base + o_rows);
-      TS *sc = reinterpret_cast<TS *>(base + o_sc);
-      uint16_t *ci = reinterpret_cast<uint16_t *>(base + o_ci);
-      TS *w = reinterpret_cast<TS *>(base + o_w);
-      const int64_t sbase = offset + pos + o_sc, wbase = offset + pos + o_w;
-      for (int32_t j = 0; j < L; ++j) {
-        const int32_t t = a + j, row = sw.rows[t];
-        rows[j] = (uint16_t)row;
-        sc[j] = (TS)sw.sc[t];
-        if (map) map->push_back(rf_scale(sw, t, sbase + (int64_t)sizeof(TS) * j, ebase));
-        const int32_t e0 = sw.rp[t], cnt = sw.rp[t + 1] - e0;
-        for (int32_t e = 0; e < K; ++e) {
-          ci[(int64_t)e * L + j] = (uint16_t)(e < cnt ? sw.ci[e0 + e] : row);
-          w[(int64_t)e * L + j] = e < cnt ? (TS)sw.w[e0 + e] : (TS)0;
-          if (map && e < cnt)
-            map->push_back(rf_weight(sw, t, e0 + e, wbase + (int64_t)sizeof(TS) * ((int64_t)e * L + j), ebase));
-        }
+    // row records: int32 [row, c_0 .. c_{K-1}, pad] then TS [sc, w_0 .. w_{K-1}, pad]
+    const int64_t o_w = 4 * (int64_t)KR * L, size = o_w + (int64_t)sizeof(TS) * KR * L;
+    data.resize(offset + pos + size, 0);
+    uint8_t *base = data.data() + offset + pos;
+    int32_t *ix = reinterpret_cast<int32_t *>(base);
+    TS *wr = reinterpret_cast<TS *>(base + o_w);
+    const int64_t wbase = offset + pos + o_w;
+    for (int32_t j = 0; j < L; ++j) {
+      const int32_t t = a + j, row = sw.rows[t];
+      const int32_t e0 = sw.rp[t], cnt = sw.rp[t + 1] - e0;
+      ix[(int64_t)j * KR] = row;
+      wr[(int64_t)j * KR] = (TS)sw.sc[t];
+      if (map) map->push_back(rf_scale(sw, t, wbase + (int64_t)sizeof(TS) * j * KR, ebase));
+      for (int32_t e = 0; e + 1 < KR; ++e) {
+        ix[(int64_t)j * KR + 1 + e] = e < cnt ? sw.ci[e0 + e] : row;
+        wr[(int64_t)j * KR + 1 + e] = e < cnt ? (TS)sw.w[e0 + e] : (TS)0;
+        if (map && e < cnt)
+          map->push_back(rf_weight(sw, t, e0 + e, wbase + (int64_t)sizeof(TS) * ((int64_t)j * KR + 1 + e), ebase));
       }
     }
     max_level_bytes = std::max<int32_t>(max_level_bytes, (int32_t)size);
@@ -1380,173 +1318,345 @@ void pack_sweep(const Sweep &sw, int32_t Kfix, std::vector<uint8_t> &data, std::
   }
 }
 
-// ELL-form sweep (any width) packed with its near-chains solved by
-// columns.  A run of at least kColRunMin consecutive levels of at most
+// Sweep of any row width as segments of tasks (layout with BlockDesc).
+//
+// A level's rows are cut into pieces of about kPieceBytes of entries; the
+// rows of a piece get the same number of lanes, by the piece's rows and its
+// widest row (or `lanes`, log2, for the whole sweep); 64 lanes make a task.  A run of at least kColRunMin consecutive levels of at most
 // kColRunRows rows each -- typically the long rows at the end of a minimum
-// degree or threshold factor, each waiting for the previous one -- is
-// packed as (1) ELL pieces holding the run's rows with their scale and the
-// entries to rows before the run (independent rows: those rows are final),
-// then (2) column segments: for each run row in order, the run rows after
-// it that use it, with their weights.  The kernel then finishes a run row
-// by a read of its value and updates the rows that use it, instead of one
-// reduction per level.  Other levels are cut into ELL pieces as
-// split_levels does.  Appends the segments' byte offsets to lvb and their
-// row counts (prefix sums, from 0) to lev; returns the segment count.
+// degree or threshold factor, each waiting for the previous one -- is packed
+// as (1) such tasks with the entries of its rows to rows before the run
+// (independent rows: those are final), then, chain by chain of kChainRows run
+// rows, (2) a dense chain with the entries to the previous chain and among
+// its own rows, solved in registers, and beside it (3) tasks that subtract
+// the previous chain's columns from the run's later rows.  Every
+// row of a run so subtracts its run entries one by one in column order.
+//
+// The tasks between two barriers (a phase) go to the solver waves, longest
+// first to the least loaded; successive chains go to successive waves, so
+// that a chain's weights are read while the one before is solved.
 constexpr int32_t kColRunRows = 8, kColRunMin = 8;
+constexpr int64_t kPieceBytes = 8192;
+// a slot of the ring also holds the words a wave reads past its program
+constexpr int32_t kSegMinBytes = 2048;
 
-int64_t csc_segment_bytes(int64_t ncol, int64_t nnz, int64_t ts) {
-  return pad16h(kEllHeaderBytes + pad8h(2 * ncol) + pad8h(2 * (ncol + 1)) + pad8h(2 * nnz) + ts * nnz);
+// Bytes of a segment: six slots beside the largest x (FP64) in lds bytes, so
+// that several are in flight, but large enough for tasks for every wave
+// (kSegBytes to three times that).
+int64_t segment_bytes(int32_t max_m, size_t lds) {
+  return std::max<int64_t>(kSegBytes, std::min<int64_t>(3 * kSegBytes, ((int64_t)lds - 8 * max_m - 16384) / 6));
 }
 
 template <typename TS>
-int32_t pack_sweep_runs(const Sweep &sw, std::vector<uint8_t> &data, std::vector<int32_t> &lvb,
-                        std::vector<int32_t> &lev, int32_t &K, int32_t &max_level_bytes, int64_t &offset) {
-  const int64_t ts = sizeof(TS);
-  K = 0;
-  for (int32_t t = 0; t < sw.nrows; ++t) K = std::max(K, sw.rp[t + 1] - sw.rp[t]);
-  offset = (int64_t)data.size();
+struct SegPacker {
+  static constexpr int64_t ts = sizeof(TS);
+  const Sweep &sw;
+  std::vector<uint8_t> &data;
+  std::vector<int32_t> &lvb, &lev;
+  std::vector<RfMap> *map;
+  const int64_t ebase, offset, seg_bytes;
+  int32_t &max_bytes;
+  bool ok = true;          // every task fits its word
   int64_t pos = 0;
-  int32_t rows_done = 0, nseg = 0;
-  lvb.push_back(0);
-  lev.push_back(0);
-  auto close_seg = [&](int64_t size, int32_t rows) {
-    max_level_bytes = std::max<int32_t>(max_level_bytes, (int32_t)size);
+  int32_t nseg = 0;
+
+  struct Task {
+    int type = 0, shape = 0, cost = 0, phase = 0, owner = -1;   // shape: word bits from 14 on
+    std::vector<uint8_t> bytes;
+    std::vector<RfMap> map;   // offsets from the task's start
+  };
+  std::vector<Task> open;   // tasks of the segment being filled
+  int64_t open_bytes = 0;
+  int phase = 0;            // of the next task, from 0 in each segment
+  bool phase_used = false;
+  int chains = 0;
+
+  void next_phase() {
+    if (phase_used) ++phase;
+    phase_used = false;
+  }
+  void add(Task &&t) {
+    const int64_t words = 4 * (kSegWaves + 1) * (int64_t)(open.size() + 2);
+    if (!open.empty() && (open_bytes + (int64_t)t.bytes.size() + words > seg_bytes || phase >= 60)) flush();
+    t.phase = phase;
+    t.bytes.resize(pad16h((int64_t)t.bytes.size()), 0);
+    open_bytes += (int64_t)t.bytes.size();
+    open.push_back(std::move(t));
+    phase_used = true;
+  }
+  void flush() {
+    if (open.empty()) return;
+    const int nph = open.back().phase + 1;
+    // waves of the tasks
+    std::vector<std::vector<size_t>> mine(kSegWaves);
+    for (int ph = 0; ph < nph; ++ph) {
+      int64_t load[kSegWaves] = {};
+      std::vector<size_t> o;
+      for (size_t k = 0; k < open.size(); ++k)
+        if (open[k].phase == ph) o.push_back(k);
+      std::stable_sort(o.begin(), o.end(), [&](size_t x, size_t y) {
+        return (open[x].owner >= 0 ? 1 << 20 : open[x].cost) > (open[y].owner >= 0 ? 1 << 20 : open[y].cost);
+      });
+      for (size_t k : o) {
+        int w = open[k].owner;
+        if (w < 0) w = (int)(std::min_element(load, load + kSegWaves) - load);
+        // (the wave of the next chain reads that one's weights meanwhile)
+        if (open[k].owner >= 0) load[(w + 1) % kSegWaves] += 300;
+        load[w] += open[k].cost;
+        mine[w].push_back(k);
+      }
+    }
+    size_t longest = 0;
+    for (const auto &v : mine) longest = std::max(longest, v.size() + 1);
+    const int64_t prog = pad16h(4 * kSegWaves * (int64_t)longest), flat = kSegHeaderBytes + prog;
+    const int64_t body = flat + pad16h(4 * (int64_t)(open.size() + 1)), size = body + open_bytes;
+    ok = ok && longest <= 64 && open.size() < 64 && size / 16 < 4096;
+    const int64_t at = offset + pos;
+    data.resize(at + size, 0);
+    uint16_t *hdr = reinterpret_cast<uint16_t *>(data.data() + at);
+    hdr[0] = (uint16_t)(nph - 1);
+    hdr[1] = (uint16_t)longest;
+    hdr[2] = (uint16_t)(flat / 16);
+    hdr[3] = (uint16_t)(open.size() + 1);
+    std::vector<int64_t> place(open.size());
+    int64_t o = body;
+    for (size_t k = 0; k < open.size(); ++k) {
+      place[k] = o;
+      std::memcpy(data.data() + at + o, open[k].bytes.data(), open[k].bytes.size());
+      if (map)
+        for (RfMap m : open[k].map) {
+          m.off += at + o;
+          map->push_back(m);
+        }
+      o += (int64_t)open[k].bytes.size();
+    }
+    auto word = [&](size_t k, int bars) {
+      return (uint32_t)(place[k] / 16) | (uint32_t)open[k].type << 12 | (uint32_t)open[k].shape << 14 |
+             (uint32_t)bars << 26;
+    };
+    uint32_t *w = reinterpret_cast<uint32_t *>(data.data() + at + kSegHeaderBytes);
+    for (int v = 0; v < kSegWaves; ++v) {
+      int ph = 0;
+      size_t i = 0;
+      for (size_t k : mine[v]) {
+        w[kSegWaves * i++ + v] = word(k, open[k].phase - ph);
+        ph = open[k].phase;
+      }
+      w[kSegWaves * i + v] = (uint32_t)(nph - 1 - ph) << 26;   // kSegEnd
+    }
+    uint32_t *f = reinterpret_cast<uint32_t *>(data.data() + at + flat);
+    for (size_t k = 0; k < open.size(); ++k) f[k] = word(k, 0);
+    max_bytes = std::max<int32_t>(max_bytes, (int32_t)size);
     pos += size;
     lvb.push_back((int32_t)pos);
-    rows_done += rows;
-    lev.push_back(rows_done);
-    ++nseg;
+    lev.push_back(++nseg);
+    open.clear();
+    open_bytes = 0;
+    phase = 0;
+    phase_used = false;
+  }
+
+  using Entries = std::vector<std::pair<int32_t, int32_t>>;   // column (or place), sweep entry
+  struct PieceRow {
+    int32_t t;
+    Entries e;
   };
-  // one ELL piece: rows at sweep positions tl[a .. b), entries kept by keep(column)
-  auto emit_ell = [&](const std::vector<int32_t> &tl, size_t a, size_t b, const std::vector<char> *skip) {
-    const int32_t L = (int32_t)(b - a);
-    auto keep = [&](int32_t col) { return !skip || !(*skip)[col]; };
-    int32_t Kl = 0;
-    for (size_t j = a; j < b; ++j) {
-      int32_t c = 0;
-      for (int32_t e = sw.rp[tl[j]]; e < sw.rp[tl[j] + 1]; ++e) c += keep(sw.ci[e]);
-      Kl = std::max(Kl, c);
-    }
-    const int64_t o_sc = kEllHeaderBytes + pad8h(2 * L), o_ci = o_sc + pad8h(ts * L);
-    const int64_t o_w = o_ci + pad8h(2 * (int64_t)Kl * L);
-    const int64_t size = ell_segment_bytes(L, Kl, ts);
-    data.resize(offset + pos + size, 0);
-    uint8_t *base = data.data() + offset + pos;
-    *reinterpret_cast<int32_t *>(base) = Kl;
-    uint16_t *rows = reinterpret_cast<uint16_t *>(base + kEllHeaderBytes);
-    TS *sc = reinterpret_cast<TS *>(base + o_sc);
-    uint16_t *ci = reinterpret_cast<uint16_t *>(base + o_ci);
-    TS *w = reinterpret_cast<TS *>(base + o_w);
-    for (int32_t j = 0; j < L; ++j) {
-      const int32_t t = tl[a + j], row = sw.rows[t];
-      rows[j] = (uint16_t)row;
-      sc[j] = (TS)sw.sc[t];
-      int32_t e2 = 0;
-      for (int32_t e = sw.rp[t]; e < sw.rp[t + 1]; ++e) {
-        if (!keep(sw.ci[e])) continue;
-        ci[(int64_t)e2 * L + j] = (uint16_t)sw.ci[e];
-        w[(int64_t)e2 * L + j] = (TS)sw.w[e];
-        ++e2;
-      }
-      for (; e2 < Kl; ++e2) {
-        ci[(int64_t)e2 * L + j] = (uint16_t)row;
-        w[(int64_t)e2 * L + j] = (TS)0;
+  static int64_t lane_entries(const PieceRow &p, int lg) { return ((int64_t)p.e.size() + (1 << lg) - 1) >> lg; }
+  // one task: rows [a, b) of pr, 1 << lg lanes each (update: rows scaled before)
+  void ell(const std::vector<const PieceRow *> &pr, size_t a, size_t b, int lg, bool update) {
+    const int64_t G = 1 << lg, n = (int64_t)(b - a);
+    int64_t nu = 0;
+    for (size_t j = a; j < b; ++j) nu = std::max(nu, lane_entries(*pr[j], lg));
+    const int64_t B = nu <= 2 ? 2 : 4, nb = std::max<int64_t>(1, (nu + B - 1) / B);
+    ok = ok && nu < 512;
+    const int64_t o_sc = 256, o_ci = o_sc + 64 * ts, o_w = o_ci + 128 * B * nb;
+    Task t;
+    t.type = kSegEll;
+    t.shape = lg | (int)nu << 3;
+    t.cost = 280 + 30 * (int)nu + 20 * lg;
+    t.bytes.assign(o_w + 64 * ts * B * nb, 0);
+    uint32_t *rows = reinterpret_cast<uint32_t *>(t.bytes.data());
+    TS *sc = reinterpret_cast<TS *>(t.bytes.data() + o_sc), *w = reinterpret_cast<TS *>(t.bytes.data() + o_w);
+    uint16_t *ci = reinterpret_cast<uint16_t *>(t.bytes.data() + o_ci);
+    for (int64_t l = 0; l < 64; ++l) {
+      const int64_t j = std::min(l / G, n - 1), g = l % G;
+      const bool real = l / G < n;
+      const PieceRow &p = *pr[a + j];
+      const int32_t row = sw.rows[p.t];
+      rows[l] = (uint32_t)row | (real && g == 0 ? 0 : 0x80000000u);
+      sc[l] = update ? (TS)1 : (TS)sw.sc[p.t];
+      if (map && real && !update) t.map.push_back(rf_scale(sw, p.t, o_sc + ts * l, ebase));
+      for (int64_t v = 0; v < nb * B; ++v) {
+        const int64_t e = v * G + g, at = ((v / B) * 64 + l) * B + v % B;
+        const bool in = real && e < (int64_t)p.e.size();
+        ci[at] = (uint16_t)(in ? p.e[e].first : row);
+        w[at] = in ? (TS)sw.w[p.e[e].second] : (TS)0;
+        if (map && in) t.map.push_back(rf_weight(sw, p.t, p.e[e].second, o_w + ts * at, ebase));
       }
     }
-    close_seg(size, L);
-  };
-  // ELL pieces of at most kEllLevelBytes (or one row) over tl
-  auto emit_ell_cut = [&](const std::vector<int32_t> &tl, const std::vector<char> *skip) {
+    add(std::move(t));
+  }
+  // Independent rows: pieces of at most kPieceBytes (or one row), each with
+  // its lanes per row; the rows with the same number of lanes fill tasks
+  // together, longest first (a row's arithmetic does not depend on the
+  // others in its task).
+  void pieces(const std::vector<PieceRow> &pr, int lanes) {
+    auto bytes = [&](int64_t L, int64_t K) {
+      return pad16h(16 + pad8h(2 * L) + pad8h(ts * L) + pad8h(2 * K * L) + ts * K * L);
+    };
+    std::vector<const PieceRow *> by[7];
+    auto piece = [&](size_t a, size_t b, int64_t K) {
+      const int64_t L = (int64_t)(b - a);
+      const int lg = lanes >= 0 ? lanes
+                                : std::min(K <= 4 ? 0 : (K <= 16 ? 2 : (K <= 64 ? 4 : 6)),
+                                           L >= 64 ? 0 : (L >= 16 ? 2 : (L >= 4 ? 4 : 6)));
+      for (size_t j = a; j < b; ++j) by[lg].push_back(&pr[j]);
+    };
     size_t a = 0;
-    int32_t Kc = 0;
-    for (size_t j = 0; j < tl.size(); ++j) {
-      int32_t c = 0;
-      for (int32_t e = sw.rp[tl[j]]; e < sw.rp[tl[j] + 1]; ++e) c += !skip || !(*skip)[sw.ci[e]];
-      const int32_t K2 = std::max(Kc, c);
-      if (j > a && ell_segment_bytes((int64_t)(j + 1 - a), K2, ts) > kEllLevelBytes) {
-        emit_ell(tl, a, j, skip);
+    int64_t Kc = 0;
+    for (size_t j = 0; j < pr.size(); ++j) {
+      const int64_t c = (int64_t)pr[j].e.size(), K2 = std::max(Kc, c);
+      if (j > a && bytes((int64_t)(j + 1 - a), K2) > kPieceBytes) {
+        piece(a, j, Kc);
         a = j;
         Kc = c;
       } else {
         Kc = K2;
       }
     }
-    if (a < tl.size()) emit_ell(tl, a, tl.size(), skip);
-  };
-  std::vector<char> in_run(std::max(sw.nrows, 1), 0);
-  std::vector<int32_t> tl;
-  int32_t l = 0;
-  while (l < sw.nlev) {
-    int32_t r = l;
-    while (r < sw.nlev && sw.levptr[r + 1] - sw.levptr[r] <= kColRunRows) ++r;
-    if (r - l >= kColRunMin) {
-      // run of levels [l, r): pre pieces, then column segments
-      const int32_t t0 = sw.levptr[l], t1 = sw.levptr[r];
-      tl.clear();
-      for (int32_t t = t0; t < t1; ++t) {
-        tl.push_back(t);
-        in_run[sw.rows[t]] = 1;
-      }
-      emit_ell_cut(tl, &in_run);
-      // columns: run row k (position t0 + k) -> (later run row, weight)
-      const int32_t R = t1 - t0;
-      std::vector<int32_t> cpos(std::max(sw.nrows, 1), -1);
-      for (int32_t k = 0; k < R; ++k) cpos[sw.rows[t0 + k]] = k;
-      std::vector<std::vector<std::pair<uint16_t, double>>> col(R);
-      for (int32_t k = 0; k < R; ++k) {
-        const int32_t t = t0 + k;
-        for (int32_t e = sw.rp[t]; e < sw.rp[t + 1]; ++e)
-          if (in_run[sw.ci[e]]) col[cpos[sw.ci[e]]].emplace_back((uint16_t)sw.rows[t], sw.w[e]);
-      }
-      int32_t c0 = 0;
-      while (c0 < R) {
-        int32_t c1 = c0 + 1;
-        int64_t nnz = (int64_t)col[c0].size();
-        while (c1 < R && csc_segment_bytes(c1 + 1 - c0, nnz + (int64_t)col[c1].size(), ts) <= kEllLevelBytes) {
-          nnz += (int64_t)col[c1].size();
-          ++c1;
-        }
-        const int32_t nc = c1 - c0;
-        const int64_t size = csc_segment_bytes(nc, nnz, ts);
-        data.resize(offset + pos + size, 0);
-        uint8_t *base = data.data() + offset + pos;
-        int32_t *hdr = reinterpret_cast<int32_t *>(base);
-        hdr[0] = -2;
-        hdr[1] = nc;
-        hdr[2] = (int32_t)nnz;
-        uint16_t *crow = reinterpret_cast<uint16_t *>(base + kEllHeaderBytes);
-        uint16_t *cptr = reinterpret_cast<uint16_t *>(base + kEllHeaderBytes + pad8h(2 * nc));
-        uint16_t *tgt = reinterpret_cast<uint16_t *>(base + kEllHeaderBytes + pad8h(2 * nc) + pad8h(2 * (nc + 1)));
-        TS *w = reinterpret_cast<TS *>(base + kEllHeaderBytes + pad8h(2 * nc) + pad8h(2 * (nc + 1)) + pad8h(2 * nnz));
-        int32_t e = 0;
-        for (int32_t c = c0; c < c1; ++c) {
-          crow[c - c0] = (uint16_t)sw.rows[t0 + c];
-          cptr[c - c0] = (uint16_t)e;
-          for (const auto &pr : col[c]) {
-            tgt[e] = pr.first;
-            w[e] = (TS)pr.second;
-            ++e;
-          }
-        }
-        cptr[nc] = (uint16_t)e;
-        close_seg(size, nc);
-        c0 = c1;
-      }
-      for (int32_t t = t0; t < t1; ++t) in_run[sw.rows[t]] = 0;
-      l = r;
-      continue;
+    if (a < pr.size()) piece(a, pr.size(), Kc);
+    for (int lg = 6; lg >= 0; --lg) {
+      std::vector<const PieceRow *> &v = by[lg];
+      std::stable_sort(v.begin(), v.end(), [&](const PieceRow *x, const PieceRow *y) {
+        return lane_entries(*x, lg) > lane_entries(*y, lg);
+      });
+      const size_t per = (size_t)64 >> lg;
+      for (size_t j = 0; j < v.size(); j += per) ell(v, j, std::min(j + per, v.size()), lg, false);
     }
-    // ordinary levels [l, max(r, l + 1))
-    const int32_t le = std::max(r, l + 1);
-    for (int32_t ll = l; ll < le; ++ll) {
-      tl.clear();
-      for (int32_t t = sw.levptr[ll]; t < sw.levptr[ll + 1]; ++t) tl.push_back(t);
-      emit_ell_cut(tl, nullptr);
-    }
-    l = le;
   }
-  return nseg;
-}
+  // the levels [l, r) as a run
+  void run(int32_t l, int32_t r, std::vector<int32_t> &place) {
+    const int32_t t0 = sw.levptr[l], R = sw.levptr[r] - t0;
+    for (int32_t k = 0; k < R; ++k) place[sw.rows[t0 + k]] = k;
+    std::vector<PieceRow> pr(R);
+    std::vector<Entries> in(R);   // entries to run rows: place, in column order
+    for (int32_t k = 0; k < R; ++k) {
+      pr[k].t = t0 + k;
+      for (int32_t e = sw.rp[t0 + k]; e < sw.rp[t0 + k + 1]; ++e) {
+        const int32_t c = place[sw.ci[e]];
+        (c < 0 ? pr[k].e : in[k]).emplace_back(c < 0 ? sw.ci[e] : c, e);
+      }
+      std::sort(in[k].begin(), in[k].end());
+    }
+    next_phase();
+    pieces(pr, -1);
+    // the entries of run row k to run rows [lo, hi)
+    auto range = [&](int32_t k, int32_t lo, int32_t hi) {
+      const auto a = std::lower_bound(in[k].begin(), in[k].end(), std::make_pair(lo, INT32_MIN));
+      return std::make_pair(a, std::lower_bound(a, in[k].end(), std::make_pair(hi, INT32_MIN)));
+    };
+    // one of them into a task's weights
+    auto put = [&](Task &t, int64_t o_w, int64_t at, int32_t k, int32_t e) {
+      reinterpret_cast<TS *>(t.bytes.data() + o_w)[at] = (TS)sw.w[e];
+      if (map) t.map.push_back(rf_weight(sw, t0 + k, e, o_w + ts * at, ebase));
+    };
+    for (int32_t c0 = 0; c0 < R; c0 += kChainRows) {
+      const int32_t n = std::min(kChainRows, R - c0), p0 = c0 - kChainRows;
+      const bool lead = c0 > 0;
+      next_phase();
+      Task t;
+      t.type = kSegChain;
+      t.owner = chains++ % kSegWaves;
+      t.shape = (lead ? 1 : 0) | n << 3;
+      t.cost = 750;
+      const int64_t o_w = 4 * kChainRows;
+      t.bytes.assign(o_w + ts * kChainRows * kChainRows * (lead ? 2 : 1), 0);
+      {
+        uint16_t *rows = reinterpret_cast<uint16_t *>(t.bytes.data());
+        for (int32_t i = 0; i < kChainRows; ++i) {
+          rows[i] = (uint16_t)sw.rows[t0 + c0 + std::min(i, n - 1)];
+          rows[kChainRows + i] = (uint16_t)sw.rows[t0 + (lead ? p0 : c0) + (lead ? i : 0)];
+        }
+      }
+      for (int32_t i = 0; i < n; ++i) {
+        const auto own = range(c0 + i, c0, c0 + n), prev = range(c0 + i, p0, c0);
+        for (auto it = own.first; it != own.second; ++it)
+          put(t, o_w, (int64_t)(it->first - c0) * kChainRows + i, c0 + i, it->second);
+        if (lead)
+          for (auto it = prev.first; it != prev.second; ++it)
+            put(t, o_w, (int64_t)(kChainRows + it->first - p0) * kChainRows + i, c0 + i, it->second);
+      }
+      add(std::move(t));
+      if (!lead) continue;
+      // the run's rows past this chain that use the previous one, longest
+      // first: dense panels where a row has more than half of the columns,
+      // else one lane per row with its entries
+      std::vector<std::pair<int32_t, int32_t>> user;   // -entries, row
+      for (int32_t k = c0 + n; k < R; ++k) {
+        const auto q = range(k, p0, c0);
+        if (q.first != q.second) user.emplace_back(-(int32_t)(q.second - q.first), k);
+      }
+      std::sort(user.begin(), user.end());
+      for (size_t u0 = 0; u0 < user.size(); u0 += 64) {
+        const int32_t nr = (int32_t)std::min<size_t>(64, user.size() - u0);
+        Task q;
+        if (-user[u0].first <= kChainRows / 2) {
+          std::vector<PieceRow> up(nr);
+          std::vector<const PieceRow *> v;
+          for (int32_t j = 0; j < nr; ++j) {
+            const auto r = range(user[u0 + j].second, p0, c0);
+            up[j].t = t0 + user[u0 + j].second;
+            for (auto it = r.first; it != r.second; ++it) up[j].e.emplace_back(sw.rows[t0 + it->first], it->second);
+            v.push_back(&up[j]);
+          }
+          ell(v, 0, v.size(), 0, true);
+          continue;
+        }
+        q.type = kSegPanel;
+        q.shape = nr << 3;
+        q.cost = 450;
+        const int64_t o_p = 2 * kChainRows + 2 * 64;
+        q.bytes.assign(o_p + ts * kChainRows * nr, 0);
+        uint16_t *cols = reinterpret_cast<uint16_t *>(q.bytes.data()), *prow = cols + kChainRows;
+        for (int32_t c = 0; c < kChainRows; ++c) cols[c] = (uint16_t)sw.rows[t0 + p0 + c];
+        for (int32_t j = 0; j < nr; ++j) {
+          const int32_t k = user[u0 + j].second;
+          prow[j] = (uint16_t)sw.rows[t0 + k];
+          const auto r = range(k, p0, c0);
+          for (auto it = r.first; it != r.second; ++it) put(q, o_p, (int64_t)(it->first - p0) * nr + j, k, it->second);
+        }
+        add(std::move(q));
+      }
+    }
+    for (int32_t k = 0; k < R; ++k) place[sw.rows[t0 + k]] = -1;
+  }
+  // lanes: log2 of the lanes per row, -1: by the piece; runs: with chains
+  void pack(int lanes, bool runs) {
+    lvb.push_back(0);
+    lev.push_back(0);
+    std::vector<int32_t> place(std::max(sw.nrows, 1), -1);
+    std::vector<PieceRow> pr;
+    for (int32_t l = 0; l < sw.nlev;) {
+      int32_t r = l;
+      while (r < sw.nlev && sw.levptr[r + 1] - sw.levptr[r] <= kColRunRows) ++r;
+      if (runs && r - l >= kColRunMin) {
+        run(l, r, place);
+        l = r;
+        continue;
+      }
+      for (const int32_t le = std::max(r, l + 1); l < le; ++l) {
+        pr.clear();
+        for (int32_t t = sw.levptr[l]; t < sw.levptr[l + 1]; ++t) {
+          pr.push_back(PieceRow{t, {}});
+          for (int32_t e = sw.rp[t]; e < sw.rp[t + 1]; ++e) pr.back().e.emplace_back(sw.ci[e], e);
+        }
+        next_phase();
+        pieces(pr, lanes);
+      }
+    }
+    flush();
+  }
+};
 
 // Sizes of a packed block set that the B kernel's LDS plan needs.
 struct BSizes {
@@ -1634,11 +1744,12 @@ int32_t packed_width(const std::vector<Block> &blocks) {
 }
 
 // Pack and upload a set of diagonal blocks (factor sweeps, E and E^T rows)
-// for the B kernel.  Every local index in the packed data is an LDS
-// position (lds_positions); B.xpos maps a block's rows to them, or is null
+// for the B kernel (lds: the bytes a workgroup should get by with).  Every
+// local index in the packed data is an LDS position (lds_positions); B.xpos maps a block's rows to them, or is null
 // when every block keeps the identity.
 template <typename TS>
-bool pack_blocks(DevPool &P, const std::vector<Block> &blocks, BlockArrays<TS> &B, BSizes &sz, RfMaps *rm) {
+bool pack_blocks(DevPool &P, const std::vector<Block> &blocks, BlockArrays<TS> &B, BSizes &sz, RfMaps *rm,
+                 size_t lds) {
   const int32_t nbk = (int32_t)blocks.size();
   std::vector<BlockDesc> desc(nbk);
   std::vector<int32_t> lev, lvb;
@@ -1650,6 +1761,44 @@ bool pack_blocks(DevPool &P, const std::vector<Block> &blocks, BlockArrays<TS> &
   int32_t max_m = 0, max_lev = 0, max_lb = 0, max_K = 0;
   bool ok = true;
   const int32_t Kfix = packed_width(blocks);
+  int32_t widest_m = 0;
+  for (const Block &b : blocks) widest_m = std::max(widest_m, b.m);
+  const int64_t seg_bytes = segment_bytes(widest_m, lds);
+  // sweeps of any width are packed block by block on several threads
+  struct Packed {
+    std::vector<uint8_t> data;
+    std::vector<int32_t> lvb[2], lev[2];
+    std::vector<RfMap> map;
+    int64_t off[2] = {0, 0};
+    int32_t nseg[2] = {0, 0}, max_bytes = 0;
+    bool ok = true;
+  };
+  std::vector<Packed> packed(Kfix == 0 ? nbk : 0);
+  if (Kfix == 0) {
+    std::atomic<int32_t> next{0};
+    auto worker = [&]() {
+      for (int32_t q = next++; q < nbk; q = next++) {
+        const Block &b = blocks[q];
+        Packed &k = packed[q];
+        for (int f = 0; f < 2; ++f) {
+          k.off[f] = (int64_t)k.data.size();
+          SegPacker<TS> pk{f ? b.bwd : b.fwd, k.data, k.lvb[f], k.lev[f], rm ? &k.map : nullptr, b.f_base, k.off[f],
+                           seg_bytes, k.max_bytes};
+          pk.pack(b.lanes, b.runs);
+          k.nseg[f] = pk.nseg;
+          k.ok = k.ok && pk.ok;
+        }
+      }
+    };
+    const int32_t nth = (int32_t)std::max(1u, std::min<unsigned>(std::thread::hardware_concurrency(), 16u));
+    std::vector<std::thread> pool;
+    for (int32_t t = 1; t < std::min(nth, nbk); ++t) pool.emplace_back(worker);
+    worker();
+    for (auto &th : pool) th.join();
+    size_t total = 0;
+    for (const Packed &k : packed) total += k.data.size();
+    data.reserve(total);
+  }
   for (int32_t q = 0; q < nbk; ++q) {
     const Block &b0 = blocks[q];
     BlockDesc &d = desc[q];
@@ -1668,30 +1817,41 @@ bool pack_blocks(DevPool &P, const std::vector<Block> &blocks, BlockArrays<TS> &
     d.m = b.m;
     if (b.m > 65535) ok = false;   // uint16 local indices
     max_m = std::max(max_m, b.m);
-    if (Kfix == 0 && !rm) {
-      // ELL form with near-chains by columns
-      d.f_lev = (int32_t)lev.size();
-      d.f_lvb = (int32_t)lvb.size();
-      d.f_nlev = pack_sweep_runs<TS>(b.fwd, data, lvb, lev, d.f_K, max_lb, d.f_data);
-      d.b_lev = (int32_t)lev.size();
-      d.b_lvb = (int32_t)lvb.size();
-      d.b_nlev = pack_sweep_runs<TS>(b.bwd, data, lvb, lev, d.b_K, max_lb, d.b_data);
-      max_lev = std::max({max_lev, d.f_nlev, d.b_nlev});
-    } else {
-      const Sweep fs = split_levels(b.fwd, Kfix, sizeof(TS)), bs = split_levels(b.bwd, Kfix, sizeof(TS));
-      max_lev = std::max({max_lev, fs.nlev, bs.nlev});
-      d.f_nlev = fs.nlev;
-      d.f_lev = (int32_t)lev.size();
-      lev.insert(lev.end(), fs.levptr.begin(), fs.levptr.end());
-      if (fs.levptr.empty()) lev.push_back(0);
-      d.f_lvb = (int32_t)lvb.size();
-      pack_sweep<TS>(fs, Kfix, data, lvb, d.f_K, max_lb, d.f_data, rm ? &rm->bdata : nullptr, b.f_base);
-      d.b_nlev = bs.nlev;
-      d.b_lev = (int32_t)lev.size();
-      lev.insert(lev.end(), bs.levptr.begin(), bs.levptr.end());
-      if (bs.levptr.empty()) lev.push_back(0);
-      d.b_lvb = (int32_t)lvb.size();
-      pack_sweep<TS>(bs, Kfix, data, lvb, d.b_K, max_lb, d.b_data, rm ? &rm->bdata : nullptr, b.f_base);
+    for (const Sweep *sp : {&b.fwd, &b.bwd}) {
+      const bool f = sp == &b.fwd;
+      int32_t &nlev = f ? d.f_nlev : d.b_nlev, &K = f ? d.f_K : d.b_K;
+      int64_t &off = f ? d.f_data : d.b_data;
+      (f ? d.f_lev : d.b_lev) = (int32_t)lev.size();
+      (f ? d.f_lvb : d.b_lvb) = (int32_t)lvb.size();
+      K = Kfix;
+      if (Kfix > 0) {
+        const Sweep cut = split_levels(*sp, Kfix);
+        nlev = cut.nlev;
+        lev.insert(lev.end(), cut.levptr.begin(), cut.levptr.end());
+        if (cut.levptr.empty()) lev.push_back(0);
+        pack_sweep<TS>(cut, Kfix, data, lvb, max_lb, off, rm ? &rm->bdata : nullptr, b.f_base);
+      } else {
+        const Packed &k = packed[q];
+        const int w = f ? 0 : 1;
+        for (int32_t t = 0; t < sp->nrows; ++t) K = std::max(K, sp->rp[t + 1] - sp->rp[t]);
+        if (f) {
+          if (rm)
+            for (RfMap m : k.map) {
+              m.off += (int64_t)data.size();
+              rm->bdata.push_back(m);
+            }
+          d.b_data = (int64_t)data.size() + k.off[1];
+          off = (int64_t)data.size();
+          data.insert(data.end(), k.data.begin(), k.data.end());
+        }
+        lvb.insert(lvb.end(), k.lvb[w].begin(), k.lvb[w].end());
+        lev.insert(lev.end(), k.lev[w].begin(), k.lev[w].end());
+        nlev = k.nseg[w];
+        max_lb = std::max(max_lb, k.max_bytes);
+        ok = ok && k.ok;
+        if (!f) std::vector<uint8_t>().swap(packed[q].data);
+      }
+      max_lev = std::max(max_lev, nlev);
     }
     max_K = std::max({max_K, d.f_K, d.b_K});
     // E rows as ELL (width = longest row)
@@ -1729,6 +1889,7 @@ bool pack_blocks(DevPool &P, const std::vector<Block> &blocks, BlockArrays<TS> &
                                  (int32_t)b.t_src[b.t_ptr[i] + e], 0, 0, RF_SRC});
       }
   }
+  if (Kfix == 0) max_lb = std::max(max_lb, kSegMinBytes);
   if (data.empty()) data.resize(16, 0);
   B.desc = P.upload(desc);
   B.lev = P.upload(lev);
@@ -1793,7 +1954,7 @@ template <typename TS>
 void upload_blocks(slr_ctx *c, const HostSetup &H, BlockArrays<TS> &B, SweepArrays<TS> &Cf, SweepArrays<TS> &Cb,
                    bool &ok, RfMaps *rm) {
   BSizes sz;
-  ok = pack_blocks<TS>(c->pool, H.blocks, B, sz, rm);
+  ok = pack_blocks<TS>(c->pool, H.blocks, B, sz, rm, c->lds_limit);
   // work estimate of one item of a subdomain for the persistent schedule:
   // its dependent levels, plus its entries (staging)
   c->b_cost_h.clear();
@@ -1824,7 +1985,7 @@ template <typename TS>
 bool upload_inner(slr_ctx *c, const HostSetup &H, BlockArrays<TS> &B, SweepArrays<TS> &Cf, SweepArrays<TS> &Cb) {
   slr_ctx::Inner &I = c->ml;
   BSizes sz;
-  bool ok = pack_blocks<TS>(c->pool, H.c1blocks, B, sz, nullptr);
+  bool ok = pack_blocks<TS>(c->pool, H.c1blocks, B, sz, nullptr, c->lds_limit / 4);
   I.max_m = sz.max_m;
   I.max_lev = sz.max_lev;
   I.max_level_bytes = sz.max_level_bytes;
@@ -1945,7 +2106,10 @@ int lowrank_done(slr_ctx *c, double t1, hipStream_t st) {
 // followed by the bytes.  Device arrays are written in a fixed order (the
 // list below), so import can allocate and fill them in that order and
 // point the same fields at them.
-constexpr char kSetupMagic[8] = {'S', 'L', 'R', 'S', 'E', 'T', 'v', '2'};
+// Version 2 held the sweeps of any row width in another form
+// (convert_streams); everything else is the same.
+constexpr char kSetupMagic[8] = {'S', 'L', 'R', 'S', 'E', 'T', 'v', '3'};
+constexpr char kSetupMagic2[8] = {'S', 'L', 'R', 'S', 'E', 'T', 'v', '2'};
 
 uint64_t fnv1a(const uint8_t *p, size_t n) {
   uint64_t h = 0xcbf29ce484222325ull;
@@ -2023,6 +2187,128 @@ size_t pool_block_bytes(const DevPool &P, const void *ptr) {
   return 0;
 }
 
+// One sweep of a version 2 stream of any row width, as it was packed: level
+// pieces with a header int32 K >= 0 (16 bytes), rows uint16[L], sc TS[L],
+// ci uint16[K L] (entry e of row j at e L + j), w TS[K L], each section padded
+// to 8 bytes; and column segments with a header int32 -2, columns, entries,
+// then crow uint16[columns], cptr uint16[columns + 1], tgt uint16[entries],
+// w TS[entries] (row tgt uses row crow).  Rows and the entries of a row come
+// in the order in which they are solved and subtracted.
+template <typename TS>
+bool sweep_of_v2(const uint8_t *data, const int32_t *lvb, const int32_t *lev, int32_t nlev, int32_t m, Sweep &sw) {
+  const int64_t ts = sizeof(TS);
+  std::vector<int32_t> order, place(std::max(m, 1), -1);
+  std::vector<std::vector<std::pair<int32_t, double>>> ent;
+  std::vector<double> sc;
+  for (int32_t l = 0; l < nlev; ++l) {
+    const uint8_t *seg = data + lvb[l];
+    const int32_t *hdr = reinterpret_cast<const int32_t *>(seg);
+    const int64_t size = lvb[l + 1] - lvb[l], K = hdr[0];
+    if (K == -2) {
+      const int64_t nc = hdr[1], nnz = hdr[2];
+      const int64_t o_ptr = 16 + pad8h(2 * nc), o_tgt = o_ptr + pad8h(2 * (nc + 1)), o_w = o_tgt + pad8h(2 * nnz);
+      if (nc < 0 || nnz < 0 || o_w + ts * nnz > size) return false;
+      const uint16_t *crow = reinterpret_cast<const uint16_t *>(seg + 16);
+      const uint16_t *cptr = reinterpret_cast<const uint16_t *>(seg + o_ptr);
+      const uint16_t *tgt = reinterpret_cast<const uint16_t *>(seg + o_tgt);
+      const TS *w = reinterpret_cast<const TS *>(seg + o_w);
+      for (int64_t c = 0; c < nc; ++c)
+        for (int64_t e = cptr[c]; e < cptr[c + 1]; ++e) {
+          if (e >= nnz || tgt[e] >= m || crow[c] >= m || place[tgt[e]] < 0 || place[crow[c]] < 0) return false;
+          ent[place[tgt[e]]].emplace_back(crow[c], (double)w[e]);
+        }
+      continue;
+    }
+    const int64_t L = lev[l + 1] - lev[l], o_sc = 16 + pad8h(2 * L), o_ci = o_sc + pad8h(ts * L);
+    const int64_t o_w = o_ci + pad8h(2 * K * L);
+    if (K < 0 || L < 0 || o_w + ts * K * L > size) return false;
+    const uint16_t *rows = reinterpret_cast<const uint16_t *>(seg + 16);
+    const TS *s = reinterpret_cast<const TS *>(seg + o_sc), *w = reinterpret_cast<const TS *>(seg + o_w);
+    const uint16_t *ci = reinterpret_cast<const uint16_t *>(seg + o_ci);
+    for (int64_t j = 0; j < L; ++j) {
+      if (rows[j] >= m || place[rows[j]] >= 0) return false;
+      place[rows[j]] = (int32_t)order.size();
+      order.push_back(rows[j]);
+      sc.push_back((double)s[j]);
+      ent.emplace_back();
+      for (int64_t e = 0; e < K; ++e)   // padding points at the row itself
+        if (ci[e * L + j] != rows[j]) ent.back().emplace_back(ci[e * L + j], (double)w[e * L + j]);
+    }
+  }
+  sw = Sweep();
+  sw.nrows = (int32_t)order.size();
+  if (sw.nrows != m) return false;
+  std::vector<int32_t> depth(std::max(m, 1), 0);   // by place
+  for (int32_t k = 0; k < m; ++k)
+    for (const auto &pr : ent[k]) {
+      if (pr.first >= m || place[pr.first] < 0 || place[pr.first] >= k) return false;
+      depth[k] = std::max(depth[k], depth[place[pr.first]] + 1);
+    }
+  for (int32_t k = 0; k < m; ++k) sw.nlev = std::max(sw.nlev, depth[k] + 1);
+  sw.levptr.assign(sw.nlev + 1, 0);
+  for (int32_t k = 0; k < m; ++k) ++sw.levptr[depth[k] + 1];
+  for (int32_t l = 0; l < sw.nlev; ++l) sw.levptr[l + 1] += sw.levptr[l];
+  std::vector<int32_t> at(sw.levptr.begin(), sw.levptr.end()), by(m);
+  for (int32_t k = 0; k < m; ++k) by[at[depth[k]]++] = k;
+  sw.rp.assign(1, 0);
+  for (int32_t k : by) {
+    sw.rows.push_back(order[k]);
+    sw.sc.push_back(sc[k]);
+    for (const auto &pr : ent[k]) {
+      sw.ci.push_back(pr.first);
+      sw.w.push_back(pr.second);
+    }
+    sw.rp.push_back((int32_t)sw.ci.size());
+  }
+  return true;
+}
+
+// The streams of a version 2 context (rows of any width) packed anew.
+template <typename TS>
+bool convert_streams(slr_ctx *c, BlockArrays<TS> &B) {
+  auto host = [&](const void *p, auto &v) {
+    using T = typename std::remove_reference_t<decltype(v)>::value_type;
+    v.resize(pool_block_bytes(c->pool, p) / sizeof(T));
+    return p && hipMemcpy(v.data(), p, v.size() * sizeof(T), hipMemcpyDeviceToHost) == hipSuccess;
+  };
+  std::vector<BlockDesc> desc;
+  std::vector<int32_t> lev, lvb, nlevs, nlvb;
+  std::vector<uint8_t> data, ndata;
+  if (!host(B.desc, desc) || !host(B.lev, lev) || !host(B.lvb, lvb) || !host(B.data, data)) return false;
+  int32_t max_lev = 0, max_lb = kSegMinBytes;
+  const int64_t seg_bytes = segment_bytes(B.max_m, c->lds_limit);
+  for (BlockDesc &d : desc)
+    for (const bool f : {true, false}) {
+      int32_t &nlev = f ? d.f_nlev : d.b_nlev, &ol = f ? d.f_lev : d.b_lev, &ob = f ? d.f_lvb : d.b_lvb;
+      int64_t &od = f ? d.f_data : d.b_data;
+      if (nlev < 0 || ol < 0 || ob < 0 || od < 0 || (size_t)ol + nlev + 1 > lev.size() ||
+          (size_t)ob + nlev + 1 > lvb.size() || od + lvb[(size_t)ob + nlev] > (int64_t)data.size())
+        return false;
+      for (int32_t l = 0; l < nlev; ++l)
+        if (lvb[ob + l] < 0 || lvb[ob + l + 1] < lvb[ob + l] + 16) return false;
+      Sweep sw;
+      if (!sweep_of_v2<TS>(data.data() + od, &lvb[ob], &lev[ol], nlev, d.m, sw)) return false;
+      ol = (int32_t)nlevs.size();
+      ob = (int32_t)nlvb.size();
+      od = (int64_t)ndata.size();
+      SegPacker<TS> pk{sw, ndata, nlvb, nlevs, nullptr, 0, od, seg_bytes, max_lb};
+      pk.pack(-1, true);
+      if (!pk.ok) return false;
+      nlev = pk.nseg;
+      max_lev = std::max(max_lev, nlev);
+    }
+  if (ndata.empty()) ndata.resize(16, 0);
+  B.desc = c->pool.upload(desc);
+  B.lev = c->pool.upload(nlevs);
+  B.lvb = c->pool.upload(nlvb);
+  B.data = c->pool.upload(ndata);
+  B.max_lev = c->b_max_lev = max_lev;
+  B.max_level_bytes = c->b_max_level_bytes = max_lb;
+  c->b_data_bytes = (int64_t)ndata.size();
+  int32_t R = 0, stage = 0;
+  return B.desc && B.lev && B.lvb && B.data && b_lds_plan(c, 1, 8, R, stage);
+}
+
 int export_setup(const slr_ctx *cc, std::vector<uint8_t> &blob) {
   slr_ctx *c = const_cast<slr_ctx *>(cc);
   Writer w;
@@ -2074,7 +2360,8 @@ int export_setup(const slr_ctx *cc, std::vector<uint8_t> &blob) {
 }
 
 int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out) {
-  if (bytes < 24 || std::memcmp(buf, kSetupMagic, 8) != 0) return fail(SLR_ERR_ARG, "not a serialised SLR setup");
+  const bool v2 = bytes >= 24 && std::memcmp(buf, kSetupMagic2, 8) == 0;
+  if (bytes < 24 || (!v2 && std::memcmp(buf, kSetupMagic, 8) != 0)) return fail(SLR_ERR_ARG, "not a serialised SLR setup");
   uint64_t len = 0, h = 0;
   std::memcpy(&len, buf + 8, 8);
   if (len != bytes - 24) return fail(SLR_ERR_ARG, "serialised setup: length mismatch");
@@ -2126,6 +2413,9 @@ int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out
   if (pool_block_bytes(c->pool, c->perm) != sizeof(int64_t) * (size_t)std::max<int64_t>(c->n, 1) ||
       pool_block_bytes(c->pool, c->a_v) != sizeof(double) * (size_t)std::max<int64_t>(c->nnz_a, 1))
     return bad("array sizes do not match the problem");
+  if (v2 && !(c->fact_prec == SLR_FP64 ? c->Bd.pack_K > 0 || convert_streams(c, c->Bd)
+                                       : c->Bf.pack_K > 0 || convert_streams(c, c->Bf)))
+    return bad("sweep streams");
   c->perm_h.resize(c->n);
   if (c->n) HIPCHK(hipMemcpy(c->perm_h.data(), c->perm, sizeof(int64_t) * c->n, hipMemcpyDeviceToHost));
   std::vector<double> U;

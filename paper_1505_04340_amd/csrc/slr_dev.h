@@ -22,22 +22,32 @@ namespace slr {
 // entries:
 //     idx   int32[L][KR]       [row, c_0, .., c_{K-1}, pad]  local indices
 //     wts   TS[L][KR]          [sc, w_0, .., w_{K-1}, pad]   scale, weights
-// Any width, ELL form, K = the widest row of the level (levels are cut into
-// pieces of at most kEllLevelBytes on the host):
-//     K     int32 (in a 16-byte header)
-//     rows  uint16[L]          local row index
-//     sc    TS[L]              row scale
-//     ci    uint16[K*L]        column of entry e of row j at [e*L + j]
-//     w     TS[K*L]            pre-divided weight, same layout
-// each ELL section padded to 8 bytes and the segment to 16.  A run of
-// consecutive levels of at most a few rows (a near-chain) is packed as ELL
-// pieces holding the run's rows with their entries to rows before the run,
-// then column segments (header int32 -2, ncol, nnz):
-//     crow  uint16[ncol]       the run row finished by column c
-//     cptr  uint16[ncol + 1]   its entries [cptr[c], cptr[c+1])
-//     tgt   uint16[nnz]        a later run row that uses it
-//     w     TS[nnz]            that row's pre-divided weight
-// solved column by column (x[tgt] -= w x[crow]).
+// Any width (pack_K == 0): a "level" is a segment of at most about kSegBytes
+// (unless one task is larger), a list of tasks with a program for each of
+// the kSegWaves solver waves:
+//     uint16    barriers inside the segment, words of the longest program,
+//               place / 16 of the flat program, its words
+//     uint32    words[i][wave]   programs, then the flat one of all tasks
+//     tasks     16-byte aligned, offsets / 16 from the segment's start
+// A word (SegWord): bits 0-11 the task's place / 16, 12-13 its type, 14-16
+// and 17-25 its shape, 26-31 the barriers to pass before it.
+//   kSegEnd
+//   kSegEll    14-16 log2 of the lanes per row, 17-25 nu entries per lane
+//     rows  uint32[64]         local row of each lane (bit 31: not stored)
+//     sc    TS[64]             row scale
+//     ci    uint16[nb][64][B]  columns; B = 2 (nu <= 2) or 4, nb = ceil(nu / B)
+//     w     TS[nb][64][B]      pre-divided weights
+//     (lane g of a row's G lanes holds its entries g, g + G, ..; padding has
+//     w = 0 and the row itself)
+//   kSegChain  14 with entries to the previous chain, 17-25 R rows
+//     rows  uint16[16]         the chain's rows in solve order (the last repeated)
+//     prev  uint16[16]         the previous chain's
+//     w     TS[16][16]         [c][i]: weight of row c in row i
+//     v     TS[16][16]         that of the previous chain's row c
+//   kSegPanel  17-25 R rows
+//     cols  uint16[16]         rows of a finished chain
+//     rows  uint16[64]
+//     w     TS[16][R]          [c][j]: weight of row c in row j
 struct BlockDesc {
   int32_t m0, m;                   // interior range in the internal order
   int32_t f_nlev, f_K, f_lev, f_lvb;   // forward sweep: levels, width, levptr / lvb offsets
@@ -97,9 +107,10 @@ struct BlockArrays {
 // past the end of x's rows: one 16-byte slot per lane of a wave, so that
 // such stores from one instruction never hit the same bank.
 constexpr int kStageDummyBytes = 1024;
-// ELL level segments: header bytes and the largest piece of a level
-constexpr int kEllHeaderBytes = 16;
-constexpr int kEllLevelBytes = 8192;
+// Segments of sweeps of any width: solver waves, stager waves, columns from which each wave
+// takes columns of its own, bytes aimed at, task types
+constexpr int kSegWaves = 6, kSegStagers = 2, kSegColumns = 4, kSegHeaderBytes = 16, kSegBytes = 8192, kChainRows = 16;
+constexpr int kSegEnd = 0, kSegEll = 1, kSegChain = 2, kSegPanel = 3;
 
 // Entries of a fixed-width row record: the row plus K columns, rounded up to
 // a multiple of 4 so that records are whole 16-byte vectors.
@@ -110,6 +121,10 @@ __host__ __device__ constexpr int rec_width(int K) { return (K + 1 + 3) & ~3; }
 // sub-levels of at most 64 * rec_passes(K) rows (rows of one level are
 // independent, so any split of a level is a valid schedule).
 __host__ __device__ constexpr int rec_passes(int K) { return K <= 2 ? 4 : (K == 3 ? 3 : 2); }
+
+// Most threads of a B kernel workgroup; sweeps of any width always take the
+// solver waves their programs are laid out for and the stagers.
+__host__ __device__ constexpr int bsolve_threads(int pack_K) { return pack_K > 0 ? 1024 : 64 * (kSegWaves + kSegStagers); }
 
 struct BArgs {
   const double *f = nullptr;  int64_t ldf = 0;  double a_f = 0.0;

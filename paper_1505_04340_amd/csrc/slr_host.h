@@ -50,6 +50,10 @@ struct Block {            // one subdomain
   std::vector<int64_t> e_src, t_src;        // entries of the input CSR behind e_val / t_val
   int64_t nnz_L = 0;
   int64_t f_base = 0;                       // first entry of this block's factor in the global B factor
+  // sweeps of any row width: log2 of the lanes per row (-1: by the rows) and
+  // whether near-chains are solved as such
+  int32_t lanes = -1;
+  bool runs = true;
 };
 
 // Lower factor of a block-diagonal matrix for a device refactorisation:

@@ -149,117 +149,389 @@ __host__ __device__ constexpr int pad16(int x) { return (x + 15) & ~15; }
 // with its own column count: its subdomain's size), in a region of
 // max_m * R + 1 values.
 //
-// One level of an ELL-packed sweep (any row width K) for one column, solved
-// by one wave.  Rows of width K <= 8: one lane per row, entries subtracted
-// in order.  Longer rows: G lanes per row (G = 4, 16, 64 for K <= 32, 128,
-// beyond), lane g summing the entries g, g + G, ..., the partial sums added
-// by a butterfly inside the group, then x_row = sc x_row - sum.  A group is
-// active or idle as a whole, so its butterfly never mixes in an idle lane.
-template <typename TS, typename TC, int G>
-__device__ __forceinline__ void ell_rows_group(const uint16_t *rows, const TS *sc, const uint16_t *ci, const TS *w,
-                                               int L, int K, TC *xc, int lane) {
-  const int g = lane % G;
-  for (int j = lane / G; j < L; j += 64 / G) {
-    TC part = 0;
-    // four entries per lane in flight: index and weight loads, then the
-    // gathers, then the sums in entry order (entries past the row end are
-    // clamped to its last one and not added, so no lane takes another path)
-    for (int e0 = g; e0 < K; e0 += 4 * G) {
-      int c[4];
-      TC wv[4], xv[4];
+// Sum over aligned groups of 1 << lg lanes (lg 0, 2, 3, 4 or 6), valid in each
+// group's first lane, halves first (the order of a butterfly from the widest
+// step down): half and row swaps, then row rotations and quad permutations.
+// Register moves only: a shuffle through the LDS crossbar would cost an LDS
+// round trip per step.  All 64 lanes must be active.
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  int p[2];
+  __builtin_memcpy(p, &v, 8);
+  p[0] = __builtin_amdgcn_update_dpp(0, p[0], CTRL, 0xF, 0xF, true);
+  p[1] = __builtin_amdgcn_update_dpp(0, p[1], CTRL, 0xF, 0xF, true);
+  __builtin_memcpy(&v, p, 8);
+  return v;
+}
+// v of the lane's own 16-lane row pair (HALF false) or wave half (true), and
+// of the other one, added
+template <bool HALF, typename TC>
+__device__ __forceinline__ TC swap_add(TC v) {
+  constexpr int N = sizeof(TC) / 4;
+  uint32_t p[N], q[N];
+  __builtin_memcpy(p, &v, sizeof(TC));
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = min(e0 + u * G, K - 1);
-        c[u] = ci[e * L + j];
-        wv[u] = cvt<TC>(w[e * L + j]);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) xv[u] = xc[c[u]];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (e0 + u * G < K) part += wv[u] * xv[u];
-    }
-#pragma unroll
-    for (int o = G / 2; o > 0; o >>= 1) part += __shfl_xor(part, o, G);
-    if (g == 0) {
-      const int row = rows[j];
-      xc[row] = cvt<TC>(sc[j]) * xc[row] - part;
-    }
+  for (int i = 0; i < N; ++i) {
+    const auto t = HALF ? __builtin_amdgcn_permlane32_swap(p[i], p[i], false, false)
+                        : __builtin_amdgcn_permlane16_swap(p[i], p[i], false, false);
+    p[i] = t[0];
+    q[i] = t[1];
   }
+  TC a, b;
+  __builtin_memcpy(&a, p, sizeof(TC));
+  __builtin_memcpy(&b, q, sizeof(TC));
+  return a + b;
+}
+template <typename TC>
+__device__ __forceinline__ TC group_sum(TC v, int lg) {
+  if (lg >= 6) {
+    v = swap_add<true>(v);
+    v = swap_add<false>(v);
+  }
+  if (lg >= 4) v += dpp_move<0x128>(v);   // row_ror 8
+  if (lg >= 3) v += dpp_move<0x104>(v);   // row_shl 4
+  if (lg >= 2) {
+    v += dpp_move<0x4E>(v);               // quad_perm 2,3,0,1
+    v += dpp_move<0xB1>(v);               // quad_perm 1,0,3,2
+  }
+  return v;
 }
 
-// A column segment of a near-chain run (marker -2 in the header, then the
-// column count and entry count): for each column in order, its row's value
-// is final; every later run row that uses it subtracts weight x value.
-// Within a column each target row appears once, so the lanes' updates
-// never collide, and the wave's program order carries them to the next
-// column.
-template <typename TS, typename TC>
-__device__ __forceinline__ void csc_segment_wave(const uint8_t *seg, TC *xc, int lane) {
-  const int32_t *hdr = reinterpret_cast<const int32_t *>(seg);
-  const int nc = hdr[1], nnz = hdr[2];
-  const uint16_t *crow = reinterpret_cast<const uint16_t *>(seg + kEllHeaderBytes);
-  const uint16_t *cptr = reinterpret_cast<const uint16_t *>(seg + kEllHeaderBytes + pad8(2 * nc));
-  const uint16_t *tgt = reinterpret_cast<const uint16_t *>(seg + kEllHeaderBytes + pad8(2 * nc) + pad8(2 * (nc + 1)));
-  const TS *w = reinterpret_cast<const TS *>(seg + kEllHeaderBytes + pad8(2 * nc) + pad8(2 * (nc + 1)) +
-                                             pad8(2 * nnz));
-  // the next column's row and entry range are read one column ahead
-  int r = crow[0], e0 = cptr[0], e1 = cptr[1];
-  for (int c = 0; c < nc; ++c) {
-    const int rn = crow[min(c + 1, nc - 1)], en = cptr[min(c + 2, nc)];
-    const TC xj = xc[r];
-    for (int e = e0 + lane; e < e1; e += 64) {
-      const int i = tgt[e];
-      xc[i] -= cvt<TC>(w[e]) * xj;
-    }
-    r = rn;
-    e0 = e1;
-    e1 = en;
-  }
+// Barrier of the workgroup that orders LDS accesses only (global loads and
+// direct global-to-LDS copies in flight are not waited for).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <typename TS, typename TC>
-__device__ __forceinline__ void ell_level_wave(const uint8_t *seg, int L, TC *xc, int lane) {
-  const int K = *reinterpret_cast<const int32_t *>(seg);
-  if (K < 0) {
-    csc_segment_wave<TS, TC>(seg, xc, lane);
-    return;
-  }
-  const uint8_t *base = seg + kEllHeaderBytes;
-  const uint16_t *rows = reinterpret_cast<const uint16_t *>(base);
-  const int o_sc = pad8(2 * L);
-  const TS *sc = reinterpret_cast<const TS *>(base + o_sc);
-  const int o_ci = o_sc + pad8((int)sizeof(TS) * L);
-  const uint16_t *ci = reinterpret_cast<const uint16_t *>(base + o_ci);
-  const TS *w = reinterpret_cast<const TS *>(base + o_ci + pad8(2 * K * L));
-  // lanes per row: enough that each lane holds few entries, no more than
-  // the level's rows leave room for
-  const int gk = K <= 4 ? 1 : (K <= 16 ? 4 : (K <= 64 ? 16 : 64));
-  const int gl = L >= 64 ? 1 : (L >= 16 ? 4 : (L >= 4 ? 16 : 64));
-  const int G = min(gk, gl);
-  if (G == 1) {
-    for (int j = lane; j < L; j += 64) {
-      const int row = rows[j];
-      TC acc = cvt<TC>(sc[j]) * xc[row];
-      for (int e = 0; e < K; ++e) acc -= cvt<TC>(w[e * L + j]) * xc[(int)ci[e * L + j]];
-      xc[row] = acc;
-    }
-  } else if (G == 4) {
-    ell_rows_group<TS, TC, 4>(rows, sc, ci, w, L, K, xc, lane);
-  } else if (G == 16) {
-    ell_rows_group<TS, TC, 16>(rows, sc, ci, w, L, K, xc, lane);
+// LDS by byte address (32-bit arithmetic and LDS instructions also where the
+// compiler does not see where a pointer came from).
+template <typename T>
+__device__ __forceinline__ T lds_get(uint32_t at) {
+  return *(__attribute__((address_space(3))) const T *)(uintptr_t)at;
+}
+template <typename T>
+__device__ __forceinline__ void lds_put(uint32_t at, T v) {
+  *(__attribute__((address_space(3))) T *)(uintptr_t)at = v;
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
+}
+// N consecutive values at an address that is a multiple of their size (16
+// bytes at most)
+template <int N, typename T>
+__device__ __forceinline__ void lds_vec(uint32_t at, T *v) {
+  if constexpr (N * sizeof(T) <= 16) {
+    typedef T V __attribute__((ext_vector_type(N)));
+    const V t = lds_get<V>(at);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = t[i];
   } else {
-    ell_rows_group<TS, TC, 64>(rows, sc, ci, w, L, K, xc, lane);
+    lds_vec<N / 2, T>(at, v);
+    lds_vec<N / 2, T>(at + N / 2 * sizeof(T), v + N / 2);
   }
 }
 
-// Levels [l0, l1) of an ELL-packed sweep staged at sbase, for one column, by
-// one wave with no barrier between levels: a wave's LDS accesses take
-// effect in program order, and a level reads only rows of earlier levels.
+// v of lane C of each 16-lane row, in the row's every lane
+template <int C>
+__device__ __forceinline__ float row_value(float v) {
+  return dpp_move<0x150 + C>(v);   // row_newbcast
+}
+template <int C>
+__device__ __forceinline__ double row_value(double v) {
+  return dpp_move<0x150 + C>(v);
+}
+
+// x minus the sum over columns C .. 15 of weight times the value y of that
+// column (held by lane C of each row), in column order.  EXACT: a weight of
+// zero adds nothing even where the value is not finite.
+template <int C, typename TS, typename TC, bool EXACT>
+__device__ __forceinline__ TC sub_columns(TC x, TC y, const TS (&w)[16]) {
+  if constexpr (C < 16) {
+    const TC t = x - cvt<TC>(w[C]) * row_value<C>(y);
+    return sub_columns<C + 1, TS, TC, EXACT>(EXACT && w[C] == (TS)0 ? x : t, y, w);
+  } else {
+    return x;
+  }
+}
+// the same with the row's own values as columns: a triangular solve
+template <int C, typename TS, typename TC, bool EXACT>
+__device__ __forceinline__ TC sub_chain(TC x, const TS (&w)[15]) {
+  if constexpr (C < 15) {
+    const TC t = x - cvt<TC>(w[C]) * row_value<C>(x);
+    return sub_chain<C + 1, TS, TC, EXACT>(EXACT && w[C] == (TS)0 ? x : t, w);
+  } else {
+    return x;
+  }
+}
+
+template <typename TC>
+__device__ __forceinline__ bool any_not_finite(TC v) {
+  return __ballot(!(v - v == (TC)0)) != 0;
+}
+
+// The columns of x that a wave works on: r0, r0 + dr, .. < Rg, column r at
+// LDS address xs + r * cs.
+struct SegCols {
+  uint32_t xs, cs;
+  int r0, dr, Rg;
+};
+
+// n barriers (LDS only): before a task that uses earlier tasks' results
+__device__ __forceinline__ void pass_barriers(int n) {
+  if (n > 0) {
+    lds_barrier();
+    for (int i = 1; i < n; ++i) __builtin_amdgcn_s_barrier();
+  }
+}
+
+// ELL task at LDS address `at` (layout with BlockDesc): the rows of 64 lanes,
+// 1 << lg lanes per row, nu entries a lane in nb blocks of B.  x_row =
+// sc x_row minus the row's weighted columns, subtracted in entry order by a
+// single lane, or summed by the lanes of the row first.  What does not depend
+// on x is read before the barriers; up to NB blocks are in flight (a block
+// waits for its columns and then for their values, two LDS latencies).
+template <typename TS, typename TC, int B, int NB>
+__device__ __forceinline__ void ell_task(uint32_t at, int lg, int nb, int nbar, const SegCols &cols, int lane) {
+  constexpr uint32_t es = sizeof(TC), ts = sizeof(TS);
+  const uint32_t raw = lds_get<uint32_t>(at + 4 * lane);
+  const TS sc = lds_get<TS>(at + 256 + ts * lane);
+  const uint32_t o_ix = at + 256 + 64 * ts + 2 * B * lane;
+  const uint32_t o_w = at + 256 + 64 * ts + (uint32_t)nb * 128 * B + ts * B * lane;
+  TS w[NB][B];
+  uint32_t c[NB][B];
+  // blocks k .. k + NB - 1 (past the end: the last one)
+  auto read = [&](int k, uint32_t xc) {
+    uint32_t ix[NB][B / 2];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const uint32_t kq = NB == 1 ? k : min(k + q, nb - 1);
+      lds_vec<B / 2, uint32_t>(o_ix + 128 * B * kq, ix[q]);
+      lds_vec<B, TS>(o_w + 64 * ts * B * kq, w[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+#pragma unroll
+      for (int u = 0; u < B; ++u) c[q][u] = xc + es * ((u & 1) ? ix[q][u / 2] >> 16 : ix[q][u / 2] & 0xFFFFu);
+  };
+  uint32_t xc = cols.xs + cols.r0 * cols.cs;
+  read(0, xc);
+  uint32_t row = xc + es * (raw & 0x7FFFFFFFu);
+  pass_barriers(nbar);
+  for (int r = cols.r0; r < cols.Rg; r += cols.dr) {
+    const TC xd = lds_get<TC>(row);
+    TC acc = 0;
+    for (int k = 0;;) {
+      TC xv[NB][B];
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int u = 0; u < B; ++u) xv[q][u] = lds_get<TC>(c[q][u]);
+      // single lane: minus the row's value
+      if (k == 0 && lg == 0) acc = -(cvt<TC>(sc) * xd);
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        if (q == 0 || k + q < nb) {
+#pragma unroll
+          for (int u = 0; u < B; ++u) acc += cvt<TC>(w[q][u]) * xv[q][u];
+        }
+      k += NB;
+      if (k >= nb) break;
+      read(k, xc);
+    }
+    if (lg > 0)
+      acc = cvt<TC>(sc) * xd - group_sum(acc, lg);
+    else
+      acc = -acc;
+    if ((int32_t)raw >= 0) lds_put<TC>(row, acc);
+    if (r + cols.dr >= cols.Rg) break;
+    const uint32_t d = cols.cs * cols.dr;
+    xc += d;
+    row += d;
+    if (nb > NB) {
+      read(0, xc);
+    } else {
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int u = 0; u < B; ++u) c[q][u] += d;
+    }
+  }
+}
+
+// Chain task: 16 rows (R of them real) in solve order whose entries to rows
+// before the previous chain are already subtracted.  Lane i of each 16-lane
+// row holds chain row i; the entries to the previous chain's rows (lead) and
+// then those among its own are subtracted column by column, the column's
+// value going to the row's lanes by a register broadcast.  The dependent
+// step is a broadcast and a fused multiply-add, 19 cycles; through the LDS (a
+// read of the value, an update and its store) a row took 370.  Zero weights
+// are multiplied, not masked; should a value not be finite, the chain is
+// solved again under masks.
 template <typename TS, typename TC>
-__device__ __forceinline__ void solve_staged_ell(const uint8_t *sbase, const int32_t *lev, const int32_t *lvb, int l0,
-                                                 int l1, TC *xc, int lane) {
-  for (int l = l0; l < l1; ++l) ell_level_wave<TS, TC>(sbase + (lvb[l] - lvb[l0]), lev[l + 1] - lev[l], xc, lane);
+__device__ __forceinline__ void chain_task(uint32_t at, int R, bool lead, int nbar, const SegCols &cols, int lane) {
+  constexpr uint32_t es = sizeof(TC), ts = sizeof(TS);
+  const int i = lane & 15;
+  const uint32_t row = es * lds_get<uint16_t>(at + 2 * i), prev = es * lds_get<uint16_t>(at + 32 + 2 * i);
+  const uint32_t wt = at + 64 + ts * i;
+  TS w[15], v[16];
+#pragma unroll
+  for (int c = 0; c < 15; ++c) w[c] = lds_get<TS>(wt + 16 * ts * c);
+  if (lead) {
+#pragma unroll
+    for (int c = 0; c < 16; ++c) v[c] = lds_get<TS>(wt + 16 * ts * (16 + c));
+  }
+  pass_barriers(nbar);
+  for (int r = cols.r0; r < cols.Rg; r += cols.dr) {
+    const uint32_t xc = cols.xs + r * cols.cs;
+    const TC x0 = lds_get<TC>(xc + row);
+    TC x = x0, y = 0;
+    if (lead) {
+      y = lds_get<TC>(xc + prev);
+      x = sub_columns<0, TS, TC, false>(x, y, v);
+    }
+    x = sub_chain<0, TS, TC, false>(x, w);
+    if (any_not_finite(x) || any_not_finite(y)) {
+      x = lead ? sub_columns<0, TS, TC, true>(x0, y, v) : x0;
+      x = sub_chain<0, TS, TC, true>(x, w);
+    }
+    if (lane < R) lds_put<TC>(xc + row, x);
+  }
+}
+
+// Panel task: up to 64 rows, one per lane, subtract their entries to the 16
+// rows of a finished chain in column order (dense columns of weights; see
+// chain_task for values that are not finite).
+template <typename TS, typename TC>
+__device__ __forceinline__ void panel_task(uint32_t at, int R, int nbar, const SegCols &cols, int lane) {
+  constexpr uint32_t es = sizeof(TC), ts = sizeof(TS);
+  const int j = min(lane, R - 1);
+  const uint32_t col = es * lds_get<uint16_t>(at + 2 * (lane & 15)), row = es * lds_get<uint16_t>(at + 32 + 2 * j);
+  uint32_t wt = at + 160 + ts * j;
+  TS w[16];
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    w[c] = lds_get<TS>(wt);
+    wt += ts * R;
+  }
+  pass_barriers(nbar);
+  for (int r = cols.r0; r < cols.Rg; r += cols.dr) {
+    const uint32_t xc = cols.xs + r * cols.cs;
+    const TC y = lds_get<TC>(xc + col), x0 = lds_get<TC>(xc + row);
+    TC x = sub_columns<0, TS, TC, false>(x0, y, w);
+    if (any_not_finite(y)) x = sub_columns<0, TS, TC, true>(x0, y, w);
+    if (lane < R) lds_put<TC>(xc + row, x);
+  }
+}
+
+// n segments of sweeps of any width, segment g in ring slot g % slots (of
+// slot bytes, from LDS address ring), for Rg columns (xs: address of x, cs:
+// bytes from column to column), by the waves wv < kSegWaves.  Few columns:
+// each wave runs its own program of a segment, the tasks of a level being
+// spread over the waves, with barriers where the programs have them.  From
+// kSegColumns columns on: each wave runs all tasks for columns of its own (a
+// wave's LDS accesses take effect in program order).  A barrier ends each
+// segment.  The host lays the programs out so that the waves decode one
+// word per task: a wave alone on its SIMD is bound by the instructions it
+// issues (five cycles each), and working shapes out of segment headers took
+// 2400 cycles a level.  Lane i holds word i of the program.  Not inlined: the
+// kernel's own values would push this loop's scalars out of their
+// registers.
+template <typename TS, typename TC>
+__device__ __attribute__((noinline)) void run_segments(uint32_t ring, int slot, int slots, int n, uint32_t xs,
+                                                       uint32_t cs, int Rg, int wv) {
+  const int lane = threadIdx.x & 63;
+  ring = __builtin_amdgcn_readfirstlane(ring);
+  slot = __builtin_amdgcn_readfirstlane(slot);
+  slots = __builtin_amdgcn_readfirstlane(slots);
+  n = __builtin_amdgcn_readfirstlane(n);
+  wv = __builtin_amdgcn_readfirstlane(wv);
+  SegCols cols;
+  cols.xs = __builtin_amdgcn_readfirstlane(xs);
+  cols.cs = __builtin_amdgcn_readfirstlane(cs);
+  cols.Rg = __builtin_amdgcn_readfirstlane(Rg);
+  const bool own = cols.Rg >= kSegColumns;
+  cols.r0 = own ? wv : 0;
+  cols.dr = own ? kSegWaves : 1;
+  uint32_t at = ring;
+  const uint32_t end = ring + slot * slots;
+  // a wave's program, or the flat one of all tasks (at most 64 words; the
+  // words past a program's end are never decoded)
+  auto program = [&](uint32_t p) {
+    return own ? lds_get<uint32_t>(p + 16u * lds_get<uint16_t>(p + 4) + 4 * lane)
+               : lds_get<uint32_t>(p + kSegHeaderBytes + 4 * (kSegWaves * lane + wv));
+  };
+  // four slots or more: a segment and the program of the one after it are
+  // read before the barrier that ends the segment before
+  const bool deep = slots > 3;
+  uint32_t words = program(at), ahead = 0;
+  int owed = 0;   // barriers to pass before the next task
+  for (int g = 0; g < n; ++g) {
+    uint32_t nxt = at + slot;
+    if (nxt == end) nxt = ring;
+    if (!deep && g > 0) {
+      pass_barriers(owed);
+      owed = 0;
+      words = program(at);
+    }
+    if (deep && g + 1 < n) ahead = program(nxt);
+    for (int i = 0;; ++i) {
+      const uint32_t wd = __builtin_amdgcn_readlane(words, i);
+      int nbar = (own ? 0 : (int)(wd >> 26)) + owed;
+      owed = 0;
+      // tell the others at once that the last task is done, unless the next
+      // one follows the very next barrier: then its reads come first
+      if (nbar > 1) {
+        lds_barrier();
+        --nbar;
+      }
+      const uint32_t t = at + (wd & 0xFFF) * 16;
+      const int type = (wd >> 12) & 3, lg = (wd >> 14) & 7, nu = (wd >> 17) & 0x1FF;
+      if (type == kSegEll) {
+        if (nu <= 2)
+          ell_task<TS, TC, 2, 1>(t, lg, 1, nbar, cols, lane);
+        else if (nu <= 4)
+          ell_task<TS, TC, 4, 1>(t, lg, 1, nbar, cols, lane);
+        else if (nu <= 8)
+          ell_task<TS, TC, 4, 2>(t, lg, 2, nbar, cols, lane);
+        else
+          ell_task<TS, TC, 4, 3>(t, lg, (nu + 3) >> 2, nbar, cols, lane);
+      } else if (type == kSegChain) {
+        chain_task<TS, TC>(t, nu, lg != 0, nbar, cols, lane);
+      } else if (type == kSegPanel) {
+        panel_task<TS, TC>(t, nu, nbar, cols, lane);
+      } else {
+        // all but the segment's last barrier, which the next task passes
+        pass_barriers(nbar);
+        owed = 1;
+        break;
+      }
+    }
+    words = ahead;
+    at = nxt;
+  }
+  pass_barriers(owed);
+}
+
+// Wait until at most k of the wave's loads are in flight (rounded down to a
+// multiple of 8).
+__device__ __forceinline__ void wait_loads(int k) {
+  // vmcnt in bits 3:0 and 15:14, nothing else waited for
+#define SLR_VM(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
+  if (k >= 56) __builtin_amdgcn_s_waitcnt(SLR_VM(56));
+  else if (k >= 48) __builtin_amdgcn_s_waitcnt(SLR_VM(48));
+  else if (k >= 40) __builtin_amdgcn_s_waitcnt(SLR_VM(40));
+  else if (k >= 32) __builtin_amdgcn_s_waitcnt(SLR_VM(32));
+  else if (k >= 24) __builtin_amdgcn_s_waitcnt(SLR_VM(24));
+  else if (k >= 16) __builtin_amdgcn_s_waitcnt(SLR_VM(16));
+  else if (k >= 8) __builtin_amdgcn_s_waitcnt(SLR_VM(8));
+  else __builtin_amdgcn_s_waitcnt(SLR_VM(0));
+#undef SLR_VM
 }
 
 // Copy nv 16-byte vectors from src into the LDS at dst with direct
@@ -267,8 +539,8 @@ __device__ __forceinline__ void solve_staged_ell(const uint8_t *sbase, const int
 // instruction (lane l's vector to the wave's base + 16 l), no registers
 // involved, so every load of the copy is in flight at once; lanes past the
 // end are inactive.  gt - lane and gn are multiples of 64.  The loads are
-// complete when this returns.
-__device__ __forceinline__ void stage_dma(const uint4 *src, int nv, uint4 *dst, int gt, int gn) {
+// complete when stage_dma returns (stage_issue: after a wait of the wave's).
+__device__ __forceinline__ void stage_issue(const uint4 *src, int nv, uint4 *dst, int gt, int gn) {
   const int lane = threadIdx.x & 63;
   for (int i0 = gt - lane; i0 < nv; i0 += gn) {
     const int i = i0 + lane;
@@ -276,7 +548,45 @@ __device__ __forceinline__ void stage_dma(const uint4 *src, int nv, uint4 *dst, 
       __builtin_amdgcn_global_load_lds(static_cast<const void *>(src + i),
                                        (__attribute__((address_space(3))) void *)(dst + i0), 16, 0, 0);
   }
+}
+__device__ __forceinline__ void stage_dma(const uint4 *src, int nv, uint4 *dst, int gt, int gn) {
+  stage_issue(src, nv, dst, gt, gn);
   __builtin_amdgcn_s_waitcnt(0);
+}
+template <int OFFSET>
+__device__ __forceinline__ void lds_load_16(const uint8_t *from, uint32_t to) {
+  __builtin_amdgcn_global_load_lds(static_cast<const void *>(from),
+                                   (__attribute__((address_space(3))) void *)(uintptr_t)to, 16, OFFSET, 0);
+}
+// The same copy by stager wave k of kSegStagers, from uniform addresses: four
+// loads at constant offsets (of the source and of the LDS alike) per
+// address.  Working an address and a lane test out for each load took 180
+// cycles a load, this 70 (what one wave's loads into the LDS take), and the
+// copy sets the pace of a solve.  Returns the wave's loads.
+__device__ __forceinline__ int stage_wave(const uint8_t *src, int nv, uint8_t *dst, int k, int lane) {
+  const uint64_t s0 = (uint64_t)(uintptr_t)src;
+  const uint8_t *s = reinterpret_cast<const uint8_t *>(
+      (uintptr_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(s0 & 0xFFFFFFFFu)) |
+                  (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(s0 >> 32)) << 32));
+  uint32_t d = __builtin_amdgcn_readfirstlane(lds_address(dst));
+  // 4 KiB in turn to the waves, the rest 1 KiB in turn
+  int n = 0, left = nv - 256 * k;
+  s += 4096 * k;
+  d += 4096 * k;
+  for (; left >= 256; left -= 256 * kSegStagers, n += 4, s += 4096 * kSegStagers, d += 4096 * kSegStagers) {
+    lds_load_16<0>(s + 16 * lane, d);
+    lds_load_16<1024>(s + 16 * lane, d);
+    lds_load_16<2048>(s + 16 * lane, d);
+    lds_load_16<3072>(s + 16 * lane, d);
+  }
+  if (left > 0) {
+    for (; left >= 64; left -= 64, ++n, s += 1024, d += 1024) lds_load_16<0>(s + 16 * lane, d);
+    if (left > 0) {
+      if (lane < left) lds_load_16<0>(s + 16 * lane, d);
+      ++n;
+    }
+  }
+  return n;
 }
 
 // Fixed-width row records (see BlockDesc): KR int32 indices [row, columns,
@@ -413,10 +723,9 @@ __device__ __forceinline__ void stage_first(const uint8_t *data, const int32_t *
   stage_dma(reinterpret_cast<const uint4 *>(data + b0), (b1 - b0) >> 4, reinterpret_cast<uint4 *>(stage), gt, gn);
 }
 
-// Both sweeps of one subdomain (fixed-width records for KE > 0, the ELL form
-// for KE == 0), one wave per right-hand side column (wave w < Rg solves
-// column w; its backward sweep follows its own forward sweep, so the
-// columns need no barrier between them).  The two
+// Both sweeps of one subdomain (fixed-width records), one wave per right-hand
+// side column (wave w < Rg solves column w; its backward sweep follows its
+// own forward sweep, so the columns need no barrier between them).  The two
 // packed streams are cut into chunks of consecutive levels of one sweep
 // (at most 64 levels, fitting half the stage) and double-buffered: while the
 // solver waves run chunk c from one half, the other waves copy chunk c + 1
@@ -465,12 +774,8 @@ __device__ __forceinline__ void sweeps_pipelined(const uint8_t *fdata, const int
     const int nl1 = more ? chunk_end(ns, nl0) : 0;
     uint8_t *cur = stage + b * half, *nxt = stage + (b ^ 1) * half;
     if (wv < Rg) {
-      for (int r = wv; r < Rg; r += nw) {
-        if constexpr (KE > 0)
-          solve_staged<TS, TC, KE>(cur, sw ? levb : levf, sw ? lvbb : lvbf, l0, l1, xs + r * XS, lane);
-        else
-          solve_staged_ell<TS, TC>(cur, sw ? levb : levf, sw ? lvbb : lvbf, l0, l1, xs + r * XS, lane);
-      }
+      for (int r = wv; r < Rg; r += nw)
+        solve_staged<TS, TC, KE>(cur, sw ? levb : levf, sw ? lvbb : lvbf, l0, l1, xs + r * XS, lane);
     } else if (more) {
       copy_chunk(ns, nl0, nl1, nxt, threadIdx.x - Rg * 64, blockDim.x - Rg * 64);
     }
@@ -487,12 +792,81 @@ __device__ __forceinline__ void sweeps_pipelined(const uint8_t *fdata, const int
   }
 }
 
+// Both sweeps of one subdomain with rows of any width: fn and then bn
+// segments through a ring of slots of slot bytes in the stage.  kSegWaves
+// waves solve; the last kSegStagers stage: while segment g is solved they copy
+// segment g + slots - 1 into the slot that segment g - 1 has left, and wait
+// for segment g + 3 only, so that several segments' copies overlap (two
+// halves in turn left one memory latency exposed per half).  The first
+// slots - 1 segments are there already (stage_segments, before a barrier).
+__device__ __forceinline__ void stage_segments(const uint8_t *fdata, const int32_t *lvbf, int fn, const uint8_t *bdata,
+                                               const int32_t *lvbb, int bn, uint8_t *stage, int slot, int slots,
+                                               int gt, int gn) {
+  for (int g = 0; g < min(slots - 1, fn + bn); ++g) {
+    const bool f = g < fn;
+    const int32_t *lvb = f ? lvbf + g : lvbb + g - fn;
+    stage_issue(reinterpret_cast<const uint4 *>((f ? fdata : bdata) + lvb[0]), (lvb[1] - lvb[0]) >> 4,
+                reinterpret_cast<uint4 *>(stage + g * slot), gt, gn);
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+}
+
+template <typename TS, typename TC>
+__device__ __forceinline__ void segments_pipelined(const uint8_t *fdata, const int32_t *lvbf, int fn,
+                                                   const uint8_t *bdata, const int32_t *lvbb, int bn, TC *xs, int XS,
+                                                   int Rg, uint8_t *stage, int slot, int slots) {
+  const int wv = threadIdx.x >> 6, n = fn + bn;
+  if (wv < kSegWaves) {
+    run_segments<TS, TC>(lds_address(stage), slot, slots, n, lds_address(xs), (uint32_t)sizeof(TC) * XS, Rg, wv);
+    return;
+  }
+  const int lane = threadIdx.x & 63, ahead = slots - 1, k = wv - kSegWaves;
+  // offset and 16-byte vectors of a segment, read one turn before their use
+  int off = 0, nv = 0;
+  auto place = [&](int g) {
+    nv = 0;
+    if (g >= n) return;
+    const int32_t *lvb = g < fn ? lvbf + g : lvbb + g - fn;
+    off = lvb[0];
+    nv = (lvb[1] - off) >> 4;
+  };
+  place(ahead);
+  // segments up to g + lag have landed when segment g ends (the first ahead
+  // ones before the start); loads of the later ones may be in flight: c[0]
+  // those of segment g + ahead, c[1] of the one before, ..
+  const int lag = ahead >= 3 ? 3 : 1;
+  int c[6] = {0, 0, 0, 0, 0, 0};
+  int at = 0, to = ahead % slots;
+  const bool own = Rg >= kSegColumns;
+  int nb = own ? 0 : *reinterpret_cast<const uint16_t *>(stage);
+  for (int g = 0; g < n; ++g) {
+    const int q = g + ahead, nvq = __builtin_amdgcn_readfirstlane(nv), bars = __builtin_amdgcn_readfirstlane(nb);
+    const uint8_t *src = (q < fn ? fdata : bdata) + off;
+    place(q + 1);
+    for (int i = 5; i > 0; --i) c[i] = c[i - 1];
+    c[0] = nvq > 0 ? stage_wave(src, nvq, stage + to * slot, k, lane) : 0;
+    for (int i = 0; i < bars; ++i) __builtin_amdgcn_s_barrier();
+    int flight = 0;
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+      if (i < ahead - lag) flight += c[i];
+    wait_loads(flight);
+    __builtin_amdgcn_s_barrier();
+    if (++at == slots) at = 0;
+    if (++to == slots) to = 0;
+    if (!own && g + 1 < n) nb = *reinterpret_cast<const uint16_t *>(stage + at * slot);
+  }
+}
+
 // One work item: subdomain sub and right-hand sides [cg * R, +Rg):
 // prologue (f, E y) into LDS, forward and backward
 // sweeps in LDS (or only one of them, by a.sweeps), then u and the E^T
 // epilogue.  KE > 0: every packed row has exactly KE entries (padding has
-// w = 0); KE == 0: the ELL form of any width.  Either way the sweeps run
-// one wave per column with double-buffered staging.
+// w = 0), the sweeps run one wave per column; KE == 0: segments of rows of
+// any width.  B solves of 27 boxes of 14^3 to 15^3 rows with ILDL^T factors
+// (tau = 1e-4, minimum degree, 6.0M sweep entries): 827 us with one wave per
+// column, barrier-free levels in two stage halves and chains through the LDS,
+// 346 us so; four exact factors of 961 rows: 296 -> 104 us.
 template <typename TS, typename TC, int KE, bool XP>
 __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArgs &a, int sub, int c0, int Rg,
                                             int XS) {
@@ -611,11 +985,16 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
   }
   // the sweeps this launch runs (a.sweeps: bit 0 forward, bit 1 backward)
   const int fn = (a.sweeps & 1) ? d.f_nlev : 0, bn = (a.sweeps & 2) ? d.b_nlev : 0;
+  // sweeps of any width: the ring of segments in the stage
+  const int slot = KE == 0 ? pad16(B.max_level_bytes) : 0, slots = KE == 0 ? min(a.stage_bytes / max(slot, 1), 8) : 0;
   {
-    // the upper half of the waves stages the first sweep chunk meanwhile
+    // the upper half of the waves stages the first part of the sweeps meanwhile
     if (tid >= nt / 2) {
       const int sw0 = fn > 0 ? 0 : 1;
-      if (sw0 == 0 || bn > 0)
+      if constexpr (KE == 0)
+        stage_segments(B.data + d.f_data, B.lvb + d.f_lvb, fn, B.data + d.b_data, B.lvb + d.b_lvb, bn, stage, slot,
+                       slots, tid - nt / 2, nt - nt / 2);
+      else if (sw0 == 0 || bn > 0)
         stage_first(B.data + (sw0 ? d.b_data : d.f_data), B.lvb + (sw0 ? d.b_lvb : d.f_lvb),
                     sw0 ? bn : fn, (a.stage_bytes >> 1) & ~15, stage, tid - nt / 2, nt - nt / 2);
     } else {
@@ -638,8 +1017,12 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
     }
     __syncthreads();
   }
-  sweeps_pipelined<TS, TC, KE>(B.data + d.f_data, levf, lvbf, fn, B.data + d.b_data, levb, lvbb, bn, xs, XS, Rg,
-                               stage, a.stage_bytes, true);
+  if constexpr (KE == 0)
+    segments_pipelined<TS, TC>(B.data + d.f_data, lvbf, fn, B.data + d.b_data, lvbb, bn, xs, XS, Rg, stage, slot,
+                               slots);
+  else
+    sweeps_pipelined<TS, TC, KE>(B.data + d.f_data, levf, lvbf, fn, B.data + d.b_data, levb, lvbb, bn, xs, XS, Rg,
+                                 stage, a.stage_bytes, true);
   if constexpr (XP) {
     if (a.u) {
       // each row's LDS position taken once for its Rg columns
@@ -682,7 +1065,7 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
 // group), or a persistent grid walking its scheduled items (the shared
 // memory is reused after a barrier between items).
 template <typename TS, typename TC, int KE, bool XP>
-__global__ void __launch_bounds__(1024) k_bsolve(BlockArrays<TS> B, BArgs a) {
+__global__ void __launch_bounds__(bsolve_threads(KE)) k_bsolve(BlockArrays<TS> B, BArgs a) {
   if (a.sched) {
     for (int it = a.sched_ptr[blockIdx.x]; it < a.sched_ptr[blockIdx.x + 1]; ++it) {
       const uint32_t item = (uint32_t)a.sched[it];
@@ -717,7 +1100,7 @@ void launch_bsolve_k(const BlockArrays<TS> &B, int32_t p, const BArgs &a, int32_
   hipLaunchKernelGGL((k_bsolve<TS, TC, KE, XP>), grid, dim3(threads), lds_bytes, st, B, a);
 }
 // the variant with LDS positions (B.xpos) exists for the fixed-width forms
-// only: the host keeps the row order for the ELL form
+// only: the host keeps the row order for rows of any width
 template <typename TS, typename TC, int KE>
 void launch_bsolve_x(const BlockArrays<TS> &B, int32_t p, const BArgs &a, int32_t threads, size_t lds_bytes,
                      hipStream_t st) {
