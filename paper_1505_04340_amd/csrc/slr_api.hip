@@ -12,6 +12,7 @@
 #include <cstring>
 #include <functional>
 #include <mutex>
+#include <numeric>
 #include <queue>
 #include <string>
 #include <thread>
@@ -271,6 +272,24 @@ struct slr_ctx {
   // row length of each sweep)
   int32_t cf_group = 1, cb_group = 1;
   bool c_two_level = false;     // interface schedules of <= 2 levels: one launch per sweep
+  // A deep interface schedule as a few launches of the B kernel: the leading
+  // t rows of the factor fall into independent blocks (connectors), the rest
+  // is one block; E rows of the leading blocks hold their entries in the
+  // rest, et the rest's entries in the leading rows (factor entries, not
+  // divided).  t == 0: one block only.
+  struct Deep {
+    bool on = false;
+    int64_t t = 0, s = 0;
+    struct Part {
+      int32_t nb = 0, max_m = 0, max_lev = 0, max_level_bytes = 0;
+      int64_t data_bytes = 0;
+      BlockArrays<double> Bd;
+      BlockArrays<float> Bf;
+    } lead, rest;
+    int64_t *et_rp = nullptr;
+    int32_t *et_ci = nullptr;
+    double *et_v = nullptr;
+  } cdeep;
   int32_t b_threads = 1024;
   int32_t n_cu = 256;           // compute units of the device
   int32_t b_max_m = 0, b_max_lev = 0, b_max_level_bytes = 0;
@@ -324,6 +343,7 @@ struct slr_ctx {
     std::vector<int32_t> f_lev_h, b_lev_h;
     int32_t f_nlev = 0, b_nlev = 0, f_group = 1, b_group = 1;
     bool one_wg = true;
+    Deep deep;                      // of C2's factor
     int64_t *ft_rp = nullptr;
     int32_t *ft_ci = nullptr;
     double *ft_v = nullptr;
@@ -611,7 +631,63 @@ int bsolve(slr_ctx *c, const BArgs &a, bool compute64, hipStream_t st) {
   return run_bsolve<float, float>(c, c->Bf, a, st);
 }
 
+// One sweep of a block set (a.sweeps) by the B kernel.  The share of the LDS
+// of a workgroup leaves room for as many as should share a compute unit.
+int block_sweep(slr_ctx *c, const slr_ctx::Deep::Part &D, BArgs a, bool compute64, hipStream_t st) {
+  const size_t tcb = (c->fact_prec == SLR_FP64 || compute64) ? 8 : 4;
+  const int64_t items = (int64_t)D.nb * a.nrhs;
+  const size_t share = items > 2 * (int64_t)c->n_cu ? 4 : (items > (int64_t)c->n_cu ? 2 : 1);
+  // few blocks: a column each, to fill the compute units
+  const int32_t most = (int32_t)std::max<int64_t>(1, (items + c->n_cu - 1) / c->n_cu);
+  int32_t R = 0, stage = 0;
+  if (!b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, std::min(a.nrhs, most), tcb, R, stage,
+                     c->lds_limit / share) &&
+      !b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, std::min(a.nrhs, most), tcb, R, stage,
+                     c->lds_limit))
+    return fail(SLR_ERR_ARG, "an interface block does not fit the LDS of one workgroup");
+  a.R = R;
+  a.stage_bytes = stage;
+  const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)tcb * ((int64_t)D.max_m * R + 1)) +
+                     16 * (size_t)(D.max_lev + 1);
+  const int32_t K = c->fact_prec == SLR_FP64 ? D.Bd.pack_K : D.Bf.pack_K, threads = K > 0 ? 512 : bsolve_threads(0);
+  if (c->fact_prec == SLR_FP64)
+    launch_bsolve<double, double>(D.Bd, D.nb, a, threads, lds, st);
+  else if (compute64)
+    launch_bsolve<float, double>(D.Bf, D.nb, a, threads, lds, st);
+  else
+    launch_bsolve<float, float>(D.Bf, D.nb, a, threads, lds, st);
+  return SLR_OK;
+}
+
+// x <- L^{-1} x (fwd) or L^{-T} x in place through the block form of L
+void deep_sweep(slr_ctx *c, const slr_ctx::Deep &D, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool compute64,
+                hipStream_t st) {
+  BArgs lead, rest;
+  lead.f = x; lead.u = x;
+  rest.f = x + D.t; rest.u = x + D.t;
+  for (BArgs *a : {&lead, &rest}) {
+    a->ldf = a->ldu = ldx;
+    a->a_f = 1.0;
+    a->nrhs = nrhs;
+    a->sweeps = fwd ? 1 : 2;
+  }
+  if (fwd) {
+    if (D.t > 0) {
+      (void)block_sweep(c, D.lead, lead, compute64, st);
+      launch_spmv_axpby(D.s - D.t, D.et_rp, D.et_ci, D.et_v, x, ldx, x + D.t, ldx, nrhs, 1.0, -1.0, st);
+    }
+    (void)block_sweep(c, D.rest, rest, compute64, st);
+  } else {
+    (void)block_sweep(c, D.rest, rest, compute64, st);
+    if (D.t > 0) {
+      lead.y = x + D.t; lead.ldy = ldx; lead.b_y = -1.0;
+      (void)block_sweep(c, D.lead, lead, compute64, st);
+    }
+  }
+}
+
 void csweep(slr_ctx *c, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool compute64, hipStream_t st) {
+  if (c->cdeep.on) return deep_sweep(c, c->cdeep, fwd, x, ldx, nrhs, compute64, st);
   const int32_t nlev = fwd ? c->cf_nlev : c->cb_nlev;
   const int32_t *lev = fwd ? c->cf_lev_h.data() : c->cb_lev_h.data();
   const int32_t G = fwd ? c->cf_group : c->cb_group;
@@ -665,6 +741,7 @@ int c1solve(slr_ctx *c, BArgs a, int32_t sweeps, bool compute64, hipStream_t st)
 // x <- L2^{-1} x (fwd) or L2^{-T} x over the inner interface, in place
 void c2sweep(slr_ctx *c, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool compute64, hipStream_t st) {
   const slr_ctx::Inner &I = c->ml;
+  if (I.deep.on) return deep_sweep(c, I.deep, fwd, x, ldx, nrhs, compute64, st);
   const int32_t nlev = fwd ? I.f_nlev : I.b_nlev;
   const int32_t *lev = fwd ? I.f_lev_h.data() : I.b_lev_h.data();
   const int32_t G = fwd ? I.f_group : I.b_group;
@@ -1950,6 +2027,217 @@ bool upload_sweep(DevPool &P, const Sweep &sw, SweepArrays<TS> &S, RfSweepMaps *
   return S.lev && S.rows && S.rp && S.ci && S.w && S.sc && okw2;
 }
 
+// Rows [lo, hi) of a sweep as a sweep of their own (local rows), and their
+// entries to other rows through out(local row, row, weight / scale).
+template <class Out>
+Sweep sub_sweep(const Sweep &sw, const std::vector<int32_t> &slots, int32_t lo, int32_t hi, Out out) {
+  const int32_t m = hi - lo;
+  std::vector<int32_t> depth(std::max(m, 1), 0);
+  Sweep o;
+  o.nrows = m;
+  for (int32_t t : slots) {   // in solve order
+    const int32_t r = sw.rows[t] - lo;
+    for (int32_t e = sw.rp[t]; e < sw.rp[t + 1]; ++e)
+      if (sw.ci[e] >= lo && sw.ci[e] < hi) depth[r] = std::max(depth[r], depth[sw.ci[e] - lo] + 1);
+    o.nlev = std::max(o.nlev, depth[r] + 1);
+  }
+  o.levptr.assign(o.nlev + 1, 0);
+  for (int32_t r = 0; r < m; ++r) ++o.levptr[depth[r] + 1];
+  for (int32_t l = 0; l < o.nlev; ++l) o.levptr[l + 1] += o.levptr[l];
+  std::vector<int32_t> at(o.levptr.begin(), o.levptr.end()), by(m);
+  for (int32_t t : slots) by[at[depth[sw.rows[t] - lo]]++] = t;
+  o.rp.assign(1, 0);
+  for (int32_t t : by) {
+    const int32_t r = sw.rows[t] - lo;
+    o.rows.push_back(r);
+    o.sc.push_back(sw.sc[t]);
+    for (int32_t e = sw.rp[t]; e < sw.rp[t + 1]; ++e) {
+      if (sw.ci[e] >= lo && sw.ci[e] < hi) {
+        o.ci.push_back(sw.ci[e] - lo);
+        o.w.push_back(sw.w[e]);
+      } else {
+        out(r, sw.ci[e], sw.w[e] / sw.sc[t]);
+      }
+    }
+    o.rp.push_back((int32_t)o.ci.size());
+  }
+  return o;
+}
+
+// Modelled time (us) of a sweep in one workgroup: 0.5 per level or 16 rows
+// of a near-chain, and its stream at 40 GB/s a compute unit.
+double deep_sweep_us(const Sweep &sw, bool runs) {
+  double us = 0.0;
+  for (int32_t l = 0; l < sw.nlev;) {
+    int32_t r = l;
+    while (r < sw.nlev && sw.levptr[r + 1] - sw.levptr[r] <= kColRunRows) ++r;
+    if (runs && r - l >= kColRunMin) {
+      us += 0.5 * (1 + (sw.levptr[r] - sw.levptr[l]) / kChainRows);
+      l = r;
+    } else {
+      us += 0.5;
+      ++l;
+    }
+  }
+  return us + 24.0 * (double)sw.ci.size() / 40e3;
+}
+
+// The block form of a deep interface factor, where it is modelled to beat
+// the schedule's own launches (old_us for both sweeps): the leading rows up
+// to the t that leaves the smallest largest piece plus remainder.  Connectors
+// (HID order) make the pieces; without them a factor that fits one
+// workgroup's LDS is one block.  lanes >= 0: every row in that many lanes
+// (log2) and no near-chains, which keeps the sums of launch_sweep with the
+// same lanes; only for t == 0.
+template <typename TS>
+bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32_t lanes, slr_ctx::Deep &D) {
+  const int32_t s = f.nrows;
+  D.on = false;
+  if (std::max(f.nlev, b.nlev) <= 8) return true;   // a few wide launches
+  for (double x : f.sc)
+    if (x == 0.0) return true;
+  // rows that fit a workgroup's LDS beside a stage and its tables
+  const int64_t cap = std::min<int64_t>(65535, ((int64_t)c->lds_limit - 49152) / 8);
+  std::vector<int32_t> tof(s), root(s), size(s, 1);
+  for (int32_t t = 0; t < s; ++t) tof[f.rows[t]] = t;
+  std::iota(root.begin(), root.end(), 0);
+  auto find = [&](int32_t x) {
+    while (root[x] != x) x = root[x] = root[root[x]];
+    return x;
+  };
+  auto join = [&](int32_t i) {   // row i with the earlier rows it uses
+    int32_t largest = 1;
+    for (int32_t e = f.rp[tof[i]]; e < f.rp[tof[i] + 1]; ++e) {
+      const int32_t x = find(f.ci[e]), y = find(i);
+      if (x != y) {
+        root[std::max(x, y)] = std::min(x, y);
+        size[std::min(x, y)] += size[std::max(x, y)];
+      }
+    }
+    largest = size[find(i)];
+    return largest;
+  };
+  int32_t t = s <= cap ? 0 : -1;
+  if (lanes < 0) {
+    int64_t best = s <= cap ? (int64_t)s * 3 / 5 : INT64_MAX, M = 0;
+    for (int32_t i = 0; i < s; ++i) {
+      if (M <= cap && s - i <= cap && M + (s - i) < best) {
+        best = M + (s - i);
+        t = i;
+      }
+      M = std::max<int64_t>(M, join(i));
+    }
+  }
+  if (t < 0) return true;
+  // pieces of the leading rows (each must be a contiguous range), small
+  // neighbours joined
+  std::iota(root.begin(), root.end(), 0);
+  std::fill(size.begin(), size.end(), 1);
+  int32_t M = 1;
+  for (int32_t i = 0; i < t; ++i) M = std::max(M, join(i));
+  std::vector<int32_t> starts;
+  std::vector<char> seen(std::max(t, 1), 0);
+  for (int32_t i = 0; i < t; ++i) {
+    const int32_t r = find(i);
+    if (i > 0 && find(i - 1) == r) continue;
+    if (seen[r]) {
+      if (s > cap) return true;
+      t = 0;   // not contiguous: one block
+      starts.clear();
+      break;
+    }
+    seen[r] = 1;
+    if (starts.empty() || i - starts.back() >= std::max(M, 128)) starts.push_back(i);
+  }
+  const int32_t nb = (int32_t)starts.size();
+  starts.push_back(t);
+  // solve slots of every block, in both sweeps
+  std::vector<int32_t> blk(s, nb);
+  for (int32_t q = 0; q < nb; ++q)
+    for (int32_t i = starts[q]; i < starts[q + 1]; ++i) blk[i] = q;
+  std::vector<std::vector<int32_t>> fs(nb + 1), bs(nb + 1);
+  for (int32_t k = 0; k < s; ++k) {
+    fs[blk[f.rows[k]]].push_back(k);
+    bs[blk[b.rows[k]]].push_back(k);
+  }
+  std::vector<Block> lead(nb), rest(1);
+  std::vector<std::vector<std::pair<int32_t, double>>> et(s - t);
+  double us = 0.0;
+  for (int32_t q = 0; q <= nb; ++q) {
+    Block &k = q < nb ? lead[q] : rest[0];
+    const int32_t lo = q < nb ? starts[q] : t, hi = q < nb ? starts[q + 1] : s;
+    k.m0 = q < nb ? lo : 0;
+    k.m = hi - lo;
+    k.lanes = lanes;
+    k.runs = lanes < 0;
+    k.fwd = sub_sweep(f, fs[q], lo, hi, [&](int32_t r, int32_t col, double w) { et[r].emplace_back(col, w); });
+    std::vector<std::vector<std::pair<int32_t, double>>> e(q < nb ? k.m : 0);
+    k.bwd = sub_sweep(b, bs[q], lo, hi, [&](int32_t r, int32_t col, double w) { e[r].emplace_back(col - t, w); });
+    for (int32_t r = 0; r < (int32_t)e.size(); ++r) {
+      if (e[r].empty()) continue;
+      k.e_row.push_back(r);
+      k.e_ptr.push_back((int32_t)k.e_q.size());
+      for (const auto &pr : e[r]) {
+        k.e_q.push_back(pr.first);
+        k.e_val.push_back(pr.second);
+      }
+    }
+    k.e_ptr.push_back((int32_t)k.e_q.size());
+    k.t_ptr.assign(1, 0);
+    const double one = deep_sweep_us(k.fwd, k.runs) + deep_sweep_us(k.bwd, k.runs);
+    us = q < nb ? std::max(us, one) : us + one;
+  }
+  if (us + 20.0 > 0.7 * old_us) return true;
+  D.t = t;
+  D.s = s;
+  auto pack = [&](const std::vector<Block> &blocks, slr_ctx::Deep::Part &P) {
+    BSizes sz;
+    bool ok;
+    if constexpr (sizeof(TS) == 8)
+      ok = pack_blocks<TS>(c->pool, blocks, P.Bd, sz, nullptr, c->lds_limit);
+    else
+      ok = pack_blocks<TS>(c->pool, blocks, P.Bf, sz, nullptr, c->lds_limit);
+    P.nb = (int32_t)blocks.size();
+    P.max_m = sz.max_m;
+    P.max_lev = sz.max_lev;
+    P.max_level_bytes = sz.max_level_bytes;
+    P.data_bytes = sz.data_bytes;
+    int32_t R = 0, stage = 0;
+    return ok && b_lds_plan_sz(P.max_m, P.max_lev, P.max_level_bytes, P.data_bytes, 1, 8, R, stage, c->lds_limit);
+  };
+  // a task or a table that does not fit leaves the schedule's own launches
+  if ((nb > 0 && !pack(lead, D.lead)) || !pack(rest, D.rest)) return true;
+  if (t > 0) {
+    std::vector<int64_t> rp(1, 0);
+    std::vector<int32_t> ci;
+    std::vector<double> v;
+    for (const auto &row : et) {
+      for (const auto &pr : row) {
+        ci.push_back(pr.first);
+        v.push_back(pr.second);
+      }
+      rp.push_back((int64_t)ci.size());
+    }
+    if (ci.empty()) {
+      ci.push_back(0);
+      v.push_back(0.0);
+    }
+    D.et_rp = c->pool.upload(rp);
+    D.et_ci = c->pool.upload(ci);
+    D.et_v = c->pool.upload(v);
+    if (!D.et_rp || !D.et_ci || !D.et_v) return false;
+  }
+  D.on = true;
+  return true;
+}
+
+// Time (us) of both sweeps of a schedule by its own launches (launch_sweep):
+// a launch per level, or one workgroup walking the levels.
+double schedule_us(const Sweep &f, const Sweep &b, bool one_wg, int32_t gf, int32_t gb) {
+  auto one = [&](const Sweep &s, int32_t G) { return s.nlev * (G > 1 ? 2.4 : (one_wg ? 1.2 : 4.0)); };
+  return one(f, gf) + one(b, gb);
+}
+
 template <typename TS>
 void upload_blocks(slr_ctx *c, const HostSetup &H, BlockArrays<TS> &B, SweepArrays<TS> &Cf, SweepArrays<TS> &Cb,
                    bool &ok, RfMaps *rm) {
@@ -2416,6 +2704,38 @@ int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out
   if (v2 && !(c->fact_prec == SLR_FP64 ? c->Bd.pack_K > 0 || convert_streams(c, c->Bd)
                                        : c->Bf.pack_K > 0 || convert_streams(c, c->Bf)))
     return bad("sweep streams");
+  if (!c->c_two_level) {
+    // the block form of a deep interface factor, from its schedule
+    auto host = [&](const void *p, auto &v, size_t n) {
+      v.resize(n);
+      return n == 0 || (p && pool_block_bytes(c->pool, p) >= n * sizeof(v[0]) &&
+                        hipMemcpy(v.data(), p, n * sizeof(v[0]), hipMemcpyDeviceToHost) == hipSuccess);
+    };
+    auto sweep = [&](const auto &A, const std::vector<int32_t> &lev, int32_t nlev, Sweep &sw) {
+      std::vector<std::remove_const_t<std::remove_reference_t<decltype(*A.w)>>> w, sc;
+      sw.nrows = (int32_t)c->s;
+      sw.nlev = nlev;
+      sw.levptr = lev;
+      if (lev.back() != c->s || !host(A.rows, sw.rows, c->s) || !host(A.rp, sw.rp, c->s + 1)) return false;
+      const int32_t nnz = sw.rp[c->s];
+      if (nnz < 0 || !host(A.ci, sw.ci, nnz) || !host(A.w, w, nnz) || !host(A.sc, sc, c->s)) return false;
+      for (int32_t r : sw.rows)
+        if (r < 0 || r >= c->s) return false;
+      for (int32_t r : sw.ci)
+        if (r < 0 || r >= c->s) return false;
+      sw.w.assign(w.begin(), w.end());
+      sw.sc.assign(sc.begin(), sc.end());
+      return true;
+    };
+    Sweep f, b;
+    const bool d = c->fact_prec == SLR_FP64;
+    if (!(d ? sweep(c->Cfd, c->cf_lev_h, c->cf_nlev, f) && sweep(c->Cbd, c->cb_lev_h, c->cb_nlev, b)
+            : sweep(c->Cff, c->cf_lev_h, c->cf_nlev, f) && sweep(c->Cbf, c->cb_lev_h, c->cb_nlev, b)))
+      return bad("interface schedule");
+    const double old_us = schedule_us(f, b, c->c_one_wg, c->cf_group, c->cb_group);
+    if (!(d ? deep_build<double>(c, f, b, old_us, -1, c->cdeep) : deep_build<float>(c, f, b, old_us, -1, c->cdeep)))
+      return bad("interface factor blocks");
+  }
   c->perm_h.resize(c->n);
   if (c->n) HIPCHK(hipMemcpy(c->perm_h.data(), c->perm, sizeof(int64_t) * c->n, hipMemcpyDeviceToHost));
   std::vector<double> U;
@@ -2627,6 +2947,14 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
       I.f_group = sweep_group(H.c2fwd);
       I.b_group = sweep_group(H.c2bwd);
     }
+    // (in the lanes of its own launches: the inner spectrum is flat, and its
+    // Lanczos vectors follow every rounding)
+    const int32_t lg = I.f_group == I.b_group ? __builtin_ctz((unsigned)I.f_group) : -1;
+    const double old_us = schedule_us(H.c2fwd, H.c2bwd, I.one_wg, I.f_group, I.b_group);
+    if (lg >= 0 && std::max(I.f_nlev, I.b_nlev) > 2 &&
+        !(c->fact_prec == SLR_FP64 ? deep_build<double>(c, H.c2fwd, H.c2bwd, old_us, lg, I.deep)
+                                   : deep_build<float>(c, H.c2fwd, H.c2bwd, old_us, lg, I.deep)))
+      return destroy_fail(fail(SLR_ERR_OOM, "inner interface factor blocks"));
     if (I.one_wg && sizeof(int32_t) * (size_t)(std::max(I.f_nlev, I.b_nlev) + 1) > c->lds_limit)
       return destroy_fail(fail(SLR_ERR_ARG, "inner level schedule too deep for one workgroup"));
     I.nnz_L1 = H.nnz_LC1;
@@ -2649,6 +2977,12 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
     c->cb_group = sweep_group(H.cbwd);
   }
   c->c_two_level = !c->ml.on && std::max(c->cf_nlev, c->cb_nlev) <= 2;
+  if (!c->ml.on && !c->c_two_level && !c->rf.on) {
+    const double old_us = schedule_us(H.cfwd, H.cbwd, c->c_one_wg, c->cf_group, c->cb_group);
+    if (!(c->fact_prec == SLR_FP64 ? deep_build<double>(c, H.cfwd, H.cbwd, old_us, -1, c->cdeep)
+                                   : deep_build<float>(c, H.cfwd, H.cbwd, old_us, -1, c->cdeep)))
+      return destroy_fail(fail(SLR_ERR_OOM, "interface factor blocks"));
+  }
   if (c->c_one_wg && sizeof(int32_t) * (size_t)(std::max(c->cf_nlev, c->cb_nlev) + 1) > c->lds_limit)
     return destroy_fail(fail(SLR_ERR_ARG, "interface level schedule too deep for one workgroup"));
   {

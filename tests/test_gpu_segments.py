@@ -65,6 +65,27 @@ def test_apply_matches_the_oracle_at_every_column_count(case, prec, tol):
         assert torch.equal(slr.apply(r[:, :c]), alone[:, :c]), c
 
 
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-12), ("fp32", 1e-5)])
+@pytest.mark.parametrize("name,over,order,cf", [
+    ("lap3d_64", dict(N=16, boxes=2), "hid", "ict"),        # connectors, small remainder
+    ("lap3d_64", dict(N=33, boxes=3), "hid", "ict"),        # uneven boxes
+    ("lap3d_64", dict(N=20, boxes=2), "subdomain", "ict"),  # one block, wide rows
+    ("lap3d_64", dict(N=24, boxes=3), "subdomain", "ic0"),  # one block, fixed width
+])
+def test_deep_interface_factor(name, over, order, cf, prec, tol):
+    print(name, over, order, cf, prec, flush=True)
+    pr, kw, slr = _setup(name, over, "ic0", cf, "natural", 1e-4, prec=prec, c_order=order)
+    assert slr.info["c_levels"] > 8
+    r = _vectors(pr.n, 17)
+    alone = torch.stack([slr.apply(r[:, i].contiguous()) for i in range(17)], 1)
+    ref = _oracle(pr, kw, slr)
+    z = ref.apply(r[:, 3].cpu().numpy())
+    assert np.linalg.norm(alone[:, 3].cpu().numpy() - z) <= tol * np.linalg.norm(z)
+    for c in (3, 5, 17):
+        assert torch.equal(slr.apply(r[:, :c]), alone[:, :c]), c
+    assert torch.equal(P.SLR.import_setup(slr.export_setup()).apply(r), alone)
+
+
 def test_few_ring_slots_and_a_resident_grid_keep_the_bits():
     pr, kw, slr = _setup("lap3d_64", dict(N=20, boxes=2), "ict", "ict", "mindeg", 1e-4)
     r = _vectors(pr.n, 5)
