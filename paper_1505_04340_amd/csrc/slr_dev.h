@@ -146,10 +146,6 @@ struct BArgs {
   // (first column << 16) | (columns << 24), each subdomain's x stored with
   // its own row count as stride, as many columns as the x region holds
   int32_t var_cols = 0;
-  // otherwise, with order != nullptr: a one-dimensional grid, workgroup w
-  // takes subdomain order[w / groups] and column group w % groups (longest
-  // subdomains first, so that the last ones to start are short)
-  const int32_t *order = nullptr;
 };
 
 // Numeric refactorisation on the device: one stored coefficient (TS) at
