@@ -132,6 +132,13 @@ struct BArgs {
   const double *g = nullptr;  int64_t ldg = 0;  double c_g = 0.0;
   double *gout = nullptr;     int64_t ldgo = 0; double d_t = 0.0;
   double *u = nullptr;        int64_t ldu = 0;
+  // idx != nullptr: f, g and u are in the caller's order, row i of the
+  // internal order (interior rows, then the interface) at idx[i]; g and gidx
+  // take the interface rows' part.  With yout, y is also stored there in the
+  // caller's order: each subdomain an even share of the s rows.
+  const int32_t *idx = nullptr, *gidx = nullptr;
+  double *yout = nullptr;     // leading dimension ldu
+  int32_t s = 0, p = 1;
   int32_t nrhs = 1;
   int32_t R = 1;              // right-hand sides per workgroup
   int32_t stage_bytes = 0;    // LDS staging buffer for the packed sweeps

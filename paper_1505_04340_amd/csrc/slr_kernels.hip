@@ -867,7 +867,7 @@ __device__ __forceinline__ void segments_pipelined(const uint8_t *fdata, const i
 // (tau = 1e-4, minimum degree, 6.0M sweep entries): 827 us with one wave per
 // column, barrier-free levels in two stage halves and chains through the LDS,
 // 346 us so; four exact factors of 961 rows: 296 -> 104 us.
-template <typename TS, typename TC, int KE, bool XP>
+template <typename TS, typename TC, int KE, bool XP, bool PM>
 __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArgs &a, int sub, int c0, int Rg,
                                             int XS) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -887,6 +887,8 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
   TC *xdummy = reinterpret_cast<TC *>(stage + a.stage_bytes) + (tid & 63);
   // LDS position of each local row (XP false: the row itself)
   const uint16_t *xp = XP ? B.xpos + d.m0 : nullptr;
+  // where the caller holds an interior row
+  auto at = [&](int row) { return PM ? a.idx[d.m0 + row] : d.m0 + row; };
   // level pointers into LDS, then rhs = a_f f_i (loads batched 4 per
   // thread), by the threads gt = 0 .. gn-1
   auto prologue = [&](int gt, int gn) {
@@ -897,6 +899,29 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
     for (int i = gt; i <= d.b_nlev; i += gn) {
       levb[i] = B.lev[d.b_lev + i];
       lvbb[i] = B.lvb[d.b_lvb + i];
+    }
+    if constexpr (PM) {
+      // each row's place taken once for its Rg columns, eight rows in flight
+      constexpr int NB = 8;
+      for (int i0 = gt; i0 < m; i0 += NB * gn) {
+        int from[NB], ps[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+          const int row = min(i0 + u * gn, m - 1);
+          from[u] = at(row);
+          ps[u] = XP ? (int)xp[row] : row;
+        }
+        for (int r = 0; r < Rg; ++r) {
+          const double *fc = a.f + (int64_t)(c0 + r) * a.ldf;
+          double v[NB];
+#pragma unroll
+          for (int u = 0; u < NB; ++u) v[u] = fc[from[u]];
+#pragma unroll
+          for (int u = 0; u < NB; ++u)
+            *(i0 + u * gn < m ? xs + r * XS + ps[u] : xdummy) = (TC)(a.a_f * v[u]);
+        }
+      }
+      return;
     }
     const int mt = m * Rg;
     if constexpr (!XP && sizeof(TC) == 8) {
@@ -1024,19 +1049,36 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
     sweeps_pipelined<TS, TC, KE>(B.data + d.f_data, levf, lvbf, fn, B.data + d.b_data, levb, lvbb, bn, xs, XS, Rg,
                                  stage, a.stage_bytes, true);
   if constexpr (XP) {
-    if (a.u) {
+    if (a.u && m > 0) {
       // each row's LDS position taken once for its Rg columns
-      double *uc = a.u + d.m0 + (int64_t)c0 * a.ldu;
+      double *uc = a.u + (int64_t)c0 * a.ldu;
+      int to[kPosPre];
+#pragma unroll
+      for (int i = 0; i < kPosPre; ++i) to[i] = at(min(tid + i * nt, m - 1));
 #pragma unroll
       for (int i = 0; i < kPosPre; ++i) {
         const int row = tid + i * nt;
         const int ps = (int)((pre[i / 2] >> (16 * (i & 1))) & 0xFFFFu);
         if (row < m)
-          for (int r = 0; r < Rg; ++r) uc[row + (int64_t)r * a.ldu] = (double)xs[r * XS + ps];
+          for (int r = 0; r < Rg; ++r) uc[to[i] + (int64_t)r * a.ldu] = (double)xs[r * XS + ps];
       }
       for (int row = tid + kPosPre * nt; row < m; row += nt) {
-        const int ps = (int)xp[row];
-        for (int r = 0; r < Rg; ++r) uc[row + (int64_t)r * a.ldu] = (double)xs[r * XS + ps];
+        const int ps = (int)xp[row], dst = at(row);
+        for (int r = 0; r < Rg; ++r) uc[dst + (int64_t)r * a.ldu] = (double)xs[r * XS + ps];
+      }
+    }
+  } else if (PM && a.u) {
+    // each row's place taken once for its Rg columns
+    double *uc = a.u + (int64_t)c0 * a.ldu;
+    for (int row0 = tid; row0 < m; row0 += 8 * nt) {
+      int to[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) to[i] = at(min(row0 + i * nt, m - 1));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int row = row0 + i * nt;
+        if (row < m)
+          for (int r = 0; r < Rg; ++r) uc[to[i] + (int64_t)r * a.ldu] = (double)xs[r * XS + row];
       }
     }
   } else if (a.u) {
@@ -1055,8 +1097,17 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
         const int64_t x = d.t_ent + (int64_t)e * tn + i;
         acc += cvt<TC>(B.t_val[x]) * xs[r * XS + (int)B.t_j[x]];
       }
-      const double gv = a.c_g != 0.0 ? a.c_g * a.g[q + (int64_t)(c0 + r) * a.ldg] : 0.0;
+      const double gv = a.c_g != 0.0 ? a.c_g * a.g[(PM ? a.gidx[q] : q) + (int64_t)(c0 + r) * a.ldg] : 0.0;
       a.gout[q + (int64_t)(c0 + r) * a.ldgo] = gv + a.d_t * (double)acc;
+    }
+  }
+  if constexpr (PM) {
+    if (a.yout) {
+      const int q1 = (int)((int64_t)a.s * (sub + 1) / a.p);
+      for (int q = (int)((int64_t)a.s * sub / a.p) + tid; q < q1; q += nt) {
+        const int dst = a.gidx[q];
+        for (int r = c0; r < c0 + Rg; ++r) a.yout[dst + (int64_t)r * a.ldu] = a.y[q + (int64_t)r * a.ldy];
+      }
     }
   }
 }
@@ -1064,7 +1115,7 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
 // One launch of the batched B solves: one workgroup per (subdomain, column
 // group), or a persistent grid walking its scheduled items (the shared
 // memory is reused after a barrier between items).
-template <typename TS, typename TC, int KE, bool XP>
+template <typename TS, typename TC, int KE, bool XP, bool PM>
 __global__ void __launch_bounds__(bsolve_threads(KE)) k_bsolve(BlockArrays<TS> B, BArgs a) {
   if (a.sched) {
     for (int it = a.sched_ptr[blockIdx.x]; it < a.sched_ptr[blockIdx.x + 1]; ++it) {
@@ -1073,41 +1124,50 @@ __global__ void __launch_bounds__(bsolve_threads(KE)) k_bsolve(BlockArrays<TS> B
       if (a.var_cols) {
         // columns [c0, c0 + Rg) of the subdomain, with its own row stride
         const int c0 = (int)((item >> 16) & 0xFFu), Rg = (int)(item >> 24);
-        bsolve_item<TS, TC, KE, XP>(B, a, sub, c0, Rg, B.desc[sub].m);
+        bsolve_item<TS, TC, KE, XP, PM>(B, a, sub, c0, Rg, B.desc[sub].m);
       } else {
         const int c0 = (int)(item >> 16) * a.R;
-        bsolve_item<TS, TC, KE, XP>(B, a, sub, c0, min(a.R, a.nrhs - c0), B.max_m);
+        bsolve_item<TS, TC, KE, XP, PM>(B, a, sub, c0, min(a.R, a.nrhs - c0), B.max_m);
       }
       __syncthreads();
     }
   } else {
     const int c0 = blockIdx.y * a.R;
-    bsolve_item<TS, TC, KE, XP>(B, a, blockIdx.x, c0, min(a.R, a.nrhs - c0), B.max_m);
+    bsolve_item<TS, TC, KE, XP, PM>(B, a, blockIdx.x, c0, min(a.R, a.nrhs - c0), B.max_m);
   }
 }
 
-template <typename TS, typename TC, int KE, bool XP>
+template <typename TS, typename TC, int KE, bool XP, bool PM>
 void launch_bsolve_k(const BlockArrays<TS> &B, int32_t p, const BArgs &a, int32_t threads, size_t lds_bytes,
                      hipStream_t st) {
   static size_t attr_bytes = 0;
   if (lds_bytes > 65536 && lds_bytes > attr_bytes) {
-    (void)hipFuncSetAttribute((const void *)k_bsolve<TS, TC, KE, XP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void *)k_bsolve<TS, TC, KE, XP, PM>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds_bytes);
     attr_bytes = lds_bytes;
   }
   // persistent: p is the number of workgroups of the schedule
   dim3 grid(p, a.sched ? 1 : (a.nrhs + a.R - 1) / a.R);
-  hipLaunchKernelGGL((k_bsolve<TS, TC, KE, XP>), grid, dim3(threads), lds_bytes, st, B, a);
+  hipLaunchKernelGGL((k_bsolve<TS, TC, KE, XP, PM>), grid, dim3(threads), lds_bytes, st, B, a);
 }
 // the variant with LDS positions (B.xpos) exists for the fixed-width forms
-// only: the host keeps the row order for rows of any width
+// only: the host keeps the row order for rows of any width; the variants in
+// the caller's order (a.idx) for the apply's precisions only
+template <typename TS, typename TC, int KE, bool XP>
+void launch_bsolve_p(const BlockArrays<TS> &B, int32_t p, const BArgs &a, int32_t threads, size_t lds_bytes,
+                     hipStream_t st) {
+  if constexpr (std::is_same<TS, TC>::value) {
+    if (a.idx) return launch_bsolve_k<TS, TC, KE, XP, true>(B, p, a, threads, lds_bytes, st);
+  }
+  launch_bsolve_k<TS, TC, KE, XP, false>(B, p, a, threads, lds_bytes, st);
+}
 template <typename TS, typename TC, int KE>
 void launch_bsolve_x(const BlockArrays<TS> &B, int32_t p, const BArgs &a, int32_t threads, size_t lds_bytes,
                      hipStream_t st) {
   if (B.xpos)
-    launch_bsolve_k<TS, TC, KE, true>(B, p, a, threads, lds_bytes, st);
+    launch_bsolve_p<TS, TC, KE, true>(B, p, a, threads, lds_bytes, st);
   else
-    launch_bsolve_k<TS, TC, KE, false>(B, p, a, threads, lds_bytes, st);
+    launch_bsolve_p<TS, TC, KE, false>(B, p, a, threads, lds_bytes, st);
 }
 
 // B.pack_K > 0: every packed row has exactly pack_K entries
@@ -1119,7 +1179,7 @@ void launch_bsolve(const BlockArrays<TS> &B, int32_t p, const BArgs &a, int32_t 
     case 2: launch_bsolve_x<TS, TC, 2>(B, p, a, threads, lds_bytes, st); break;
     case 3: launch_bsolve_x<TS, TC, 3>(B, p, a, threads, lds_bytes, st); break;
     case 4: launch_bsolve_x<TS, TC, 4>(B, p, a, threads, lds_bytes, st); break;
-    default: launch_bsolve_k<TS, TC, 0, false>(B, p, a, threads, lds_bytes, st); break;
+    default: launch_bsolve_p<TS, TC, 0, false>(B, p, a, threads, lds_bytes, st); break;
   }
 }
 
