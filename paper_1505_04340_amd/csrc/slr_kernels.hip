@@ -2072,6 +2072,7 @@ __device__ __forceinline__ void chunk_rows_pf(int64_t n, Ld ld, Mid mid, Op op) 
 }
 
 constexpr int CG_RPT = 4;   // rows per thread whose loads go out together
+constexpr int CG_T = 4;     // columns per tile of k_cg_spmv
 
 // One column, y = A x, the rows of this thread's chunk one at a time (BD
 // threads per block): a row's pointer loads and own(i) (the loads of the
@@ -2168,7 +2169,7 @@ __global__ void __launch_bounds__(RED_THREADS) k_relres2(KArgs K, int c0, int nc
 __host__ __device__ constexpr int cg_np(int flexible) { return flexible ? 4 : 3; }
 
 // w = A z ; partials gamma, delta, rho = r.r (, eps) ->
-// part[b*np*nc + np*cc + (0, 1, 2 (, 3))]
+// part[(np*cc + (0, 1, 2 (, 3)))*nblk + b]
 // One column (slr_solve with one right-hand side): 512 threads per block,
 // one row per thread at 512 rows per block, for the loads in flight.  No
 // load waits for the column's state: an inactive column's w and partials
@@ -2199,51 +2200,58 @@ __global__ void __launch_bounds__(CG_SPMV1_THREADS) k_cg_spmv1(int64_t n, const 
   double t[4] = {g, d, rr, ep};
   block_sums<4>(t, sh);
   if (threadIdx.x == 0)
-    for (int j = 0; j < np; ++j) K.part[(int64_t)blockIdx.x * np + j] = t[j];
+    for (int j = 0; j < np; ++j) K.part[(int64_t)j * K.nblk + blockIdx.x] = t[j];
 }
 
-// Column tiles of TT (several right-hand sides, and every batch): each row's
-// entries are read once per tile, and a column's arithmetic (entry order,
-// row order, block sums) does not depend on the tile it falls in or on the
-// number of columns.
+// Column tiles of TT (several right-hand sides, and every batch), tile
+// blockIdx.y: each row's entries are read once per tile, and a column's
+// arithmetic (entry order, row order, block sums) does not depend on the tile
+// it falls in or on the number of columns.  Bound by the loads in flight: a
+// row's own entries go out first, then 16 gathers at a time.  16 columns of
+// 65536 rows: 39 us with the tiles of 8 one after another in a block, 26.7 so
+// (a batch of 16 served in 61.5 ms with tiles of 8, 56.9 with 4, 56.0 with 2;
+// 32 columns of 96^3 solved in 380, 380 and 397 ms).
 template <int TT>
 __global__ void __launch_bounds__(RED_THREADS) k_cg_spmv(int64_t n, const int64_t *rp, const int32_t *ci,
                                                          const double *v, KArgs K, int c0, int nc, int flexible) {
-  __shared__ double sh[4 * (RED_THREADS / 64)];
-  const int np = cg_np(flexible);
-  for (int ct = 0; ct < nc; ct += TT) {
-    const int nct = min(TT, nc - ct);
-    bool act[TT];
-    double g[TT], d[TT], rr[TT], ep[TT];
+  __shared__ double sh[4 * TT * (RED_THREADS / 64)];
+  const int np = cg_np(flexible), ct = blockIdx.y * TT, nct = min(TT, nc - ct);
+  bool act[TT];
+  double sums[4 * TT];
+#pragma unroll
+  for (int t = 0; t < TT; ++t) act[t] = t < nct && K.st[c0 + ct + t].active;
+#pragma unroll
+  for (int t = 0; t < 4 * TT; ++t) sums[t] = 0.0;
+  chunk_rows(n, [&](int64_t i) {
+    const int64_t e0 = rp[i], e1 = rp[i + 1];
+    double sum[TT], z[TT], r[TT], q[TT];
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
-      act[t] = t < nct && K.st[c0 + ct + t].active;
-      g[t] = d[t] = rr[t] = ep[t] = 0.0;
+      const int64_t o = i + (int64_t)(c0 + ct + t) * K.ld;
+      sum[t] = 0.0;
+      z[t] = act[t] ? K.Z[o] : 0.0;
+      r[t] = act[t] ? K.R[o] : 0.0;
+      q[t] = act[t] && flexible ? K.S[o] : 0.0;
     }
-    chunk_rows(n, [&](int64_t i) {
-      double sum[TT];
+    csr_row_acc<TT, 16 / TT>(e0, e1, ci, v, K.Z, K.ld, c0 + ct, act, sum);
 #pragma unroll
-      for (int t = 0; t < TT; ++t) sum[t] = 0.0;
-      csr_row_acc<TT, TT == 1 ? 8 : 2>(rp[i], rp[i + 1], ci, v, K.Z, K.ld, c0 + ct, act, sum);
+    for (int t = 0; t < TT; ++t)
+      if (act[t]) {
+        K.Q[i + (int64_t)(c0 + ct + t) * K.ld] = sum[t];
+        sums[4 * t] += r[t] * z[t];
+        sums[4 * t + 1] += z[t] * sum[t];
+        sums[4 * t + 2] += r[t] * r[t];
+        if (flexible) sums[4 * t + 3] += z[t] * q[t];
+      }
+  });
+  block_sums<4 * TT>(sums, sh);
+  if (threadIdx.x == 0)
 #pragma unroll
-      for (int t = 0; t < TT; ++t)
-        if (act[t]) {
-          const int64_t o = i + (int64_t)(c0 + ct + t) * K.ld;
-          const double zi = K.Z[o], ri = K.R[o];
-          K.Q[o] = sum[t];
-          g[t] += ri * zi;
-          d[t] += zi * sum[t];
-          rr[t] += ri * ri;
-          if (flexible) ep[t] += zi * K.S[o];
-        }
-    });
-    for (int t = 0; t < nct; ++t) {
-      double u[4] = {g[t], d[t], rr[t], ep[t]};
-      block_sums<4>(u, sh);
-      if (threadIdx.x == 0)
-        for (int j = 0; j < np; ++j) K.part[(int64_t)blockIdx.x * np * nc + np * (ct + t) + j] = u[j];
-    }
-  }
+    for (int t = 0; t < TT; ++t)
+      if (t < nct)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (j < np) K.part[((int64_t)np * (ct + t) + j) * K.nblk + blockIdx.x] = sums[4 * t + j];
 }
 
 // The decision of iteration `it` for one column from its folded partials f
@@ -2280,69 +2288,66 @@ __device__ __forceinline__ CgStep cg_step(const KState &s, const double *f, int 
 }
 
 // fold ; stop or p = z + beta p, s = w + beta s, x += alpha p, r -= alpha s
-// (the first column's vectors are loaded while the partials are folded)
-__global__ void __launch_bounds__(RED_THREADS) k_cg_update(int64_t n, KArgs K, int c0, int nc, int flexible,
-                                                            int it) {
-  __shared__ double fin[MAX_FOLD];
-  const int np = cg_np(flexible);
-  for (int cc = 0; cc < nc; ++cc) {
-    const int c = c0 + cc;
-    const KState &s = K.st[c];
-    const bool live = s.active;
-    const int64_t o = (int64_t)c * K.ld;
-    double *X = K.X + o, *R = K.R + o, *P = K.P + o, *S = K.S + o;
-    const double *Z = K.Z + o, *W = K.Q + o;
-    double xv[CG_RPT], rv[CG_RPT], pv[CG_RPT], sv[CG_RPT], zv[CG_RPT], wv[CG_RPT];
-    CgStep q{};
-    bool go = false;
-    chunk_rows_pf<CG_RPT>(
-        n,
-        [&](int r, int64_t i) {
-          if (cc == 0 || live) {
-            xv[r] = X[i];
-            rv[r] = R[i];
-            pv[r] = P[i];
-            sv[r] = S[i];
-            zv[r] = Z[i];
-            wv[r] = W[i];
-          }
-        },
-        [&]() {
-          if (cc == 0) fold_to_lds(K.part, K.nblk, np * nc, fin);
-          q = cg_step(s, fin + np * cc, it, K.maxit, K.rtol2, flexible);
-          go = live && !q.stop && !q.brk;
-        },
-        [&](int r, int64_t i) {
-          if (go) {
-            const double pn = q.first ? zv[r] : zv[r] + q.beta * pv[r];
-            const double sn = q.first ? wv[r] : wv[r] + q.beta * sv[r];
-            P[i] = pn;
-            S[i] = sn;
-            X[i] = xv[r] + q.alpha * pn;
-            R[i] = rv[r] - q.alpha * sn;
-          }
-        });
-  }
-  __syncthreads();
-  if (blockIdx.x == 0) {
-    for (int cc = threadIdx.x; cc < nc; cc += RED_THREADS) {
-      KState &s = K.st[c0 + cc];
-      if (!s.active) continue;
-      const CgStep q = cg_step(s, fin + np * cc, it, K.maxit, K.rtol2, flexible);
-      s.rr = fin[np * cc + 2];
-      if (q.stop || q.brk) {
-        s.active = 0;
-        s.status = (q.stop && q.ok) ? 0 : -8;
-        s.iters = q.done;
-      } else {
-        s.rz[it & 1] = fin[np * cc];
-        s.al[it & 1] = q.alpha;
-        s.pq[it & 1] = q.pap;
-        s.alpha = q.alpha;
-        s.beta = q.beta;
-        s.iters = q.done + 1;
-      }
-    }
+// of column blockIdx.y (its vectors are loaded while the partials are folded;
+// every block folds its own column's only).  16 columns of 65536 rows: 67 us
+// with a block's columns one after another, 12.9 so (84 MB, 6.5 TB/s).
+__global__ void __launch_bounds__(RED_THREADS) k_cg_update(int64_t n, KArgs K, int c0, int flexible, int it) {
+  __shared__ double fin[4];
+  const int np = cg_np(flexible), cc = blockIdx.y, c = c0 + cc;
+  KState &s = K.st[c];
+  const bool live = s.active, one = gridDim.y == 1;   // one column: loads that wait for no state
+  const int64_t o = (int64_t)c * K.ld;
+  double *X = K.X + o, *R = K.R + o, *P = K.P + o, *S = K.S + o;
+  const double *Z = K.Z + o, *W = K.Q + o;
+  double xv[CG_RPT], rv[CG_RPT], pv[CG_RPT], sv[CG_RPT], zv[CG_RPT], wv[CG_RPT];
+  CgStep q{};
+  bool go = false;
+  chunk_rows_pf<CG_RPT>(
+      n,
+      [&](int r, int64_t i) {
+        if (one || live) {
+          xv[r] = X[i];
+          rv[r] = R[i];
+          pv[r] = P[i];
+          sv[r] = S[i];
+          zv[r] = Z[i];
+          wv[r] = W[i];
+        }
+      },
+      [&]() {
+        const int lane = threadIdx.x & 63;
+        const double *part = K.part + (int64_t)np * cc * K.nblk;
+        for (int j = threadIdx.x >> 6; j < np; j += RED_THREADS / 64) {
+          const double f = wave_sum(lane_fold(part + (int64_t)j * K.nblk, K.nblk, 1, 0, lane));
+          if (lane == 0) fin[j] = f;
+        }
+        __syncthreads();
+        q = cg_step(s, fin, it, K.maxit, K.rtol2, flexible);
+        go = live && !q.stop && !q.brk;
+      },
+      [&](int r, int64_t i) {
+        if (go) {
+          const double pn = q.first ? zv[r] : zv[r] + q.beta * pv[r];
+          const double sn = q.first ? wv[r] : wv[r] + q.beta * sv[r];
+          P[i] = pn;
+          S[i] = sn;
+          X[i] = xv[r] + q.alpha * pn;
+          R[i] = rv[r] - q.alpha * sn;
+        }
+      });
+  if (blockIdx.x != 0 || threadIdx.x != 0 || !live) return;
+  s.rr = fin[2];
+  if (q.stop || q.brk) {
+    s.active = 0;
+    s.status = (q.stop && q.ok) ? 0 : -8;
+    s.iters = q.done;
+  } else {
+    s.rz[it & 1] = fin[0];
+    s.al[it & 1] = q.alpha;
+    s.pq[it & 1] = q.pap;
+    s.alpha = q.alpha;
+    s.beta = q.beta;
+    s.iters = q.done + 1;
   }
 }
 
@@ -2388,10 +2393,16 @@ void launch_cg(int op, int64_t n, const int64_t *rp, const int32_t *ci, const do
       }
       [[fallthrough]];
     case CG_SPMV_TILES:
-      hipLaunchKernelGGL(k_cg_spmv<SPMV_T>, dim3(nb), dim3(RED_THREADS), 0, st, n, rp, ci, v, K, c0, nc, flexible);
+      hipLaunchKernelGGL(k_cg_spmv<CG_T>, dim3(nb, (nc + CG_T - 1) / CG_T), dim3(RED_THREADS), 0, st, n, rp, ci, v, K,
+                         c0, nc, flexible);
       break;
-    case CG_UPDATE:
-      hipLaunchKernelGGL(k_cg_update, dim3(nb), dim3(RED_THREADS), 0, st, n, K, c0, nc, flexible, it);
+    case CG_UPDATE: {
+      // several columns: CG_RPT rows a thread, unless that leaves few blocks
+      const int64_t few = (n + CG_RPT * RED_THREADS - 1) / (CG_RPT * RED_THREADS), many = (n + RED_THREADS - 1) / RED_THREADS;
+      const int64_t nbx = std::min<int64_t>(nb, std::max<int64_t>(few, std::min<int64_t>(many, 2048 / nc)));
+      hipLaunchKernelGGL(k_cg_update, dim3(nc == 1 ? nb : (unsigned)nbx, nc), dim3(RED_THREADS), 0, st, n, K, c0,
+                         flexible, it);
+    }
       break;
     default:
       break;
