@@ -376,6 +376,7 @@ struct slr_ctx {
       std::vector<int32_t> lev;
       int kind = 0;
     } fb, fc;
+    FactBlocks fblk;                 // fb by blocks (nb = 0: level by level)
     struct Map {
       RfMap *m = nullptr;
       int64_t n = 0;
@@ -2351,6 +2352,62 @@ const double *seeded_v0(int64_t n, uint64_t seed, std::vector<double> &v0) {
   return v0.data();
 }
 
+// The B factors' plan by blocks (FactBlocks), where their rows qualify.  False:
+// device memory exhausted.
+bool fact_blocks(slr_ctx *c, const HostSetup &H) {
+  const RefactorPlan &P = H.fb;
+  std::vector<int4> rec;
+  std::vector<int32_t> blk(1, 0), lev(1, 0);
+  std::vector<int64_t> row;
+  int32_t max_m = 0;
+  for (const Block &b : H.blocks) {
+    max_m = std::max(max_m, b.m);
+    if (b.m > 65535) return true;
+    for (int32_t l = 0; l < b.fwd.nlev; ++l)
+      for (int32_t t0 = b.fwd.levptr[l]; t0 < b.fwd.levptr[l + 1]; t0 += kFactThreads) {
+        const int32_t t1 = std::min(t0 + kFactThreads, b.fwd.levptr[l + 1]);
+        for (int32_t t = t0; t < t1; ++t) {
+          const int64_t i = (int64_t)b.m0 + b.fwd.rows[t], e0 = P.rp[i], n = P.rp[i + 1] - 1 - e0;
+          if (n < 0 || n > kFactEntries || P.ci[e0 + n] != i) return true;
+          uint32_t j[kFactEntries] = {0, 0, 0, 0};
+          for (int64_t u = 0; u < n; ++u) {
+            const int32_t k = P.ci[e0 + u];
+            j[u] = (uint32_t)(k - b.m0);
+            // a product where rows i and k share a column before k
+            for (int64_t e = P.rp[k]; e + 1 < P.rp[k + 1]; ++e)
+              if (std::binary_search(P.ci.begin() + e0, P.ci.begin() + e0 + u, P.ci[e])) return true;
+          }
+          rec.push_back(make_int4((int32_t)(j[0] | j[1] << 16), (int32_t)(j[2] | j[3] << 16), (int32_t)e0,
+                                  b.fwd.rows[t] | (int32_t)n << 16));
+          row.push_back(i);
+        }
+        lev.push_back((int32_t)rec.size());
+      }
+    blk.push_back((int32_t)lev.size() - 1);
+  }
+  if (rec.empty() || sizeof(double) * (size_t)max_m > c->lds_limit) return true;
+  const size_t ns = rec.size();
+  std::vector<int32_t> src(ns * (kFactEntries + 1));
+  for (size_t r = 0; r < ns; ++r) {
+    const int64_t e0 = P.rp[row[r]], n = P.rp[row[r] + 1] - 1 - e0;
+    for (int64_t u = 0; u <= kFactEntries; ++u)
+      src[u * ns + r] = (int32_t)P.src[u == 0 || u > n ? e0 + n : e0 + u - 1];
+  }
+  FactBlocks F;
+  DevPool &pool = c->rf.pool;
+  F.rec = pool.upload(rec);
+  F.src = pool.upload(src);
+  F.blk = pool.upload(blk);
+  F.lev = pool.upload(lev);
+  F.slots = (int32_t)ns;
+  F.max_m = max_m;
+  F.ldl = P.kind == 2;
+  if (!F.rec || !F.src || !F.blk || !F.lev) return false;
+  F.nb = (int32_t)H.blocks.size();
+  c->rf.fblk = F;
+  return true;
+}
+
 // Keep what slr_refactor needs: the input pattern (symmetry check), the
 // gather maps of A / E / E^T, the factor plans and the coefficient maps.
 bool rf_upload(slr_ctx *c, const HostSetup &H, const RfMaps &rm, const slr_csr *A) {
@@ -2390,6 +2447,7 @@ bool rf_upload(slr_ctx *c, const HostSetup &H, const RfMaps &rm, const slr_csr *
     return D.m != nullptr;
   };
   bool ok = R.val && R.err && R.a_src && R.tr && R.stage && plan(H.fb, R.fb) && plan(H.fc, R.fc);
+  ok = ok && fact_blocks(c, H);
   ok = ok && map(rm.bdata, R.bdata) && map(rm.ev, R.ev) && map(rm.tv, R.tv);
   ok = ok && map(rm.cf.sc, R.cfsc) && map(rm.cf.w, R.cfw) && map(rm.cf.w2, R.cfw2);
   ok = ok && map(rm.cb.sc, R.cbsc) && map(rm.cb.w, R.cbw) && map(rm.cb.w2, R.cbw2);
@@ -2401,8 +2459,13 @@ template <typename TS>
 void rf_pack_all(slr_ctx *c, const BlockArrays<TS> &B, const SweepArrays<TS> &Cf, const SweepArrays<TS> &Cb,
                  hipStream_t st) {
   auto &R = c->rf;
+  RfPack P;
+  int q = 0;
   auto run = [&](const slr_ctx::Refactor::Map &m, const double *V, const void *base) {
-    launch_rf_pack<TS>(m.n, m.m, V, R.val, const_cast<void *>(base), st);
+    P.map[q] = m.m;
+    P.n[q] = m.n;
+    P.V[q] = V;
+    P.base[q++] = const_cast<void *>(base);
   };
   run(R.bdata, R.fb.v, B.data);
   run(R.ev, nullptr, B.e_val);
@@ -2413,6 +2476,7 @@ void rf_pack_all(slr_ctx *c, const BlockArrays<TS> &B, const SweepArrays<TS> &Cf
   run(R.cbsc, R.fc.v, Cb.sc);
   run(R.cbw, R.fc.v, Cb.w);
   run(R.cbw2, R.fc.v, Cb.w2);
+  launch_rf_pack<TS>(P, R.val, st);
 }
 
 // After a change of the low-rank part: workspace sized for the new k, stats.
@@ -3166,9 +3230,12 @@ int slr_refactor(slr_ctx *c, const double *val, int32_t on_device, void *hip_str
     HIPCHK(hipMemcpyAsync(R.val, R.stage, sizeof(double) * R.nnz, hipMemcpyHostToDevice, st));
   }
   // factors into their own value arrays (level by level)
-  launch_gather(R.fb.nnz, R.fb.src, R.val, R.fb.v, st);
+  if (R.fblk.nb > 0)
+    launch_fact_blocks(R.fblk, R.val, R.fb.v, R.err, st);
+  else
+    launch_gather(R.fb.nnz, R.fb.src, R.val, R.fb.v, st);
   launch_gather(R.fc.nnz, R.fc.src, R.val, R.fc.v, st);
-  for (size_t l = 0; l + 1 < R.fb.lev.size(); ++l)
+  for (size_t l = 0; R.fblk.nb == 0 && l + 1 < R.fb.lev.size(); ++l)
     launch_fact_level(R.fb.rp, R.fb.ci, R.fb.v, R.fb.rows, R.fb.lev[l], R.fb.lev[l + 1], R.fb.kind == 2, R.err, st);
   for (size_t l = 0; l + 1 < R.fc.lev.size(); ++l)
     launch_fact_level(R.fc.rp, R.fc.ci, R.fc.v, R.fc.rows, R.fc.lev[l], R.fc.lev[l + 1], 0, R.err + 1, st);

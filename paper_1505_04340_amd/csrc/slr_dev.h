@@ -171,13 +171,36 @@ struct RfMap {
   int32_t a, b, c, op;
 };
 
+// every map of a refactorisation in one launch; V: the factor of a map's
+// values (RF_SRC reads val)
+constexpr int kRfMaps = 9;
+struct RfPack {
+  const RfMap *map[kRfMaps] = {};
+  int64_t n[kRfMaps] = {};
+  const double *V[kRfMaps] = {};
+  void *base[kRfMaps] = {};
+};
 template <typename TS>
-void launch_rf_pack(int64_t nmap, const RfMap *map, const double *V, const double *val, void *base,
-                    hipStream_t st);
+void launch_rf_pack(const RfPack &P, const double *val, hipStream_t st);
 // *flag = 1 if some val[e] != val[tr[e]] (tr: the mirror entry of each entry)
 void launch_mirror_check(int64_t n, const int64_t *tr, const double *val, int *flag, hipStream_t st);
 // out[e] = val[src[e]]
 void launch_gather(int64_t n, const int64_t *src, const double *val, double *out, hipStream_t st);
+// Block-diagonal factor without fill whose rows have at most kFactEntries
+// entries off the diagonal, no two of which share a column (no products to
+// subtract): the rows of a block level by level, at most kFactThreads a
+// level.  Slot r holds row (rec[r].w & 0xFFFF) of its block, its entry count
+// (rec[r].w >> 16), its first entry in V (rec[r].z) and the block's rows of
+// its columns, 16 bits each (rec[r].x, .y); src[u * slots + r] is the matrix
+// entry of its diagonal (u = 0) and of entry u - 1 (past the end: the
+// diagonal's).  Block b has the levels lev[blk[b]] .. lev[blk[b + 1]].
+constexpr int kFactEntries = 4, kFactThreads = 256;
+struct FactBlocks {
+  const int4 *rec = nullptr;
+  const int32_t *src = nullptr, *blk = nullptr, *lev = nullptr;
+  int32_t slots = 0, nb = 0, max_m = 0, ldl = 0;
+};
+void launch_fact_blocks(const FactBlocks &F, const double *val, double *V, int *err, hipStream_t st);
 // IC(0) (ldl = 0) or ILDL^T(0) (ldl = 1) of the rows rows[r0 .. r1) of the
 // lower CSR (rp, ci, diagonal last) whose values V hold the matrix entries
 // on entry; earlier rows must be final.  *err is set to 1 on a failed pivot.
