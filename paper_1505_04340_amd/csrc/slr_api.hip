@@ -683,7 +683,7 @@ void deep_sweep(slr_ctx *c, const slr_ctx::Deep &D, bool fwd, double *x, int64_t
   if (fwd) {
     if (D.t > 0) {
       (void)block_sweep(c, D.lead, lead, compute64, st);
-      launch_spmv_axpby(D.s - D.t, D.et_rp, D.et_ci, D.et_v, x, ldx, x + D.t, ldx, nrhs, 1.0, -1.0, st);
+      launch_rows_sub(D.s - D.t, D.et_rp, D.et_ci, D.et_v, x, ldx, x + D.t, ldx, nrhs, st);
     }
     (void)block_sweep(c, D.rest, rest, compute64, st);
   } else {

@@ -2016,6 +2016,42 @@ void launch_spmv_axpby(int64_t n, const int64_t *rp, const int32_t *ci, const do
                        v, x, ldx, y, ldy, nrhs, a, b);
 }
 
+// y -= A x, a wave per row and column: lane l sums the row's entries l, l +
+// 64, .. in order, a butterfly sums the lanes.  For the rows of a deep
+// interface factor's remainder, which are few and long: a thread per row took
+// 38.3 us at 2176 rows of the interface of 27 boxes of 48^3 (25408 rows,
+// threshold factor), this 5.1.
+__global__ void __launch_bounds__(256) k_rows_sub(int64_t n, const int64_t *rp, const int32_t *ci, const double *v,
+                                                  const double *x, int64_t ldx, double *y, int64_t ldy) {
+  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (i >= n) return;
+  const double *xc = x + (int64_t)blockIdx.y * ldx;
+  double *yp = y + i + (int64_t)blockIdx.y * ldy;
+  const int64_t e0 = rp[i], e1 = rp[i + 1];
+  double acc = 0.0;
+  for (int64_t e = e0; e < e1; e += 256) {
+    double a[4], b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t k = min(e + lane + 64 * u, e1 - 1);
+      a[u] = v[k];
+      b[u] = xc[ci[k]];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e + lane + 64 * u < e1) acc += a[u] * b[u];
+  }
+  acc = wave_sum(acc);
+  if (lane == 0) *yp -= acc;
+}
+
+void launch_rows_sub(int64_t n, const int64_t *rp, const int32_t *ci, const double *v, const double *x, int64_t ldx,
+                     double *y, int64_t ldy, int32_t nrhs, hipStream_t st) {
+  if (n == 0 || nrhs == 0) return;
+  hipLaunchKernelGGL(k_rows_sub, dim3((unsigned)((n + 3) / 4), nrhs), dim3(256), 0, st, n, rp, ci, v, x, ldx, y, ldy);
+}
+
 // ---------------------------------------------------------------------------
 // K6: Krylov BLAS-1 with deterministic reductions, CG / flexible CG.
 // Every reduction writes per-block partials part[b*width + col]; the next
