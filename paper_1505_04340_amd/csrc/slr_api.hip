@@ -723,21 +723,26 @@ void csweep2(slr_ctx *c, bool fwd, const double *x, int64_t ldx, double *y, int6
 
 // ---- recursive interface solver (Sec. 5.2) --------------------------------
 // C1 solves: the B kernel over the connectors (sweeps: 1 = L1^{-1} only,
-// 2 = L1^{-T} only, 3 = both); a quarter of the LDS per workgroup when the
-// connectors fit it, so that several share a compute unit.
+// 2 = L1^{-T} only, 3 = both); a quarter of the LDS per workgroup (half for
+// rows of any width) when the connectors fit it, so that several share a
+// compute unit.
 int c1solve(slr_ctx *c, BArgs a, int32_t sweeps, bool compute64, hipStream_t st) {
   const slr_ctx::Inner &I = c->ml;
   a.sweeps = sweeps;
   const size_t tcb = (c->fact_prec == SLR_FP64 || compute64) ? 8 : 4;
+  // Sweeps of any width take 8 waves of 116 registers: two workgroups fit a
+  // compute unit, whatever their LDS (540 blocks of about 410 rows, a half
+  // solve: 150 us at a quarter each, 106 at a half with longer segments).
+  const int32_t K = c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K, share = K > 0 ? 4 : 2;
   int32_t R = 0, stage = 0;
-  if (!b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, a.nrhs, tcb, R, stage, c->lds_limit / 4) &&
+  if (!b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, a.nrhs, tcb, R, stage, c->lds_limit / share) &&
       !b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, a.nrhs, tcb, R, stage, c->lds_limit))
     return fail(SLR_ERR_ARG, "a connector does not fit the LDS of one workgroup");
   a.R = R;
   a.stage_bytes = stage;
   const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)tcb * ((int64_t)I.max_m * R + 1)) +
                      16 * (size_t)(I.max_lev + 1);
-  const int32_t threads = (c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K) > 0 ? 256 : bsolve_threads(0);
+  const int32_t threads = K > 0 ? 256 : bsolve_threads(0);
   if (c->fact_prec == SLR_FP64)
     launch_bsolve<double, double>(I.Bd, I.nb, a, threads, lds, st);
   else if (compute64)
@@ -2314,7 +2319,7 @@ template <typename TS>
 bool upload_inner(slr_ctx *c, const HostSetup &H, BlockArrays<TS> &B, SweepArrays<TS> &Cf, SweepArrays<TS> &Cb) {
   slr_ctx::Inner &I = c->ml;
   BSizes sz;
-  bool ok = pack_blocks<TS>(c->pool, H.c1blocks, B, sz, nullptr, c->lds_limit / 4);
+  bool ok = pack_blocks<TS>(c->pool, H.c1blocks, B, sz, nullptr, c->lds_limit / 2);
   I.max_m = sz.max_m;
   I.max_lev = sz.max_lev;
   I.max_level_bytes = sz.max_level_bytes;
