@@ -202,7 +202,9 @@ __device__ __forceinline__ TC group_sum(TC v, int lg) {
 }
 
 // Barrier of the workgroup that orders LDS accesses only (global loads and
-// direct global-to-LDS copies in flight are not waited for).
+// direct global-to-LDS copies in flight are not waited for).  The builtin by
+// itself orders nothing for the compiler, so every barrier is this one or
+// __syncthreads.
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
@@ -284,10 +286,7 @@ struct SegCols {
 
 // n barriers (LDS only): before a task that uses earlier tasks' results
 __device__ __forceinline__ void pass_barriers(int n) {
-  if (n > 0) {
-    lds_barrier();
-    for (int i = 1; i < n; ++i) __builtin_amdgcn_s_barrier();
-  }
+  for (int i = 0; i < n; ++i) lds_barrier();
 }
 
 // ELL task at LDS address `at` (layout with BlockDesc): the rows of 64 lanes,
@@ -845,13 +844,15 @@ __device__ __forceinline__ void segments_pipelined(const uint8_t *fdata, const i
     place(q + 1);
     for (int i = 5; i > 0; --i) c[i] = c[i - 1];
     c[0] = nvq > 0 ? stage_wave(src, nvq, stage + to * slot, k, lane) : 0;
-    for (int i = 0; i < bars; ++i) __builtin_amdgcn_s_barrier();
+    pass_barriers(bars);
     int flight = 0;
 #pragma unroll
     for (int i = 0; i < 5; ++i)
       if (i < ahead - lag) flight += c[i];
     wait_loads(flight);
-    __builtin_amdgcn_s_barrier();
+    // ordered: the next segment's barrier count and, after the last one, x are
+    // read behind it, in part written by other waves
+    lds_barrier();
     if (++at == slots) at = 0;
     if (++to == slots) to = 0;
     if (!own && g + 1 < n) nb = *reinterpret_cast<const uint16_t *>(stage + at * slot);
