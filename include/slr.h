@@ -225,6 +225,24 @@ typedef struct {
   int32_t b_lds_level_order;
 } slr_info;
 
+/* Which of several forms a context's solves take (slr_query_forms). */
+typedef struct {
+  int64_t c_lead;         /* leading rows of C's factor that fall into
+                             independent blocks (0 when c_deep is 0)         */
+  int64_t c2_lead;        /* the same of C2's (recursive interface solver)   */
+  int32_t c_deep;         /* 1: the sweeps of C's factor run by blocks in the
+                             B kernel, 0: by launches of their own           */
+  int32_t c_blocks;       /* workgroups of the leading blocks                */
+  int32_t c2_deep, c2_blocks;
+  int32_t refactor_blocks; /* B_i refactored a workgroup each (0: level by
+                             level, or no opts.refactor)                     */
+  int32_t b_slots;        /* segments of a B sweep of any row width that fit
+                             the LDS at once, one column (0: rows of fixed
+                             width)                                          */
+  int32_t c1_slots;       /* the same of the connector solves                */
+  int32_t reserved;
+} slr_forms;
+
 typedef struct slr_ctx slr_ctx;
 typedef struct slr_batch slr_batch;
 
@@ -403,6 +421,10 @@ int slr_trim(slr_ctx *c);
 
 /* slr_query: sizes, level depths, theta, timings, memory. */
 int slr_query(const slr_ctx *c, slr_info *info);
+
+/* slr_query_forms: which forms the context's solves take (they depend on
+ * the sizes and patterns only). */
+int slr_query_forms(const slr_ctx *c, slr_forms *forms);
 
 /* slr_export: copy setup results to host buffers (any may be NULL):
  * perm (n int64, internal -> original index), ritz (lanczos_steps values,

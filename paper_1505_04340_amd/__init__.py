@@ -93,6 +93,12 @@ class slr_info(ctypes.Structure):
                 ("tune_b_persistentM", _I32), ("b_lds_level_order", _I32)]
 
 
+class slr_forms(ctypes.Structure):
+    _fields_ = [("c_lead", _I64), ("c2_lead", _I64), ("c_deep", _I32), ("c_blocks", _I32), ("c2_deep", _I32),
+                ("c2_blocks", _I32), ("refactor_blocks", _I32), ("b_slots", _I32), ("c1_slots", _I32),
+                ("reserved", _I32)]
+
+
 def _sig(name, res, args):
     f = getattr(_lib, name)
     f.restype = res
@@ -125,6 +131,7 @@ SLR_ALLOC_FN = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_
 SLR_FREE_FN = ctypes.CFUNCTYPE(None, ctypes.c_void_p, ctypes.c_void_p)
 slr_set_allocator = _sig("slr_set_allocator", None, [SLR_ALLOC_FN, SLR_FREE_FN, _P])
 slr_query = _sig("slr_query", ctypes.c_int, [_P, ctypes.POINTER(slr_info)])
+slr_query_forms = _sig("slr_query_forms", ctypes.c_int, [_P, ctypes.POINTER(slr_forms)])
 slr_export = _sig("slr_export", ctypes.c_int, [_P, _P, _P, _P, _P, _P, _P])
 slr_export_inner = _sig("slr_export_inner", ctypes.c_int, [_P, _P, _P, _P])
 slr_set_bsolve_plan = _sig("slr_set_bsolve_plan", ctypes.c_int, [_P, _I32, _I32, _I32, _I32, _I32])
@@ -144,7 +151,7 @@ slr_device_lds_bytes = _sig("slr_device_lds_bytes", ctypes.c_int, [])
 EXPORTED = ("slr_default_opts", "slr_default_solve_opts", "slr_setup", "slr_analyze", "slr_update_lowrank",
             "slr_grow_lowrank", "slr_refactor",
             "slr_time_kernel", "slr_apply", "slr_apply_dd", "slr_apply_dd_noalloc",
-            "slr_solve", "slr_solve_workspace_bytes", "slr_query", "slr_export", "slr_export_inner", "slr_spmv",
+            "slr_solve", "slr_solve_workspace_bytes", "slr_query", "slr_query_forms", "slr_export", "slr_export_inner", "slr_spmv",
             "slr_trim", "slr_export_setup", "slr_import", "slr_set_allocator", "slr_autotune", "slr_set_bsolve_plan",
             "slr_batch_create", "slr_batch_admit", "slr_batch_step", "slr_batch_poll",
             "slr_batch_active", "slr_batch_bytes", "slr_batch_destroy", "slr_destroy",
@@ -427,6 +434,12 @@ class SLR:
         i = slr_info()
         _check(slr_query(self._h, ctypes.byref(i)), "slr_query")
         return {f: getattr(i, f) for f, _ in slr_info._fields_}
+
+    def forms(self) -> dict:
+        """Which forms the solves take (slr_query_forms)."""
+        f = slr_forms()
+        _check(slr_query_forms(self._h, ctypes.byref(f)), "slr_query_forms")
+        return {n: getattr(f, n) for n, _ in slr_forms._fields_ if n != "reserved"}
 
     def export(self) -> dict:
         inf = self.query()

@@ -583,32 +583,41 @@ bool b_lds_plan(const slr_ctx *c, int32_t nrhs, size_t tc_bytes, int32_t &R, int
                        limit == 0 ? c->lds_limit : limit);
 }
 
+// Columns per workgroup, stage and threads of a B solve of nrhs columns.
 // With more subdomains than compute units and one right-hand side, the B
 // kernel runs two workgroups per CU: half the threads (one solver wave,
 // the rest staging) and at most half the LDS each, so that the second
 // round of subdomains runs beside the first instead of after it.
-template <typename TS, typename TC>
-int run_bsolve(slr_ctx *c, const BlockArrays<TS> &B, const BArgs &a0, hipStream_t st) {
-  BArgs a = a0;
-  int32_t R = 0, stage = 0;
-  int32_t threads = c->b_threads;
-  const slr_ctx::BTune &tu = a.nrhs == 1 ? c->tune1 : c->tuneM;
-  const bool pair = a.nrhs == 1 && (int64_t)c->p > (int64_t)c->n_cu;
+bool b_plan(const slr_ctx *c, int32_t pack_K, int32_t nrhs, size_t tc_bytes, int32_t &R, int32_t &stage,
+            int32_t &threads) {
+  threads = c->b_threads;
+  const slr_ctx::BTune &tu = nrhs == 1 ? c->tune1 : c->tuneM;
+  const bool pair = nrhs == 1 && (int64_t)c->p > (int64_t)c->n_cu;
   // No more columns a workgroup than fill the compute units: the waves of a
   // workgroup share one LDS, and its columns' sweeps run no faster than that
   // serves them.  64 subdomains of 4096 rows, 8 columns (FP32): 51.6 / 63.8 us
   // the two solves with all columns in one workgroup, 25.0 / 28.8 with two;
   // 16 of 4096, 16 columns: 57.4 / 65.6 against 32.1 / 34.0 with one.
   const int32_t fill =
-      (int32_t)std::min<int64_t>(a.nrhs, ((int64_t)c->p * a.nrhs + c->n_cu - 1) / std::max(c->n_cu, 1));
-  if (tu.threads > 0 && b_lds_plan(c, std::min(a.nrhs, tu.rmax), sizeof(TC), R, stage, c->lds_limit / tu.lds_div)) {
+      (int32_t)std::min<int64_t>(nrhs, ((int64_t)c->p * nrhs + c->n_cu - 1) / std::max(c->n_cu, 1));
+  if (tu.threads > 0 && b_lds_plan(c, std::min(nrhs, tu.rmax), tc_bytes, R, stage, c->lds_limit / tu.lds_div)) {
     threads = tu.threads;
-  } else if (pair && b_lds_plan(c, a.nrhs, sizeof(TC), R, stage, c->lds_limit / 2)) {
+  } else if (pair && b_lds_plan(c, nrhs, tc_bytes, R, stage, c->lds_limit / 2)) {
     threads = c->b_threads / 2;
-  } else if (!b_lds_plan(c, fill, sizeof(TC), R, stage)) {
-    return fail(SLR_ERR_ARG, "a subdomain does not fit the LDS of one workgroup");
+  } else if (!b_lds_plan(c, fill, tc_bytes, R, stage)) {
+    return false;
   }
-  if (B.pack_K == 0) threads = bsolve_threads(0);   // its programs are laid out for that many waves
+  if (pack_K == 0) threads = bsolve_threads(0);   // its programs are laid out for that many waves
+  return true;
+}
+
+template <typename TS, typename TC>
+int run_bsolve(slr_ctx *c, const BlockArrays<TS> &B, const BArgs &a0, hipStream_t st) {
+  BArgs a = a0;
+  int32_t R = 0, stage = 0, threads = 0;
+  const slr_ctx::BTune &tu = a.nrhs == 1 ? c->tune1 : c->tuneM;
+  if (!b_plan(c, B.pack_K, a.nrhs, sizeof(TC), R, stage, threads))
+    return fail(SLR_ERR_ARG, "a subdomain does not fit the LDS of one workgroup");
   a.R = R;
   a.stage_bytes = stage;
   const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)sizeof(TC) * (c->b_max_m * R + 1)) +
@@ -726,23 +735,28 @@ void csweep2(slr_ctx *c, bool fwd, const double *x, int64_t ldx, double *y, int6
 // 2 = L1^{-T} only, 3 = both); a quarter of the LDS per workgroup (half for
 // rows of any width) when the connectors fit it, so that several share a
 // compute unit.
-int c1solve(slr_ctx *c, BArgs a, int32_t sweeps, bool compute64, hipStream_t st) {
+bool c1_plan(const slr_ctx *c, int32_t nrhs, size_t tcb, int32_t &R, int32_t &stage, int32_t &threads) {
   const slr_ctx::Inner &I = c->ml;
-  a.sweeps = sweeps;
-  const size_t tcb = (c->fact_prec == SLR_FP64 || compute64) ? 8 : 4;
   // Sweeps of any width take 8 waves of 116 registers: two workgroups fit a
   // compute unit, whatever their LDS (540 blocks of about 410 rows, a half
   // solve: 150 us at a quarter each, 106 at a half with longer segments).
   const int32_t K = c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K, share = K > 0 ? 4 : 2;
-  int32_t R = 0, stage = 0;
-  if (!b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, a.nrhs, tcb, R, stage, c->lds_limit / share) &&
-      !b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, a.nrhs, tcb, R, stage, c->lds_limit))
+  threads = K > 0 ? 256 : bsolve_threads(0);
+  return b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, nrhs, tcb, R, stage, c->lds_limit / share) ||
+         b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, nrhs, tcb, R, stage, c->lds_limit);
+}
+
+int c1solve(slr_ctx *c, BArgs a, int32_t sweeps, bool compute64, hipStream_t st) {
+  const slr_ctx::Inner &I = c->ml;
+  a.sweeps = sweeps;
+  const size_t tcb = (c->fact_prec == SLR_FP64 || compute64) ? 8 : 4;
+  int32_t R = 0, stage = 0, threads = 0;
+  if (!c1_plan(c, a.nrhs, tcb, R, stage, threads))
     return fail(SLR_ERR_ARG, "a connector does not fit the LDS of one workgroup");
   a.R = R;
   a.stage_bytes = stage;
   const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)tcb * ((int64_t)I.max_m * R + 1)) +
                      16 * (size_t)(I.max_lev + 1);
-  const int32_t threads = K > 0 ? 256 : bsolve_threads(0);
   if (c->fact_prec == SLR_FP64)
     launch_bsolve<double, double>(I.Bd, I.nb, a, threads, lds, st);
   else if (compute64)
@@ -3530,6 +3544,26 @@ int slr_query(const slr_ctx *c, slr_info *info) {
   info->device_bytes =
       c->pool.bytes + c->lrpool.bytes + c->ws.pool.bytes + c->spool.bytes + c->ppool.bytes + c->rf.pool.bytes +
       c->schedpool.bytes + (int64_t)(c->lz.cap + c->gm.cap);
+  return SLR_OK;
+}
+
+int slr_query_forms(const slr_ctx *c, slr_forms *f) {
+  if (!c || !f) return fail(SLR_ERR_ARG, "null");
+  *f = slr_forms{};
+  const bool d = c->fact_prec == SLR_FP64;
+  const size_t tcb = d ? 8 : 4;
+  f->c_deep = c->cdeep.on;
+  f->c_lead = c->cdeep.on ? c->cdeep.t : 0;
+  f->c_blocks = f->c_lead > 0 ? c->cdeep.lead.nb : 0;
+  f->c2_deep = c->ml.deep.on;
+  f->c2_lead = c->ml.deep.on ? c->ml.deep.t : 0;
+  f->c2_blocks = f->c2_lead > 0 ? c->ml.deep.lead.nb : 0;
+  f->refactor_blocks = c->rf.on ? c->rf.fblk.nb : 0;
+  int32_t R = 0, stage = 0, threads = 0;
+  const int32_t K = d ? c->Bd.pack_K : c->Bf.pack_K, K1 = d ? c->ml.Bd.pack_K : c->ml.Bf.pack_K;
+  if (K == 0 && b_plan(c, K, 1, tcb, R, stage, threads)) f->b_slots = ring_slots(stage, c->b_max_level_bytes);
+  if (c->ml.on && K1 == 0 && c1_plan(c, 1, tcb, R, stage, threads))
+    f->c1_slots = ring_slots(stage, c->ml.max_level_bytes);
   return SLR_OK;
 }
 

@@ -126,6 +126,12 @@ __host__ __device__ constexpr int rec_passes(int K) { return K <= 2 ? 4 : (K == 
 // solver waves their programs are laid out for and the stagers.
 __host__ __device__ constexpr int bsolve_threads(int pack_K) { return pack_K > 0 ? 1024 : 64 * (kSegWaves + kSegStagers); }
 
+// Sweeps of any width: slots of a ring of segments in the stage.
+__host__ __device__ constexpr int ring_slots(int stage_bytes, int max_segment) {
+  const int slot = (max_segment + 15) & ~15, n = stage_bytes / (slot > 0 ? slot : 1);
+  return n < 8 ? n : 8;
+}
+
 struct BArgs {
   const double *f = nullptr;  int64_t ldf = 0;  double a_f = 0.0;
   const double *y = nullptr;  int64_t ldy = 0;  double b_y = 0.0;

@@ -1012,7 +1012,7 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
   // the sweeps this launch runs (a.sweeps: bit 0 forward, bit 1 backward)
   const int fn = (a.sweeps & 1) ? d.f_nlev : 0, bn = (a.sweeps & 2) ? d.b_nlev : 0;
   // sweeps of any width: the ring of segments in the stage
-  const int slot = KE == 0 ? pad16(B.max_level_bytes) : 0, slots = KE == 0 ? min(a.stage_bytes / max(slot, 1), 8) : 0;
+  const int slot = KE == 0 ? pad16(B.max_level_bytes) : 0, slots = KE == 0 ? ring_slots(a.stage_bytes, B.max_level_bytes) : 0;
   {
     // the upper half of the waves stages the first part of the sweeps meanwhile
     if (tid >= nt / 2) {
