@@ -332,9 +332,7 @@ int slr_grow_lowrank(slr_ctx *c, int32_t k_add, int32_t lanczos_steps, const dou
  * one workgroup), and every stored coefficient of the
  * apply (sweep scales and weights, E, E^T, A for the Krylov products) is
  * rewritten in place in the context's storage precision; the results equal
- * those of a fresh slr_setup with the new values (to rounding where the
- * interface schedule is deep: such a context keeps one launch per level, a
- * context set up without opts.refactor solves it by blocks).  The low-rank part
+ * those of a fresh slr_setup with the new values.  The low-rank part
  * (U_k, Lambda_k, theta) is kept: call slr_update_lowrank to rebuild it for
  * the new H.  Errors: SLR_ERR_NOT_SYMMETRIC (every value must equal its
  * mirror's; checked where the values are),

@@ -380,7 +380,7 @@ struct slr_ctx {
     struct Map {
       RfMap *m = nullptr;
       int64_t n = 0;
-    } bdata, ev, tv, cfsc, cfw, cfw2, cbsc, cbw, cbw2;
+    } bdata, ev, tv, cfsc, cfw, cfw2, cbsc, cbw, cbw2, dlead, dlev, drest, det;
   } rf;
   // stats
   slr_info info{};
@@ -1390,6 +1390,11 @@ struct RfMaps {
   std::vector<RfMap> bdata, ev, tv;   // B sweep streams, E and E^T values
   RfSweepMaps cf, cb;                 // interface sweeps
 };
+// those of a deep interface factor's block form
+struct RfDeepMaps {
+  RfMaps lead, rest;
+  std::vector<RfMap> et;
+};
 
 // Coefficient sources of the stored scale / weights of sweep row t (for the
 // device refactorisation; ebase = first entry of the factor).
@@ -1995,9 +2000,12 @@ bool pack_blocks(DevPool &P, const std::vector<Block> &blocks, BlockArrays<TS> &
       for (int32_t e = 0; e < b.e_ptr[i + 1] - b.e_ptr[i]; ++e) {
         e_q[d.e_ent + (size_t)e * d.e_n + i] = b.e_q[b.e_ptr[i] + e];
         e_val[d.e_ent + (size_t)e * d.e_n + i] = b.e_val[b.e_ptr[i] + e];
-        if (rm)
-          rm->ev.push_back(RfMap{(int64_t)sizeof(TS) * (int64_t)(d.e_ent + (size_t)e * d.e_n + i),
-                                 (int32_t)b.e_src[b.e_ptr[i] + e], 0, 0, RF_SRC});
+        if (rm) {
+          const int64_t off = (int64_t)sizeof(TS) * (int64_t)(d.e_ent + (size_t)e * d.e_n + i);
+          const int32_t at = b.e_ptr[i] + e;
+          rm->ev.push_back(b.e_fac.empty() ? RfMap{off, (int32_t)b.e_src[at], 0, 0, RF_SRC}
+                                           : RfMap{off, b.e_fac[at], b.e_diag[at], 0, RF_ENT});
+        }
       }
     // E^T rows as ELL
     d.t_row = (int32_t)t_q.size();
@@ -2090,13 +2098,17 @@ bool upload_sweep(DevPool &P, const Sweep &sw, SweepArrays<TS> &S, RfSweepMaps *
 }
 
 // Rows [lo, hi) of a sweep as a sweep of their own (local rows), and their
-// entries to other rows through out(local row, row, weight / scale).
+// entries to other rows through out(local row, row, weight / scale, entry,
+// diagonal) with the factor's entries behind the weight, where they are kept.
 template <class Out>
 Sweep sub_sweep(const Sweep &sw, const std::vector<int32_t> &slots, int32_t lo, int32_t hi, Out out) {
   const int32_t m = hi - lo;
+  const bool src = !sw.w_e.empty() || !sw.sc_e.empty();
   std::vector<int32_t> depth(std::max(m, 1), 0);
   Sweep o;
   o.nrows = m;
+  o.divided = sw.divided;
+  o.unit_sc = sw.unit_sc;
   for (int32_t t : slots) {   // in solve order
     const int32_t r = sw.rows[t] - lo;
     for (int32_t e = sw.rp[t]; e < sw.rp[t + 1]; ++e)
@@ -2113,12 +2125,14 @@ Sweep sub_sweep(const Sweep &sw, const std::vector<int32_t> &slots, int32_t lo, 
     const int32_t r = sw.rows[t] - lo;
     o.rows.push_back(r);
     o.sc.push_back(sw.sc[t]);
+    if (src) o.sc_e.push_back(sw.sc_e[t]);
     for (int32_t e = sw.rp[t]; e < sw.rp[t + 1]; ++e) {
       if (sw.ci[e] >= lo && sw.ci[e] < hi) {
         o.ci.push_back(sw.ci[e] - lo);
         o.w.push_back(sw.w[e]);
+        if (src) o.w_e.push_back(sw.w_e[e]);
       } else {
-        out(r, sw.ci[e], sw.w[e] / sw.sc[t]);
+        out(r, sw.ci[e], sw.w[e] / sw.sc[t], src ? sw.w_e[e] : -1, src ? sw.sc_e[t] : -1);
       }
     }
     o.rp.push_back((int32_t)o.ci.size());
@@ -2150,9 +2164,10 @@ double deep_sweep_us(const Sweep &sw, bool runs) {
 // (HID order) make the pieces; without them a factor that fits one
 // workgroup's LDS is one block.  lanes >= 0: every row in that many lanes
 // (log2) and no near-chains, which keeps the sums of launch_sweep with the
-// same lanes; only for t == 0.
+// same lanes; only for t == 0.  rm: where the coefficients come from.
 template <typename TS>
-bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32_t lanes, slr_ctx::Deep &D) {
+bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32_t lanes, slr_ctx::Deep &D,
+                RfDeepMaps *rm = nullptr) {
   const int32_t s = f.nrows;
   D.on = false;
   if (std::max(f.nlev, b.nlev) <= 8) return true;   // a few wide launches
@@ -2223,7 +2238,12 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
     bs[blk[b.rows[k]]].push_back(k);
   }
   std::vector<Block> lead(nb), rest(1);
-  std::vector<std::vector<std::pair<int32_t, double>>> et(s - t);
+  struct Ent {
+    int32_t col;
+    double v;
+    int32_t fac, diag;
+  };
+  std::vector<std::vector<Ent>> et(s - t);
   double us = 0.0;
   for (int32_t q = 0; q <= nb; ++q) {
     Block &k = q < nb ? lead[q] : rest[0];
@@ -2232,16 +2252,22 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
     k.m = hi - lo;
     k.lanes = lanes;
     k.runs = lanes < 0;
-    k.fwd = sub_sweep(f, fs[q], lo, hi, [&](int32_t r, int32_t col, double w) { et[r].emplace_back(col, w); });
-    std::vector<std::vector<std::pair<int32_t, double>>> e(q < nb ? k.m : 0);
-    k.bwd = sub_sweep(b, bs[q], lo, hi, [&](int32_t r, int32_t col, double w) { e[r].emplace_back(col - t, w); });
+    k.fwd = sub_sweep(f, fs[q], lo, hi, [&](int32_t r, int32_t col, double v, int32_t fac, int32_t diag) {
+      et[r].push_back(Ent{col, v, fac, diag});
+    });
+    std::vector<std::vector<Ent>> e(q < nb ? k.m : 0);
+    k.bwd = sub_sweep(b, bs[q], lo, hi, [&](int32_t r, int32_t col, double v, int32_t fac, int32_t diag) {
+      e[r].push_back(Ent{col - t, v, fac, diag});
+    });
     for (int32_t r = 0; r < (int32_t)e.size(); ++r) {
       if (e[r].empty()) continue;
       k.e_row.push_back(r);
       k.e_ptr.push_back((int32_t)k.e_q.size());
-      for (const auto &pr : e[r]) {
-        k.e_q.push_back(pr.first);
-        k.e_val.push_back(pr.second);
+      for (const Ent &x : e[r]) {
+        k.e_q.push_back(x.col);
+        k.e_val.push_back(x.v);
+        k.e_fac.push_back(x.fac);
+        k.e_diag.push_back(x.diag);
       }
     }
     k.e_ptr.push_back((int32_t)k.e_q.size());
@@ -2252,13 +2278,13 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
   if (us + 20.0 > 0.7 * old_us) return true;
   D.t = t;
   D.s = s;
-  auto pack = [&](const std::vector<Block> &blocks, slr_ctx::Deep::Part &P) {
+  auto pack = [&](const std::vector<Block> &blocks, slr_ctx::Deep::Part &P, RfMaps *pm) {
     BSizes sz;
     bool ok;
     if constexpr (sizeof(TS) == 8)
-      ok = pack_blocks<TS>(c->pool, blocks, P.Bd, sz, nullptr, c->lds_limit);
+      ok = pack_blocks<TS>(c->pool, blocks, P.Bd, sz, pm, c->lds_limit);
     else
-      ok = pack_blocks<TS>(c->pool, blocks, P.Bf, sz, nullptr, c->lds_limit);
+      ok = pack_blocks<TS>(c->pool, blocks, P.Bf, sz, pm, c->lds_limit);
     P.nb = (int32_t)blocks.size();
     P.max_m = sz.max_m;
     P.max_lev = sz.max_lev;
@@ -2268,15 +2294,17 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
     return ok && b_lds_plan_sz(P.max_m, P.max_lev, P.max_level_bytes, P.data_bytes, 1, 8, R, stage, c->lds_limit);
   };
   // a task or a table that does not fit leaves the schedule's own launches
-  if ((nb > 0 && !pack(lead, D.lead)) || !pack(rest, D.rest)) return true;
+  if ((nb > 0 && !pack(lead, D.lead, rm ? &rm->lead : nullptr)) || !pack(rest, D.rest, rm ? &rm->rest : nullptr))
+    return true;
   if (t > 0) {
     std::vector<int64_t> rp(1, 0);
     std::vector<int32_t> ci;
     std::vector<double> v;
     for (const auto &row : et) {
-      for (const auto &pr : row) {
-        ci.push_back(pr.first);
-        v.push_back(pr.second);
+      for (const Ent &x : row) {
+        if (rm) rm->et.push_back(RfMap{(int64_t)sizeof(double) * (int64_t)v.size(), x.fac, x.diag, 0, RF_ENT64});
+        ci.push_back(x.col);
+        v.push_back(x.v);
       }
       rp.push_back((int64_t)ci.size());
     }
@@ -2429,7 +2457,7 @@ bool fact_blocks(slr_ctx *c, const HostSetup &H) {
 
 // Keep what slr_refactor needs: the input pattern (symmetry check), the
 // gather maps of A / E / E^T, the factor plans and the coefficient maps.
-bool rf_upload(slr_ctx *c, const HostSetup &H, const RfMaps &rm, const slr_csr *A) {
+bool rf_upload(slr_ctx *c, const HostSetup &H, const RfMaps &rm, const RfDeepMaps &dm, const slr_csr *A) {
   auto &R = c->rf;
   auto &P = R.pool;
   // mirror entries (the symmetry test of new values becomes one pass)
@@ -2470,6 +2498,9 @@ bool rf_upload(slr_ctx *c, const HostSetup &H, const RfMaps &rm, const slr_csr *
   ok = ok && map(rm.bdata, R.bdata) && map(rm.ev, R.ev) && map(rm.tv, R.tv);
   ok = ok && map(rm.cf.sc, R.cfsc) && map(rm.cf.w, R.cfw) && map(rm.cf.w2, R.cfw2);
   ok = ok && map(rm.cb.sc, R.cbsc) && map(rm.cb.w, R.cbw) && map(rm.cb.w2, R.cbw2);
+  if (c->cdeep.on)
+    ok = ok && map(dm.lead.bdata, R.dlead) && map(dm.lead.ev, R.dlev) && map(dm.rest.bdata, R.drest) &&
+         map(dm.et, R.det);
   R.on = ok;
   return ok;
 }
@@ -2495,6 +2526,16 @@ void rf_pack_all(slr_ctx *c, const BlockArrays<TS> &B, const SweepArrays<TS> &Cf
   run(R.cbsc, R.fc.v, Cb.sc);
   run(R.cbw, R.fc.v, Cb.w);
   run(R.cbw2, R.fc.v, Cb.w2);
+  auto part = [&](const slr_ctx::Deep::Part &D) -> const BlockArrays<TS> & {
+    if constexpr (sizeof(TS) == 8)
+      return D.Bd;
+    else
+      return D.Bf;
+  };
+  run(R.dlead, R.fc.v, part(c->cdeep.lead).data);
+  run(R.dlev, R.fc.v, part(c->cdeep.lead).e_val);
+  run(R.drest, R.fc.v, part(c->cdeep.rest).data);
+  run(R.det, R.fc.v, c->cdeep.et_v);
   launch_rf_pack<TS>(P, R.val, st);
 }
 
@@ -3054,7 +3095,6 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
     ok = ok && ok2;
   }
   if (!ok) return destroy_fail(fail(SLR_ERR_OOM, "factor upload (or a subdomain above 65535 rows)"));
-  if (rm && !rf_upload(c, H, *rm, A)) return destroy_fail(fail(SLR_ERR_OOM, "refactorisation plan"));
   if (H.s1 > 0) {
     slr_ctx::Inner &I = c->ml;
     I.on = true;
@@ -3105,12 +3145,15 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
     c->cb_group = sweep_group(H.cbwd);
   }
   c->c_two_level = !c->ml.on && std::max(c->cf_nlev, c->cb_nlev) <= 2;
-  if (!c->ml.on && !c->c_two_level && !c->rf.on) {
+  RfDeepMaps dmaps;
+  RfDeepMaps *dm = rm ? &dmaps : nullptr;
+  if (!c->ml.on && !c->c_two_level) {
     const double old_us = schedule_us(H.cfwd, H.cbwd, c->c_one_wg, c->cf_group, c->cb_group);
-    if (!(c->fact_prec == SLR_FP64 ? deep_build<double>(c, H.cfwd, H.cbwd, old_us, -1, c->cdeep)
-                                   : deep_build<float>(c, H.cfwd, H.cbwd, old_us, -1, c->cdeep)))
+    if (!(c->fact_prec == SLR_FP64 ? deep_build<double>(c, H.cfwd, H.cbwd, old_us, -1, c->cdeep, dm)
+                                   : deep_build<float>(c, H.cfwd, H.cbwd, old_us, -1, c->cdeep, dm)))
       return destroy_fail(fail(SLR_ERR_OOM, "interface factor blocks"));
   }
+  if (rm && !rf_upload(c, H, *rm, dmaps, A)) return destroy_fail(fail(SLR_ERR_OOM, "refactorisation plan"));
   if (c->c_one_wg && sizeof(int32_t) * (size_t)(std::max(c->cf_nlev, c->cb_nlev) + 1) > c->lds_limit)
     return destroy_fail(fail(SLR_ERR_ARG, "interface level schedule too deep for one workgroup"));
   {

@@ -170,8 +170,10 @@ struct BArgs {
 //   RF_RECIP  rd(1 / V[a])                (row scales)
 //   RF_DIV    rd(V[a] / V[b])             (pre-divided weights)
 //   RF_W2     rd(rd(V[a] / V[b]) * rd(1 / V[c]))   (two-level interface weights)
+//   RF_ENT    rd(V[a] / V[b]) / rd(1 / V[b])       (entries between the blocks of a deep factor)
+//   RF_ENT64  the same, stored in FP64 whatever TS is
 // rd() rounds to TS, exactly as the host packing does.
-enum { RF_SRC = 0, RF_ONE, RF_RAW, RF_RECIP, RF_DIV, RF_W2 };
+enum { RF_SRC = 0, RF_ONE, RF_RAW, RF_RECIP, RF_DIV, RF_W2, RF_ENT, RF_ENT64 };
 struct RfMap {
   int64_t off;
   int32_t a, b, c, op;
@@ -179,7 +181,7 @@ struct RfMap {
 
 // every map of a refactorisation in one launch; V: the factor of a map's
 // values (RF_SRC reads val)
-constexpr int kRfMaps = 9;
+constexpr int kRfMaps = 13;
 struct RfPack {
   const RfMap *map[kRfMaps] = {};
   int64_t n[kRfMaps] = {};

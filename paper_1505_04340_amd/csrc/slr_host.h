@@ -48,6 +48,7 @@ struct Block {            // one subdomain
   std::vector<int32_t> t_q, t_ptr, t_j;     // t_j: local interior index
   std::vector<double> t_val;
   std::vector<int64_t> e_src, t_src;        // entries of the input CSR behind e_val / t_val
+  std::vector<int32_t> e_fac, e_diag;       // or the factor's entry behind e_val and its row's diagonal
   int64_t nnz_L = 0;
   int64_t f_base = 0;                       // first entry of this block's factor in the global B factor
   // sweeps of any row width: log2 of the lanes per row (-1: by the rows) and

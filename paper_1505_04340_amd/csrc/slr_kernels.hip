@@ -3760,7 +3760,13 @@ __global__ void k_rf_pack(RfPack P, const double *val) {
     case RF_RECIP: v = rd(1.0 / rd(V[m.a])); break;
     case RF_DIV: v = rd(rd(V[m.a]) / rd(V[m.b])); break;
     case RF_W2: v = rd(rd(rd(V[m.a]) / rd(V[m.b])) * rd(1.0 / rd(V[m.c]))); break;
+    case RF_ENT:
+    case RF_ENT64: v = rd(rd(V[m.a]) / rd(V[m.b])) / rd(1.0 / rd(V[m.b])); break;
     default: break;
+  }
+  if (m.op == RF_ENT64) {
+    *reinterpret_cast<double *>((uint8_t *)P.base[blockIdx.y] + m.off) = v;
+    return;
   }
   *reinterpret_cast<TS *>((uint8_t *)P.base[blockIdx.y] + m.off) = (TS)v;
 }
