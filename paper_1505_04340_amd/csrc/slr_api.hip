@@ -2328,11 +2328,11 @@ double schedule_us(const Sweep &f, const Sweep &b, bool one_wg, int32_t gf, int3
   return one(f, gf) + one(b, gb);
 }
 
+// The B_i's sweeps and couplings.
 template <typename TS>
-void upload_blocks(slr_ctx *c, const HostSetup &H, BlockArrays<TS> &B, SweepArrays<TS> &Cf, SweepArrays<TS> &Cb,
-                   bool &ok, RfMaps *rm) {
+bool upload_blocks(slr_ctx *c, const HostSetup &H, BlockArrays<TS> &B, RfMaps *rm) {
   BSizes sz;
-  ok = pack_blocks<TS>(c->pool, H.blocks, B, sz, rm, c->lds_limit);
+  const bool ok = pack_blocks<TS>(c->pool, H.blocks, B, sz, rm, c->lds_limit);
   c->b_cost_h.clear();
   c->b_m_h.clear();
   for (int32_t q : sz.order) {
@@ -2344,9 +2344,19 @@ void upload_blocks(slr_ctx *c, const HostSetup &H, BlockArrays<TS> &B, SweepArra
   c->b_max_lev = sz.max_lev;
   c->b_max_level_bytes = sz.max_level_bytes;
   c->b_data_bytes = sz.data_bytes;
-  if (H.s1 > 0) return;   // the recursive interface solver has no single factor of C
-  ok = ok && upload_sweep<TS>(c->pool, H.cfwd, Cf, rm ? &rm->cf : nullptr) &&
-       upload_sweep<TS>(c->pool, H.cbwd, Cb, rm ? &rm->cb : nullptr);
+  return ok;
+}
+
+// C's sweeps: the block form where deep_build takes it, else the schedules.
+template <typename TS>
+bool upload_c(slr_ctx *c, const HostSetup &H, SweepArrays<TS> &Cf, SweepArrays<TS> &Cb, RfMaps *rm, RfDeepMaps *dm) {
+  if (!c->c_two_level) {
+    const double old_us = schedule_us(H.cfwd, H.cbwd, c->c_one_wg, c->cf_group, c->cb_group);
+    if (!deep_build<TS>(c, H.cfwd, H.cbwd, old_us, -1, c->cdeep, dm)) return false;
+    if (c->cdeep.on) return true;
+  }
+  return upload_sweep<TS>(c->pool, H.cfwd, Cf, rm ? &rm->cf : nullptr) &&
+         upload_sweep<TS>(c->pool, H.cbwd, Cb, rm ? &rm->cb : nullptr);
 }
 
 // Lanes per row of an interface sweep launched one level at a time: by the
@@ -2558,10 +2568,11 @@ int lowrank_done(slr_ctx *c, double t1, hipStream_t st) {
 // followed by the bytes.  Device arrays are written in a fixed order (the
 // list below), so import can allocate and fill them in that order and
 // point the same fields at them.
-// Version 2 held the sweeps of any row width in another form
-// (convert_streams); everything else is the same.
-constexpr char kSetupMagic[8] = {'S', 'L', 'R', 'S', 'E', 'T', 'v', '3'};
-constexpr char kSetupMagic2[8] = {'S', 'L', 'R', 'S', 'E', 'T', 'v', '2'};
+// Version 3 held no block form of a deep interface factor, which is built
+// from the schedules then; version 2 also held the sweeps of any row width in
+// another form (convert_streams).  Everything else is the same.
+constexpr char kSetupMagic[8] = {'S', 'L', 'R', 'S', 'E', 'T', 'v', '4'};
+constexpr char kSetupOldest = '2';
 
 uint64_t fnv1a(const uint8_t *p, size_t n) {
   uint64_t h = 0xcbf29ce484222325ull;
@@ -2619,15 +2630,26 @@ struct Reader {
   }
 };
 
+template <typename T>
+const void **array_field(T &ptr) {
+  return reinterpret_cast<const void **>(const_cast<void *>((const void *)&ptr));
+}
+template <typename TS>
+std::vector<const void **> block_fields(BlockArrays<TS> &B) {
+  auto f = [](auto &ptr) { return array_field(ptr); };
+  return {f(B.desc), f(B.lev), f(B.lvb),  f(B.data), f(B.e_row), f(B.e_q),
+          f(B.e_val), f(B.t_q), f(B.t_j), f(B.t_val), f(B.xpos)};
+}
+
 // The device arrays of a context that make up its preconditioner (not the
 // low-rank part, not scratch), in serialisation order.  Absent arrays (w2
-// of a deep interface schedule) are null.
+// of a deep interface schedule, the schedules where the block form takes
+// their place) are null.
 template <typename TS>
 std::vector<const void **> setup_fields(slr_ctx *c, BlockArrays<TS> &B, SweepArrays<TS> &Cf, SweepArrays<TS> &Cb) {
-  auto f = [](auto &ptr) { return reinterpret_cast<const void **>(const_cast<void *>((const void *)&ptr)); };
-  std::vector<const void **> v = {f(c->perm), f(c->a_rp), f(c->a_ci), f(c->a_v),
-                                  f(B.desc), f(B.lev), f(B.lvb), f(B.data), f(B.e_row), f(B.e_q), f(B.e_val),
-                                  f(B.t_q), f(B.t_j), f(B.t_val), f(B.xpos)};
+  auto f = [](auto &ptr) { return array_field(ptr); };
+  std::vector<const void **> v = {f(c->perm), f(c->a_rp), f(c->a_ci), f(c->a_v)};
+  for (const void **q : block_fields(B)) v.push_back(q);
   for (SweepArrays<TS> *S : {&Cf, &Cb})
     for (const void **q : {f(S->lev), f(S->rows), f(S->rp), f(S->ci), f(S->w), f(S->sc), f(S->w2)}) v.push_back(q);
   return v;
@@ -2777,9 +2799,8 @@ int export_setup(const slr_ctx *cc, std::vector<uint8_t> &blob) {
   w.pod(c->cf_nlev); w.pod(c->cb_nlev); w.pod(c->cb_nnz);
   w.pod(c->c_one_wg); w.pod(c->c_two_level); w.pod(c->nnz_a); w.pod(c->cf_group); w.pod(c->cb_group);
   w.pod(c->b_max_m); w.pod(c->b_max_lev); w.pod(c->b_max_level_bytes); w.pod(c->b_data_bytes);
-  auto dump = [&](auto &B, auto &Cf, auto &Cb) -> int {
-    w.pod(B.max_m); w.pod(B.max_lev); w.pod(B.max_level_bytes); w.pod(B.max_K); w.pod(B.pack_K);
-    for (const void **q : setup_fields(c, B, Cf, Cb)) {
+  auto arrays = [&](const std::vector<const void **> &fields) -> int {
+    for (const void **q : fields) {
       const size_t b = *q ? pool_block_bytes(c->pool, *q) : 0;
       if (*q && b == 0) return fail(SLR_ERR_ARG, "an array of the context is not in its pool");
       w.pod<uint64_t>(b);
@@ -2789,8 +2810,27 @@ int export_setup(const slr_ctx *cc, std::vector<uint8_t> &blob) {
     }
     return SLR_OK;
   };
+  auto dump = [&](auto &B, auto &Cf, auto &Cb) -> int {
+    w.pod(B.max_m); w.pod(B.max_lev); w.pod(B.max_level_bytes); w.pod(B.max_K); w.pod(B.pack_K);
+    return arrays(setup_fields(c, B, Cf, Cb));
+  };
   int rc = c->fact_prec == SLR_FP64 ? dump(c->Bd, c->Cfd, c->Cbd) : dump(c->Bf, c->Cff, c->Cbf);
   if (rc) return rc;
+  // the block form of a deep interface factor
+  slr_ctx::Deep &D = c->cdeep;
+  w.pod(D.on);
+  if (D.on) {
+    w.pod(D.t); w.pod(D.s);
+    for (slr_ctx::Deep::Part *q : {&D.lead, &D.rest}) {
+      w.pod(q->nb); w.pod(q->max_m); w.pod(q->max_lev); w.pod(q->max_level_bytes); w.pod(q->data_bytes);
+      auto blocks = [&](auto &B) {
+        w.pod(B.max_m); w.pod(B.max_lev); w.pod(B.max_level_bytes); w.pod(B.max_K); w.pod(B.pack_K);
+        return arrays(block_fields(B));
+      };
+      if ((rc = c->fact_prec == SLR_FP64 ? blocks(q->Bd) : blocks(q->Bf))) return rc;
+    }
+    if ((rc = arrays({array_field(D.et_rp), array_field(D.et_ci), array_field(D.et_v)}))) return rc;
+  }
   // launch shapes and rank-k chunks (slr_autotune)
   w.pod(c->tune1); w.pod(c->tuneM); w.pod(c->lr_nblk_tuned); w.pod(c->lrm_nblk);
   w.vec(c->b_cost_h);
@@ -2812,8 +2852,9 @@ int export_setup(const slr_ctx *cc, std::vector<uint8_t> &blob) {
 }
 
 int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out) {
-  const bool v2 = bytes >= 24 && std::memcmp(buf, kSetupMagic2, 8) == 0;
-  if (bytes < 24 || (!v2 && std::memcmp(buf, kSetupMagic, 8) != 0)) return fail(SLR_ERR_ARG, "not a serialised SLR setup");
+  if (bytes < 24 || std::memcmp(buf, kSetupMagic, 7) != 0 || buf[7] < kSetupOldest || buf[7] > kSetupMagic[7])
+    return fail(SLR_ERR_ARG, "not a serialised SLR setup");
+  const int version = buf[7] - '0';
   uint64_t len = 0, h = 0;
   std::memcpy(&len, buf + 8, 8);
   if (len != bytes - 24) return fail(SLR_ERR_ARG, "serialised setup: length mismatch");
@@ -2844,9 +2885,8 @@ int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out
     return bad("inconsistent sizes");
   c->lds_limit = (size_t)slr_device_lds_bytes();
   c->n_cu = device_cu_count();
-  auto load = [&](auto &B, auto &Cf, auto &Cb) -> bool {
-    r.pod(B.max_m); r.pod(B.max_lev); r.pod(B.max_level_bytes); r.pod(B.max_K); r.pod(B.pack_K);
-    for (const void **q : setup_fields(c, B, Cf, Cb)) {
+  auto arrays = [&](const std::vector<const void **> &fields) -> bool {
+    for (const void **q : fields) {
       const uint8_t *src = nullptr;
       uint64_t b = 0;
       if (!r.span(src, b)) return false;
@@ -2860,15 +2900,41 @@ int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out
     }
     return true;
   };
+  auto load = [&](auto &B, auto &Cf, auto &Cb) -> bool {
+    r.pod(B.max_m); r.pod(B.max_lev); r.pod(B.max_level_bytes); r.pod(B.max_K); r.pod(B.pack_K);
+    return arrays(setup_fields(c, B, Cf, Cb));
+  };
   const bool ok = c->fact_prec == SLR_FP64 ? load(c->Bd, c->Cfd, c->Cbd) : load(c->Bf, c->Cff, c->Cbf);
   if (!ok) return bad("device arrays (truncated, or device memory exhausted)");
   if (pool_block_bytes(c->pool, c->perm) != sizeof(int64_t) * (size_t)std::max<int64_t>(c->n, 1) ||
       pool_block_bytes(c->pool, c->a_v) != sizeof(double) * (size_t)std::max<int64_t>(c->nnz_a, 1))
     return bad("array sizes do not match the problem");
-  if (v2 && !(c->fact_prec == SLR_FP64 ? c->Bd.pack_K > 0 || convert_streams(c, c->Bd)
+  if (version == 2 && !(c->fact_prec == SLR_FP64 ? c->Bd.pack_K > 0 || convert_streams(c, c->Bd)
                                        : c->Bf.pack_K > 0 || convert_streams(c, c->Bf)))
     return bad("sweep streams");
-  if (!c->c_two_level) {
+  if (version >= 4) {
+    slr_ctx::Deep &D = c->cdeep;
+    r.pod(D.on);
+    if (r.ok && D.on) {
+      r.pod(D.t); r.pod(D.s);
+      for (slr_ctx::Deep::Part *q : {&D.lead, &D.rest}) {
+        r.pod(q->nb); r.pod(q->max_m); r.pod(q->max_lev); r.pod(q->max_level_bytes); r.pod(q->data_bytes);
+        auto blocks = [&](auto &B) {
+          r.pod(B.max_m); r.pod(B.max_lev); r.pod(B.max_level_bytes); r.pod(B.max_K); r.pod(B.pack_K);
+          return arrays(block_fields(B));
+        };
+        if (!(c->fact_prec == SLR_FP64 ? blocks(q->Bd) : blocks(q->Bf))) return bad("interface factor blocks");
+      }
+      if (!arrays({array_field(D.et_rp), array_field(D.et_ci), array_field(D.et_v)}))
+        return bad("interface factor blocks");
+      int32_t R = 0, stage = 0;
+      auto fits = [&](const slr_ctx::Deep::Part &q) {
+        return q.nb > 0 && b_lds_plan_sz(q.max_m, q.max_lev, q.max_level_bytes, q.data_bytes, 1, 8, R, stage, c->lds_limit);
+      };
+      if (D.s != c->s || D.t < 0 || D.t > D.s || (D.t > 0 && !fits(D.lead)) || !fits(D.rest))
+        return bad("interface factor blocks");
+    }
+  } else if (!c->c_two_level) {
     // the block form of a deep interface factor, from its schedule
     auto host = [&](const void *p, auto &v, size_t n) {
       v.resize(n);
@@ -3087,13 +3153,7 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
   }
   RfMaps rmaps;
   RfMaps *rm = H.have_plan ? &rmaps : nullptr;
-  if (c->fact_prec == SLR_FP64)
-    upload_blocks<double>(c, H, c->Bd, c->Cfd, c->Cbd, ok, rm);
-  else {
-    bool ok2 = true;
-    upload_blocks<float>(c, H, c->Bf, c->Cff, c->Cbf, ok2, rm);
-    ok = ok && ok2;
-  }
+  ok = ok && (c->fact_prec == SLR_FP64 ? upload_blocks<double>(c, H, c->Bd, rm) : upload_blocks<float>(c, H, c->Bf, rm));
   if (!ok) return destroy_fail(fail(SLR_ERR_OOM, "factor upload (or a subdomain above 65535 rows)"));
   if (H.s1 > 0) {
     slr_ctx::Inner &I = c->ml;
@@ -3147,12 +3207,10 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
   c->c_two_level = !c->ml.on && std::max(c->cf_nlev, c->cb_nlev) <= 2;
   RfDeepMaps dmaps;
   RfDeepMaps *dm = rm ? &dmaps : nullptr;
-  if (!c->ml.on && !c->c_two_level) {
-    const double old_us = schedule_us(H.cfwd, H.cbwd, c->c_one_wg, c->cf_group, c->cb_group);
-    if (!(c->fact_prec == SLR_FP64 ? deep_build<double>(c, H.cfwd, H.cbwd, old_us, -1, c->cdeep, dm)
-                                   : deep_build<float>(c, H.cfwd, H.cbwd, old_us, -1, c->cdeep, dm)))
-      return destroy_fail(fail(SLR_ERR_OOM, "interface factor blocks"));
-  }
+  // (the recursive interface solver has no single factor of C)
+  if (!c->ml.on && !(c->fact_prec == SLR_FP64 ? upload_c<double>(c, H, c->Cfd, c->Cbd, rm, dm)
+                                              : upload_c<float>(c, H, c->Cff, c->Cbf, rm, dm)))
+    return destroy_fail(fail(SLR_ERR_OOM, "interface factor upload"));
   if (rm && !rf_upload(c, H, *rm, dmaps, A)) return destroy_fail(fail(SLR_ERR_OOM, "refactorisation plan"));
   if (c->c_one_wg && sizeof(int32_t) * (size_t)(std::max(c->cf_nlev, c->cb_nlev) + 1) > c->lds_limit)
     return destroy_fail(fail(SLR_ERR_ARG, "interface level schedule too deep for one workgroup"));
