@@ -201,14 +201,23 @@ __device__ __forceinline__ TC group_sum(TC v, int lg) {
   return v;
 }
 
-// Barrier of the workgroup that orders LDS accesses only (global loads and
-// direct global-to-LDS copies in flight are not waited for).  The builtin by
-// itself orders nothing for the compiler, so every barrier is this one or
-// __syncthreads.
+// Barrier of the workgroup that orders LDS accesses only (global loads in
+// flight are not waited for).  The builtin by itself orders nothing for the
+// compiler, so every barrier is this one, the next one or __syncthreads.
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The same for waves with direct global-to-LDS copies in flight: a fence waits
+// for them (their target is LDS), so the order is given to the compiler only.
+// The caller waits for the copies that others read after the barrier
+// (wait_loads); a wave's LDS reads are issued in program order.
+__device__ __forceinline__ void stager_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // LDS by byte address (32-bit arithmetic and LDS instructions also where the
@@ -844,15 +853,15 @@ __device__ __forceinline__ void segments_pipelined(const uint8_t *fdata, const i
     place(q + 1);
     for (int i = 5; i > 0; --i) c[i] = c[i - 1];
     c[0] = nvq > 0 ? stage_wave(src, nvq, stage + to * slot, k, lane) : 0;
-    pass_barriers(bars);
+    for (int i = 0; i < bars; ++i) stager_barrier();
     int flight = 0;
 #pragma unroll
     for (int i = 0; i < 5; ++i)
       if (i < ahead - lag) flight += c[i];
     wait_loads(flight);
-    // ordered: the next segment's barrier count and, after the last one, x are
-    // read behind it, in part written by other waves
-    lds_barrier();
+    // (the next segment's barrier count and, after the last one, x are read
+    // behind it, in part written by other waves)
+    stager_barrier();
     if (++at == slots) at = 0;
     if (++to == slots) to = 0;
     if (!own && g + 1 < n) nb = *reinterpret_cast<const uint16_t *>(stage + at * slot);
