@@ -583,6 +583,12 @@ bool b_lds_plan(const slr_ctx *c, int32_t nrhs, size_t tc_bytes, int32_t &R, int
                        limit == 0 ? c->lds_limit : limit);
 }
 
+// Whether workgroups of lds bytes share compute units: more of them than
+// compute units, and room for two.
+bool shared_cu(const slr_ctx *c, int64_t workgroups, size_t lds) {
+  return workgroups > (int64_t)c->n_cu && 2 * lds <= c->lds_limit;
+}
+
 // Columns per workgroup, stage and threads of a B solve of nrhs columns.
 // With more subdomains than compute units and one right-hand side, the B
 // kernel runs two workgroups per CU: half the threads (one solver wave,
@@ -623,6 +629,7 @@ int run_bsolve(slr_ctx *c, const BlockArrays<TS> &B, const BArgs &a0, hipStream_
   const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)sizeof(TC) * (c->b_max_m * R + 1)) +
                     16 * (size_t)(c->b_max_lev + 1);
   int32_t grid = c->p;
+  a.shared = shared_cu(c, (int64_t)c->p * ((a.nrhs + R - 1) / R), lds);
   if (tu.threads > 0 && tu.persistent) {
     // resident workgroups: by waves (32 per CU) and by LDS
     const int32_t per_cu = std::max<int32_t>(1, std::min<int32_t>(2048 / threads, (int32_t)(c->lds_limit / lds)));
@@ -667,6 +674,7 @@ int block_sweep(slr_ctx *c, const slr_ctx::Deep::Part &D, BArgs a, bool compute6
   a.stage_bytes = stage;
   const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)tcb * ((int64_t)D.max_m * R + 1)) +
                      16 * (size_t)(D.max_lev + 1);
+  a.shared = shared_cu(c, (int64_t)D.nb * ((a.nrhs + R - 1) / R), lds);
   const int32_t K = c->fact_prec == SLR_FP64 ? D.Bd.pack_K : D.Bf.pack_K, threads = K > 0 ? 512 : bsolve_threads(0);
   if (c->fact_prec == SLR_FP64)
     launch_bsolve<double, double>(D.Bd, D.nb, a, threads, lds, st);
@@ -732,18 +740,24 @@ void csweep2(slr_ctx *c, bool fwd, const double *x, int64_t ldx, double *y, int6
 
 // ---- recursive interface solver (Sec. 5.2) --------------------------------
 // C1 solves: the B kernel over the connectors (sweeps: 1 = L1^{-1} only,
-// 2 = L1^{-T} only, 3 = both); a quarter of the LDS per workgroup (half for
-// rows of any width) when the connectors fit it, so that several share a
-// compute unit.
+// 2 = L1^{-T} only, 3 = both); a quarter of the LDS per workgroup of 256
+// threads when the connectors fit it, so that several share a compute unit.
+// Sweeps of any width: so where more than two a compute unit wait (each
+// solver wave takes columns of its own), else all waves work on a connector
+// and half of the LDS holds its segments.  A half solve of 540 connectors of
+// about 410 rows 73 us with 256 threads, 84 with 512 (two a compute unit), 106
+// with one a compute unit; of 144 the other way round: C's first half 203 us
+// with 512 threads, 231 with 256.
+bool c1_many(const slr_ctx *c) { return (int64_t)c->ml.nb > 2 * (int64_t)c->n_cu; }
 bool c1_plan(const slr_ctx *c, int32_t nrhs, size_t tcb, int32_t &R, int32_t &stage, int32_t &threads) {
   const slr_ctx::Inner &I = c->ml;
-  // Sweeps of any width take 8 waves of 116 registers: two workgroups fit a
-  // compute unit, whatever their LDS (540 blocks of about 410 rows, a half
-  // solve: 150 us at a quarter each, 106 at a half with longer segments).
-  const int32_t K = c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K, share = K > 0 ? 4 : 2;
-  threads = K > 0 ? 256 : bsolve_threads(0);
-  return b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, nrhs, tcb, R, stage, c->lds_limit / share) ||
-         b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, nrhs, tcb, R, stage, c->lds_limit);
+  const int32_t K = c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K;
+  const int32_t share = K > 0 || c1_many(c) ? 4 : 2;
+  threads = share == 4 ? 256 : bsolve_threads(0);
+  if (b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, nrhs, tcb, R, stage, c->lds_limit / share))
+    return true;
+  if (K == 0) threads = bsolve_threads(0);
+  return b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, nrhs, tcb, R, stage, c->lds_limit);
 }
 
 int c1solve(slr_ctx *c, BArgs a, int32_t sweeps, bool compute64, hipStream_t st) {
@@ -757,6 +771,7 @@ int c1solve(slr_ctx *c, BArgs a, int32_t sweeps, bool compute64, hipStream_t st)
   a.stage_bytes = stage;
   const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)tcb * ((int64_t)I.max_m * R + 1)) +
                      16 * (size_t)(I.max_lev + 1);
+  a.shared = shared_cu(c, (int64_t)I.nb * ((a.nrhs + R - 1) / R), lds);
   if (c->fact_prec == SLR_FP64)
     launch_bsolve<double, double>(I.Bd, I.nb, a, threads, lds, st);
   else if (compute64)
@@ -2371,7 +2386,7 @@ template <typename TS>
 bool upload_inner(slr_ctx *c, const HostSetup &H, BlockArrays<TS> &B, SweepArrays<TS> &Cf, SweepArrays<TS> &Cb) {
   slr_ctx::Inner &I = c->ml;
   BSizes sz;
-  bool ok = pack_blocks<TS>(c->pool, H.c1blocks, B, sz, nullptr, c->lds_limit / 2);
+  bool ok = pack_blocks<TS>(c->pool, H.c1blocks, B, sz, nullptr, c->lds_limit / (c1_many(c) ? 4 : 2));
   I.max_m = sz.max_m;
   I.max_lev = sz.max_lev;
   I.max_level_bytes = sz.max_level_bytes;

@@ -122,8 +122,9 @@ __host__ __device__ constexpr int rec_width(int K) { return (K + 1 + 3) & ~3; }
 // independent, so any split of a level is a valid schedule).
 __host__ __device__ constexpr int rec_passes(int K) { return K <= 2 ? 4 : (K == 3 ? 3 : 2); }
 
-// Most threads of a B kernel workgroup; sweeps of any width always take the
-// solver waves their programs are laid out for and the stagers.
+// Most threads of a B kernel workgroup.  Sweeps of any width: the solver waves
+// that their programs are laid out for and the stagers; with fewer waves each
+// solver wave takes columns of its own.
 __host__ __device__ constexpr int bsolve_threads(int pack_K) { return pack_K > 0 ? 1024 : 64 * (kSegWaves + kSegStagers); }
 
 // Sweeps of any width: slots of a ring of segments in the stage.
@@ -159,6 +160,7 @@ struct BArgs {
   // (first column << 16) | (columns << 24), each subdomain's x stored with
   // its own row count as stride, as many columns as the x region holds
   int32_t var_cols = 0;
+  int32_t shared = 0;         // several workgroups a compute unit (sweeps of any width: fewer registers)
 };
 
 // Numeric refactorisation on the device: one stored coefficient (TS) at

@@ -307,6 +307,9 @@ __device__ __forceinline__ void pass_barriers(int n) {
 template <typename TS, typename TC, int B, int NB>
 __device__ __forceinline__ void ell_task(uint32_t at, int lg, int nb, int nbar, const SegCols &cols, int lane) {
   constexpr uint32_t es = sizeof(TC), ts = sizeof(TS);
+  // (addresses are worked out here: kept over the tasks they would not fit
+  // the registers, and their reload takes a memory latency per task)
+  asm("" : "+v"(lane));
   const uint32_t raw = lds_get<uint32_t>(at + 4 * lane);
   const TS sc = lds_get<TS>(at + 256 + ts * lane);
   const uint32_t o_ix = at + 256 + 64 * ts + 2 * B * lane;
@@ -437,35 +440,41 @@ __device__ __forceinline__ void panel_task(uint32_t at, int R, int nbar, const S
   }
 }
 
+// Whether the solver waves of a workgroup take columns of their own: from
+// kSegColumns columns on, and where there are fewer of them than programs.
+__device__ __forceinline__ bool own_columns(int Rg, int solvers) { return Rg >= kSegColumns || solvers < kSegWaves; }
+
 // n segments of sweeps of any width, segment g in ring slot g % slots (of
 // slot bytes, from LDS address ring), for Rg columns (xs: address of x, cs:
-// bytes from column to column), by the waves wv < kSegWaves.  Few columns:
+// bytes from column to column), by the waves wv < solvers.  Few columns:
 // each wave runs its own program of a segment, the tasks of a level being
-// spread over the waves, with barriers where the programs have them.  From
-// kSegColumns columns on: each wave runs all tasks for columns of its own (a
-// wave's LDS accesses take effect in program order).  A barrier ends each
+// spread over the waves, with barriers where the programs have them.  Else
+// (own_columns) each wave runs all tasks for columns of its own (a wave's LDS
+// accesses take effect in program order).  A barrier ends each
 // segment.  The host lays the programs out so that the waves decode one
 // word per task: a wave alone on its SIMD is bound by the instructions it
 // issues (five cycles each), and working shapes out of segment headers took
 // 2400 cycles a level.  Lane i holds word i of the program.  Not inlined: the
 // kernel's own values would push this loop's scalars out of their
 // registers.
-template <typename TS, typename TC>
+// (kernels with more registers call an instance of their own: MANY)
+template <typename TS, typename TC, bool MANY>
 __device__ __attribute__((noinline)) void run_segments(uint32_t ring, int slot, int slots, int n, uint32_t xs,
-                                                       uint32_t cs, int Rg, int wv) {
+                                                       uint32_t cs, int Rg, int wv, int solvers) {
   const int lane = threadIdx.x & 63;
   ring = __builtin_amdgcn_readfirstlane(ring);
   slot = __builtin_amdgcn_readfirstlane(slot);
   slots = __builtin_amdgcn_readfirstlane(slots);
   n = __builtin_amdgcn_readfirstlane(n);
   wv = __builtin_amdgcn_readfirstlane(wv);
+  solvers = __builtin_amdgcn_readfirstlane(solvers);
   SegCols cols;
   cols.xs = __builtin_amdgcn_readfirstlane(xs);
   cols.cs = __builtin_amdgcn_readfirstlane(cs);
   cols.Rg = __builtin_amdgcn_readfirstlane(Rg);
-  const bool own = cols.Rg >= kSegColumns;
+  const bool own = own_columns(cols.Rg, solvers);
   cols.r0 = own ? wv : 0;
-  cols.dr = own ? kSegWaves : 1;
+  cols.dr = own ? solvers : 1;
   uint32_t at = ring;
   const uint32_t end = ring + slot * slots;
   // a wave's program, or the flat one of all tasks (at most 64 words; the
@@ -801,8 +810,8 @@ __device__ __forceinline__ void sweeps_pipelined(const uint8_t *fdata, const int
 }
 
 // Both sweeps of one subdomain with rows of any width: fn and then bn
-// segments through a ring of slots of slot bytes in the stage.  kSegWaves
-// waves solve; the last kSegStagers stage: while segment g is solved they copy
+// segments through a ring of slots of slot bytes in the stage.  The last
+// kSegStagers waves stage, the others solve: while segment g is solved they copy
 // segment g + slots - 1 into the slot that segment g - 1 has left, and wait
 // for segment g + 3 only, so that several segments' copies overlap (two
 // halves in turn left one memory latency exposed per half).  The first
@@ -819,16 +828,17 @@ __device__ __forceinline__ void stage_segments(const uint8_t *fdata, const int32
   __builtin_amdgcn_s_waitcnt(0);
 }
 
-template <typename TS, typename TC>
+template <typename TS, typename TC, bool MANY>
 __device__ __forceinline__ void segments_pipelined(const uint8_t *fdata, const int32_t *lvbf, int fn,
                                                    const uint8_t *bdata, const int32_t *lvbb, int bn, TC *xs, int XS,
                                                    int Rg, uint8_t *stage, int slot, int slots) {
-  const int wv = threadIdx.x >> 6, n = fn + bn;
-  if (wv < kSegWaves) {
-    run_segments<TS, TC>(lds_address(stage), slot, slots, n, lds_address(xs), (uint32_t)sizeof(TC) * XS, Rg, wv);
+  const int wv = threadIdx.x >> 6, n = fn + bn, solvers = (int)(blockDim.x >> 6) - kSegStagers;
+  if (wv < solvers) {
+    run_segments<TS, TC, MANY>(lds_address(stage), slot, slots, n, lds_address(xs), (uint32_t)sizeof(TC) * XS, Rg, wv,
+                         solvers);
     return;
   }
-  const int lane = threadIdx.x & 63, ahead = slots - 1, k = wv - kSegWaves;
+  const int lane = threadIdx.x & 63, ahead = slots - 1, k = wv - solvers;
   // offset and 16-byte vectors of a segment, read one turn before their use
   int off = 0, nv = 0;
   auto place = [&](int g) {
@@ -845,7 +855,7 @@ __device__ __forceinline__ void segments_pipelined(const uint8_t *fdata, const i
   const int lag = ahead >= 3 ? 3 : 1;
   int c[6] = {0, 0, 0, 0, 0, 0};
   int at = 0, to = ahead % slots;
-  const bool own = Rg >= kSegColumns;
+  const bool own = own_columns(Rg, solvers);
   int nb = own ? 0 : *reinterpret_cast<const uint16_t *>(stage);
   for (int g = 0; g < n; ++g) {
     const int q = g + ahead, nvq = __builtin_amdgcn_readfirstlane(nv), bars = __builtin_amdgcn_readfirstlane(nb);
@@ -877,7 +887,7 @@ __device__ __forceinline__ void segments_pipelined(const uint8_t *fdata, const i
 // (tau = 1e-4, minimum degree, 6.0M sweep entries): 827 us with one wave per
 // column, barrier-free levels in two stage halves and chains through the LDS,
 // 346 us so; four exact factors of 961 rows: 296 -> 104 us.
-template <typename TS, typename TC, int KE, bool XP, bool PM>
+template <typename TS, typename TC, int KE, bool XP, bool PM, bool MANY>
 __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArgs &a, int sub, int c0, int Rg,
                                             int XS) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1053,7 +1063,7 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
     __syncthreads();
   }
   if constexpr (KE == 0)
-    segments_pipelined<TS, TC>(B.data + d.f_data, lvbf, fn, B.data + d.b_data, lvbb, bn, xs, XS, Rg, stage, slot,
+    segments_pipelined<TS, TC, MANY>(B.data + d.f_data, lvbf, fn, B.data + d.b_data, lvbb, bn, xs, XS, Rg, stage, slot,
                                slots);
   else
     sweeps_pipelined<TS, TC, KE>(B.data + d.f_data, levf, lvbf, fn, B.data + d.b_data, levb, lvbb, bn, xs, XS, Rg,
@@ -1125,8 +1135,15 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
 // One launch of the batched B solves: one workgroup per (subdomain, column
 // group), or a persistent grid walking its scheduled items (the shared
 // memory is reused after a barrier between items).
-template <typename TS, typename TC, int KE, bool XP, bool PM>
-__global__ void __launch_bounds__(bsolve_threads(KE)) k_bsolve(BlockArrays<TS> B, BArgs a) {
+// MANY (sweeps of any width): at most 128 registers, so that two workgroups of
+// 512 threads or four of 256 share a compute unit (a.shared).  Without the
+// bound the solver loop takes 230 and a compute unit holds one: 512 blocks of
+// 3375 rows (threshold factors) 492 us, with it 378, 400 exact blocks of 361
+// rows 72 and 45.  Where one workgroup a compute unit is all there is, the
+// registers saved on entry cost 1% (27 blocks of 48^3) to 5% (32 x 32 small
+// blocks, 16 columns), so the unbounded kernel stays for that.
+template <typename TS, typename TC, int KE, bool XP, bool PM, bool MANY>
+__global__ void __launch_bounds__(bsolve_threads(KE), MANY ? 4 : 1) k_bsolve(BlockArrays<TS> B, BArgs a) {
   if (a.sched) {
     for (int it = a.sched_ptr[blockIdx.x]; it < a.sched_ptr[blockIdx.x + 1]; ++it) {
       const uint32_t item = (uint32_t)a.sched[it];
@@ -1134,31 +1151,31 @@ __global__ void __launch_bounds__(bsolve_threads(KE)) k_bsolve(BlockArrays<TS> B
       if (a.var_cols) {
         // columns [c0, c0 + Rg) of the subdomain, with its own row stride
         const int c0 = (int)((item >> 16) & 0xFFu), Rg = (int)(item >> 24);
-        bsolve_item<TS, TC, KE, XP, PM>(B, a, sub, c0, Rg, B.desc[sub].m);
+        bsolve_item<TS, TC, KE, XP, PM, MANY>(B, a, sub, c0, Rg, B.desc[sub].m);
       } else {
         const int c0 = (int)(item >> 16) * a.R;
-        bsolve_item<TS, TC, KE, XP, PM>(B, a, sub, c0, min(a.R, a.nrhs - c0), B.max_m);
+        bsolve_item<TS, TC, KE, XP, PM, MANY>(B, a, sub, c0, min(a.R, a.nrhs - c0), B.max_m);
       }
       __syncthreads();
     }
   } else {
     const int c0 = blockIdx.y * a.R;
-    bsolve_item<TS, TC, KE, XP, PM>(B, a, blockIdx.x, c0, min(a.R, a.nrhs - c0), B.max_m);
+    bsolve_item<TS, TC, KE, XP, PM, MANY>(B, a, blockIdx.x, c0, min(a.R, a.nrhs - c0), B.max_m);
   }
 }
 
-template <typename TS, typename TC, int KE, bool XP, bool PM>
+template <typename TS, typename TC, int KE, bool XP, bool PM, bool MANY = false>
 void launch_bsolve_k(const BlockArrays<TS> &B, int32_t p, const BArgs &a, int32_t threads, size_t lds_bytes,
                      hipStream_t st) {
   static size_t attr_bytes = 0;
   if (lds_bytes > 65536 && lds_bytes > attr_bytes) {
-    (void)hipFuncSetAttribute((const void *)k_bsolve<TS, TC, KE, XP, PM>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void *)k_bsolve<TS, TC, KE, XP, PM, MANY>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds_bytes);
     attr_bytes = lds_bytes;
   }
   // persistent: p is the number of workgroups of the schedule
   dim3 grid(p, a.sched ? 1 : (a.nrhs + a.R - 1) / a.R);
-  hipLaunchKernelGGL((k_bsolve<TS, TC, KE, XP, PM>), grid, dim3(threads), lds_bytes, st, B, a);
+  hipLaunchKernelGGL((k_bsolve<TS, TC, KE, XP, PM, MANY>), grid, dim3(threads), lds_bytes, st, B, a);
 }
 // the variant with LDS positions (B.xpos) exists for the fixed-width forms
 // only: the host keeps the row order for rows of any width; the variants in
@@ -1167,8 +1184,12 @@ template <typename TS, typename TC, int KE, bool XP>
 void launch_bsolve_p(const BlockArrays<TS> &B, int32_t p, const BArgs &a, int32_t threads, size_t lds_bytes,
                      hipStream_t st) {
   if constexpr (std::is_same<TS, TC>::value) {
+    if constexpr (KE == 0)
+      if (a.idx && a.shared) return launch_bsolve_k<TS, TC, KE, XP, true, true>(B, p, a, threads, lds_bytes, st);
     if (a.idx) return launch_bsolve_k<TS, TC, KE, XP, true>(B, p, a, threads, lds_bytes, st);
   }
+  if constexpr (KE == 0)
+    if (a.shared) return launch_bsolve_k<TS, TC, KE, XP, false, true>(B, p, a, threads, lds_bytes, st);
   launch_bsolve_k<TS, TC, KE, XP, false>(B, p, a, threads, lds_bytes, st);
 }
 template <typename TS, typename TC, int KE>
