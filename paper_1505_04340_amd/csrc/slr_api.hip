@@ -589,6 +589,14 @@ bool shared_cu(const slr_ctx *c, int64_t workgroups, size_t lds) {
   return workgroups > (int64_t)c->n_cu && 2 * lds <= c->lds_limit;
 }
 
+// Columns per workgroup of the most groups of columns with which all blocks'
+// workgroups fit the compute units at once (one group where the blocks alone
+// are more).
+int32_t columns_in_one_round(const slr_ctx *c, int32_t blocks, int32_t nrhs) {
+  const int32_t groups = std::max(1, c->n_cu / std::max(blocks, 1));
+  return (nrhs + groups - 1) / groups;
+}
+
 // Columns per workgroup, stage and threads of a B solve of nrhs columns.
 // With more subdomains than compute units and one right-hand side, the B
 // kernel runs two workgroups per CU: half the threads (one solver wave,
@@ -599,13 +607,15 @@ bool b_plan(const slr_ctx *c, int32_t pack_K, int32_t nrhs, size_t tc_bytes, int
   threads = c->b_threads;
   const slr_ctx::BTune &tu = nrhs == 1 ? c->tune1 : c->tuneM;
   const bool pair = nrhs == 1 && (int64_t)c->p > (int64_t)c->n_cu;
-  // No more columns a workgroup than fill the compute units: the waves of a
-  // workgroup share one LDS, and its columns' sweeps run no faster than that
-  // serves them.  64 subdomains of 4096 rows, 8 columns (FP32): 51.6 / 63.8 us
-  // the two solves with all columns in one workgroup, 25.0 / 28.8 with two;
-  // 16 of 4096, 16 columns: 57.4 / 65.6 against 32.1 / 34.0 with one.
-  const int32_t fill =
-      (int32_t)std::min<int64_t>(nrhs, ((int64_t)c->p * nrhs + c->n_cu - 1) / std::max(c->n_cu, 1));
+  // As many groups of columns as the compute units hold in one round: the
+  // waves of a workgroup share one LDS, and its columns' sweeps run no faster
+  // than that serves them.  64 subdomains of 4096 rows, 8 columns (FP32): 51.6 /
+  // 63.8 us the two solves with all columns in one workgroup, 25.0 / 28.8 with
+  // two; 16 of 4096, 16 columns: 57.4 / 65.6 against 32.1 / 34.0 with one.  A
+  // second round costs more than it saves: 144 of 58^2, 4 columns, both solves
+  // 75.0 us in one group, 122.7 in two; 100 of 50^2, 5 columns 70.5 in two groups,
+  // 119.0 in three.
+  const int32_t fill = columns_in_one_round(c, c->p, nrhs);
   if (tu.threads > 0 && b_lds_plan(c, std::min(nrhs, tu.rmax), tc_bytes, R, stage, c->lds_limit / tu.lds_div)) {
     threads = tu.threads;
   } else if (pair && b_lds_plan(c, nrhs, tc_bytes, R, stage, c->lds_limit / 2)) {
@@ -662,8 +672,8 @@ int block_sweep(slr_ctx *c, const slr_ctx::Deep::Part &D, BArgs a, bool compute6
   const size_t tcb = (c->fact_prec == SLR_FP64 || compute64) ? 8 : 4;
   const int64_t items = (int64_t)D.nb * a.nrhs;
   const size_t share = items > 2 * (int64_t)c->n_cu ? 4 : (items > (int64_t)c->n_cu ? 2 : 1);
-  // few blocks: a column each, to fill the compute units
-  const int32_t most = (int32_t)std::max<int64_t>(1, (items + c->n_cu - 1) / c->n_cu);
+  // few blocks: more groups of columns, as many as run in one round
+  const int32_t most = columns_in_one_round(c, D.nb, a.nrhs);
   int32_t R = 0, stage = 0;
   if (!b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, std::min(a.nrhs, most), tcb, R, stage,
                      c->lds_limit / share) &&
