@@ -559,27 +559,39 @@ const slr_ctx::BSched *b_schedule(slr_ctx *c, int32_t mode, int32_t nrhs, int32_
 // LDS plan of the B kernel: right-hand sides per workgroup R and the
 // staging buffer for the packed sweeps.  Total LDS = stage + pad16(x) +
 // 16 (max_lev + 1).  R is the largest value (<= nrhs, <= 16) that still
-// leaves a staging buffer of at least max(largest level, min(24 KiB,
-// largest sweep)).  Returns false when not even R = 1 fits.
-bool b_lds_plan_sz(int32_t max_m, int32_t max_lev, int32_t max_level_bytes, int64_t data_bytes, int32_t nrhs,
-                   size_t tc_bytes, int32_t &R, int32_t &stage, size_t limit) {
+// leaves a staging buffer of at least max(two levels or segments, min(24 KiB,
+// all sweeps)); sweeps of any width also run with room for one segment, which
+// is taken where it allows twice the columns.  Returns false when not even
+// R = 1 fits.
+bool b_lds_plan_sz(int32_t max_m, int32_t max_lev, int32_t max_level_bytes, int64_t data_bytes, bool any_width,
+                   int32_t nrhs, size_t tc_bytes, int32_t &R, int32_t &stage, size_t limit) {
   const int64_t fixed = 16 * (int64_t)(max_lev + 1) + kStageDummyBytes;
   // the fixed-width path double-buffers the stage: each half holds a level
-  const int64_t need = std::max<int64_t>(2 * (int64_t)max_level_bytes, std::min<int64_t>(24576, data_bytes));
-  for (int32_t r = std::min<int32_t>(std::max(nrhs, 1), 16); r >= 1; --r) {
-    const int64_t xb = pad16h((int64_t)tc_bytes * (std::max(max_m, 1) * r + 1));
-    const int64_t rest = ((int64_t)limit - fixed - xb) & ~int64_t(15);
-    if (rest >= need) {
-      R = r;
-      stage = (int32_t)std::min<int64_t>(rest, std::max<int64_t>(pad16h(data_bytes), 2 * pad16h(max_level_bytes)));
-      return true;
-    }
+  const int64_t two = 2 * pad16h(max_level_bytes), need = std::max(two, std::min<int64_t>(24576, data_bytes));
+  const int64_t most = std::max(pad16h(data_bytes), two);
+  auto rest = [&](int32_t r) {
+    return ((int64_t)limit - fixed - pad16h((int64_t)tc_bytes * (std::max(max_m, 1) * r + 1))) & ~int64_t(15);
+  };
+  auto largest = [&](int64_t bytes) {
+    int32_t r = std::min<int32_t>(std::max(nrhs, 1), 16);
+    while (r > 0 && rest(r) < bytes) --r;
+    return r;
+  };
+  R = largest(need);
+  if (any_width) {
+    // a segment at a time costs a quarter at most, half of the columns twice
+    // the workgroups
+    const int32_t one = largest(pad16h(max_level_bytes));
+    if (one >= 2 * R) R = one;
   }
-  return false;
+  if (R == 0) return false;
+  stage = (int32_t)std::min(rest(R), most);
+  return true;
 }
 
 bool b_lds_plan(const slr_ctx *c, int32_t nrhs, size_t tc_bytes, int32_t &R, int32_t &stage, size_t limit = 0) {
-  return b_lds_plan_sz(c->b_max_m, c->b_max_lev, c->b_max_level_bytes, c->b_data_bytes, nrhs, tc_bytes, R, stage,
+  const int32_t K = c->fact_prec == SLR_FP64 ? c->Bd.pack_K : c->Bf.pack_K;
+  return b_lds_plan_sz(c->b_max_m, c->b_max_lev, c->b_max_level_bytes, c->b_data_bytes, K == 0, nrhs, tc_bytes, R, stage,
                        limit == 0 ? c->lds_limit : limit);
 }
 
@@ -675,9 +687,9 @@ int block_sweep(slr_ctx *c, const slr_ctx::Deep::Part &D, BArgs a, bool compute6
   // few blocks: more groups of columns, as many as run in one round
   const int32_t most = columns_in_one_round(c, D.nb, a.nrhs);
   int32_t R = 0, stage = 0;
-  if (!b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, std::min(a.nrhs, most), tcb, R, stage,
+  if (!b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, false, std::min(a.nrhs, most), tcb, R, stage,
                      c->lds_limit / share) &&
-      !b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, std::min(a.nrhs, most), tcb, R, stage,
+      !b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, false, std::min(a.nrhs, most), tcb, R, stage,
                      c->lds_limit))
     return fail(SLR_ERR_ARG, "an interface block does not fit the LDS of one workgroup");
   a.R = R;
@@ -764,10 +776,11 @@ bool c1_plan(const slr_ctx *c, int32_t nrhs, size_t tcb, int32_t &R, int32_t &st
   const int32_t K = c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K;
   const int32_t share = K > 0 || c1_many(c) ? 4 : 2;
   threads = share == 4 ? 256 : bsolve_threads(0);
-  if (b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, nrhs, tcb, R, stage, c->lds_limit / share))
+  if (b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, false, nrhs, tcb, R, stage,
+                    c->lds_limit / share))
     return true;
   if (K == 0) threads = bsolve_threads(0);
-  return b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, nrhs, tcb, R, stage, c->lds_limit);
+  return b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, K == 0, nrhs, tcb, R, stage, c->lds_limit);
 }
 
 int c1solve(slr_ctx *c, BArgs a, int32_t sweeps, bool compute64, hipStream_t st) {
@@ -1491,11 +1504,17 @@ constexpr int64_t kPieceBytes = 8192;
 // a slot of the ring also holds the words a wave reads past its program
 constexpr int32_t kSegMinBytes = 2048;
 
-// Bytes of a segment: six slots beside the largest x (FP64) in lds bytes, so
-// that several are in flight, but large enough for tasks for every wave
-// (kSegBytes to three times that).
-int64_t segment_bytes(int32_t max_m, size_t lds) {
-  return std::max<int64_t>(kSegBytes, std::min<int64_t>(3 * kSegBytes, ((int64_t)lds - 8 * max_m - 16384) / 6));
+// Bytes of a segment: six slots beside the largest x (FP64) in lds bytes, but
+// large enough for tasks for every wave (kSegBytes to three times that).
+// Larger segments pay more than more slots: 512 blocks of 3375 rows (threshold
+// factors) at half of the LDS take 335 us with two slots of 20 KiB and 547 with
+// six of 8, 27 of 3375 at the whole 340 us with six of 20 KiB and 428 with ten of
+// 12.  At most 24 KiB, which a launch plan's share of the LDS leaves beside x
+// (slr_set_bsolve_plan) unless all sweeps together are smaller: then (stream:
+// their bytes without padding) the least.
+int64_t segment_bytes(int32_t max_m, size_t lds, int64_t stream) {
+  if (stream < 3 * kSegBytes) return kSegBytes;
+  return std::max<int64_t>(kSegBytes, std::min<int64_t>(3 * kSegBytes - 128, ((int64_t)lds - 8 * max_m - 16384) / 6));
 }
 
 template <typename TS>
@@ -1921,7 +1940,10 @@ bool pack_blocks(DevPool &P, const std::vector<Block> &blocks, BlockArrays<TS> &
   const int32_t Kfix = packed_width(blocks);
   int32_t widest_m = 0;
   for (const Block &b : blocks) widest_m = std::max(widest_m, b.m);
-  const int64_t seg_bytes = segment_bytes(widest_m, lds);
+  int64_t stream = 0;
+  for (const Block &b : blocks)
+    for (const Sweep *sw : {&b.fwd, &b.bwd}) stream += (2 + (int64_t)sizeof(TS)) * (sw->nrows + (int64_t)sw->ci.size());
+  const int64_t seg_bytes = segment_bytes(widest_m, lds, stream);
   // sweeps of any width are packed block by block on several threads
   struct Packed {
     std::vector<uint8_t> data;
@@ -2316,7 +2338,7 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
     P.max_level_bytes = sz.max_level_bytes;
     P.data_bytes = sz.data_bytes;
     int32_t R = 0, stage = 0;
-    return ok && b_lds_plan_sz(P.max_m, P.max_lev, P.max_level_bytes, P.data_bytes, 1, 8, R, stage, c->lds_limit);
+    return ok && b_lds_plan_sz(P.max_m, P.max_lev, P.max_level_bytes, P.data_bytes, false, 1, 8, R, stage, c->lds_limit);
   };
   // a task or a table that does not fit leaves the schedule's own launches
   if ((nb > 0 && !pack(lead, D.lead, rm ? &rm->lead : nullptr)) || !pack(rest, D.rest, rm ? &rm->rest : nullptr))
@@ -2775,7 +2797,7 @@ bool convert_streams(slr_ctx *c, BlockArrays<TS> &B) {
   std::vector<uint8_t> data, ndata;
   if (!host(B.desc, desc) || !host(B.lev, lev) || !host(B.lvb, lvb) || !host(B.data, data)) return false;
   int32_t max_lev = 0, max_lb = kSegMinBytes;
-  const int64_t seg_bytes = segment_bytes(B.max_m, c->lds_limit);
+  const int64_t seg_bytes = segment_bytes(B.max_m, c->lds_limit, (int64_t)data.size());
   for (BlockDesc &d : desc)
     for (const bool f : {true, false}) {
       int32_t &nlev = f ? d.f_nlev : d.b_nlev, &ol = f ? d.f_lev : d.b_lev, &ob = f ? d.f_lvb : d.b_lvb;
@@ -2954,7 +2976,8 @@ int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out
         return bad("interface factor blocks");
       int32_t R = 0, stage = 0;
       auto fits = [&](const slr_ctx::Deep::Part &q) {
-        return q.nb > 0 && b_lds_plan_sz(q.max_m, q.max_lev, q.max_level_bytes, q.data_bytes, 1, 8, R, stage, c->lds_limit);
+        return q.nb > 0 && b_lds_plan_sz(q.max_m, q.max_lev, q.max_level_bytes, q.data_bytes, false, 1, 8, R, stage,
+                                          c->lds_limit);
       };
       if (D.s != c->s || D.t < 0 || D.t > D.s || (D.t > 0 && !fits(D.lead)) || !fits(D.rest))
         return bad("interface factor blocks");
@@ -3214,7 +3237,8 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
     I.nnz_L2 = H.nnz_LC2;
     I.k2 = o->k2 > 0 ? o->k2 : o->k;
     int32_t R1 = 0, st1 = 0;
-    if (!b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, 1, 8, R1, st1, c->lds_limit))
+    const int32_t K1 = c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K;
+    if (!b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, K1 == 0, 1, 8, R1, st1, c->lds_limit))
       return destroy_fail(fail(SLR_ERR_ARG, "largest connector does not fit one workgroup's LDS"));
   }
   c->cf_lev_h = H.cfwd.levptr;

@@ -457,8 +457,10 @@ __device__ __forceinline__ bool own_columns(int Rg, int solvers) { return Rg >= 
 // 2400 cycles a level.  Lane i holds word i of the program.  Not inlined: the
 // kernel's own values would push this loop's scalars out of their
 // registers.
-// (kernels with more registers call an instance of their own: MANY)
-template <typename TS, typename TC, bool MANY>
+// (kernels with more registers call an instance of their own: MANY.  ONE: a
+// ring of one slot; a second barrier after each segment says that the next one
+// has landed.  An instance of its own, for the loop's scalars just fit.)
+template <typename TS, typename TC, bool MANY, bool ONE>
 __device__ __attribute__((noinline)) void run_segments(uint32_t ring, int slot, int slots, int n, uint32_t xs,
                                                        uint32_t cs, int Rg, int wv, int solvers) {
   const int lane = threadIdx.x & 63;
@@ -525,7 +527,7 @@ __device__ __attribute__((noinline)) void run_segments(uint32_t ring, int slot, 
       } else {
         // all but the segment's last barrier, which the next task passes
         pass_barriers(nbar);
-        owed = 1;
+        owed = ONE ? 2 : 1;
         break;
       }
     }
@@ -816,10 +818,12 @@ __device__ __forceinline__ void sweeps_pipelined(const uint8_t *fdata, const int
 // for segment g + 3 only, so that several segments' copies overlap (two
 // halves in turn left one memory latency exposed per half).  The first
 // slots - 1 segments are there already (stage_segments, before a barrier).
+// One slot only (the largest subdomains, the smallest shares of the LDS): a
+// segment is copied when the one before has ended, with one barrier more.
 __device__ __forceinline__ void stage_segments(const uint8_t *fdata, const int32_t *lvbf, int fn, const uint8_t *bdata,
                                                const int32_t *lvbb, int bn, uint8_t *stage, int slot, int slots,
                                                int gt, int gn) {
-  for (int g = 0; g < min(slots - 1, fn + bn); ++g) {
+  for (int g = 0; g < min(max(slots - 1, 1), fn + bn); ++g) {
     const bool f = g < fn;
     const int32_t *lvb = f ? lvbf + g : lvbb + g - fn;
     stage_issue(reinterpret_cast<const uint4 *>((f ? fdata : bdata) + lvb[0]), (lvb[1] - lvb[0]) >> 4,
@@ -834,8 +838,11 @@ __device__ __forceinline__ void segments_pipelined(const uint8_t *fdata, const i
                                                    int Rg, uint8_t *stage, int slot, int slots) {
   const int wv = threadIdx.x >> 6, n = fn + bn, solvers = (int)(blockDim.x >> 6) - kSegStagers;
   if (wv < solvers) {
-    run_segments<TS, TC, MANY>(lds_address(stage), slot, slots, n, lds_address(xs), (uint32_t)sizeof(TC) * XS, Rg, wv,
-                         solvers);
+    const uint32_t ring = lds_address(stage), x = lds_address(xs), cs = (uint32_t)sizeof(TC) * XS;
+    if (slots == 1)
+      run_segments<TS, TC, MANY, true>(ring, slot, slots, n, x, cs, Rg, wv, solvers);
+    else
+      run_segments<TS, TC, MANY, false>(ring, slot, slots, n, x, cs, Rg, wv, solvers);
     return;
   }
   const int lane = threadIdx.x & 63, ahead = slots - 1, k = wv - solvers;
@@ -848,6 +855,18 @@ __device__ __forceinline__ void segments_pipelined(const uint8_t *fdata, const i
     off = lvb[0];
     nv = (lvb[1] - off) >> 4;
   };
+  const bool own = own_columns(Rg, solvers);
+  if (slots == 1) {
+    for (int g = 0; g < n; ++g) {
+      place(g + 1);
+      const int bars = own ? 0 : *reinterpret_cast<const uint16_t *>(stage);
+      for (int i = 0; i <= bars; ++i) stager_barrier();
+      if (nv > 0) stage_wave((g + 1 < fn ? fdata : bdata) + off, nv, stage, k, lane);
+      wait_loads(0);
+      stager_barrier();
+    }
+    return;
+  }
   place(ahead);
   // segments up to g + lag have landed when segment g ends (the first ahead
   // ones before the start); loads of the later ones may be in flight: c[0]
@@ -855,7 +874,6 @@ __device__ __forceinline__ void segments_pipelined(const uint8_t *fdata, const i
   const int lag = ahead >= 3 ? 3 : 1;
   int c[6] = {0, 0, 0, 0, 0, 0};
   int at = 0, to = ahead % slots;
-  const bool own = own_columns(Rg, solvers);
   int nb = own ? 0 : *reinterpret_cast<const uint16_t *>(stage);
   for (int g = 0; g < n; ++g) {
     const int q = g + ahead, nvq = __builtin_amdgcn_readfirstlane(nv), bars = __builtin_amdgcn_readfirstlane(nb);
