@@ -517,9 +517,10 @@ const slr_ctx::BSched *b_schedule(slr_ctx *c, int32_t mode, int32_t nrhs, int32_
     for (int32_t g = 0; g < ncg; ++g)
       for (int32_t q = 0; q < p; ++q) items.push_back((g << 16) | q);
   } else {
-    const int64_t cap = (int64_t)c->b_max_m * R;
+    const int32_t K = c->fact_prec == SLR_FP64 ? c->Bd.pack_K : c->Bf.pack_K;
+    const int64_t cap = (int64_t)x_stride(c->b_max_m, K) * R;
     for (int32_t q = 0; q < p; ++q) {
-      const int64_t mq = std::max<int64_t>(c->b_m_h[q], 1);
+      const int64_t mq = std::max<int64_t>(x_stride(c->b_m_h[q], K), 1);
       const int32_t rq = (int32_t)std::max<int64_t>(1, std::min<int64_t>({cap / mq, std::max(waves - 1, 1), 255}));
       for (int32_t c0 = 0; c0 < nrhs; c0 += rq) {
         const int32_t rg = std::min(rq, nrhs - c0);
@@ -560,17 +561,17 @@ const slr_ctx::BSched *b_schedule(slr_ctx *c, int32_t mode, int32_t nrhs, int32_
 // staging buffer for the packed sweeps.  Total LDS = stage + pad16(x) +
 // 16 (max_lev + 1).  R is the largest value (<= nrhs, <= 16) that still
 // leaves a staging buffer of at least max(two levels or segments, min(24 KiB,
-// all sweeps)); sweeps of any width also run with room for one segment, which
-// is taken where it allows twice the columns.  Returns false when not even
+// all sweeps)); with one_slot, sweeps of any width also run with room for one
+// segment, which is taken where it allows twice the columns.  Returns false when not even
 // R = 1 fits.
-bool b_lds_plan_sz(int32_t max_m, int32_t max_lev, int32_t max_level_bytes, int64_t data_bytes, bool any_width,
-                   int32_t nrhs, size_t tc_bytes, int32_t &R, int32_t &stage, size_t limit) {
+bool b_lds_plan_sz(int32_t max_m, int32_t max_lev, int32_t max_level_bytes, int64_t data_bytes, int32_t pack_K,
+                   bool one_slot, int32_t nrhs, size_t tc_bytes, int32_t &R, int32_t &stage, size_t limit) {
   const int64_t fixed = 16 * (int64_t)(max_lev + 1) + kStageDummyBytes;
   // the fixed-width path double-buffers the stage: each half holds a level
   const int64_t two = 2 * pad16h(max_level_bytes), need = std::max(two, std::min<int64_t>(24576, data_bytes));
   const int64_t most = std::max(pad16h(data_bytes), two);
   auto rest = [&](int32_t r) {
-    return ((int64_t)limit - fixed - pad16h((int64_t)tc_bytes * (std::max(max_m, 1) * r + 1))) & ~int64_t(15);
+    return ((int64_t)limit - fixed - x_bytes((int64_t)tc_bytes, std::max(max_m, 1), pack_K, r)) & ~int64_t(15);
   };
   auto largest = [&](int64_t bytes) {
     int32_t r = std::min<int32_t>(std::max(nrhs, 1), 16);
@@ -578,7 +579,7 @@ bool b_lds_plan_sz(int32_t max_m, int32_t max_lev, int32_t max_level_bytes, int6
     return r;
   };
   R = largest(need);
-  if (any_width) {
+  if (pack_K == 0 && one_slot) {
     // a segment at a time costs a quarter at most, half of the columns twice
     // the workgroups
     const int32_t one = largest(pad16h(max_level_bytes));
@@ -591,7 +592,7 @@ bool b_lds_plan_sz(int32_t max_m, int32_t max_lev, int32_t max_level_bytes, int6
 
 bool b_lds_plan(const slr_ctx *c, int32_t nrhs, size_t tc_bytes, int32_t &R, int32_t &stage, size_t limit = 0) {
   const int32_t K = c->fact_prec == SLR_FP64 ? c->Bd.pack_K : c->Bf.pack_K;
-  return b_lds_plan_sz(c->b_max_m, c->b_max_lev, c->b_max_level_bytes, c->b_data_bytes, K == 0, nrhs, tc_bytes, R, stage,
+  return b_lds_plan_sz(c->b_max_m, c->b_max_lev, c->b_max_level_bytes, c->b_data_bytes, K, true, nrhs, tc_bytes, R, stage,
                        limit == 0 ? c->lds_limit : limit);
 }
 
@@ -648,7 +649,7 @@ int run_bsolve(slr_ctx *c, const BlockArrays<TS> &B, const BArgs &a0, hipStream_
     return fail(SLR_ERR_ARG, "a subdomain does not fit the LDS of one workgroup");
   a.R = R;
   a.stage_bytes = stage;
-  const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)sizeof(TC) * (c->b_max_m * R + 1)) +
+  const size_t lds = (size_t)stage + kStageDummyBytes + x_bytes(sizeof(TC), c->b_max_m, B.pack_K, R) +
                     16 * (size_t)(c->b_max_lev + 1);
   int32_t grid = c->p;
   a.shared = shared_cu(c, (int64_t)c->p * ((a.nrhs + R - 1) / R), lds);
@@ -682,22 +683,23 @@ int bsolve(slr_ctx *c, const BArgs &a, bool compute64, hipStream_t st) {
 // of a workgroup leaves room for as many as should share a compute unit.
 int block_sweep(slr_ctx *c, const slr_ctx::Deep::Part &D, BArgs a, bool compute64, hipStream_t st) {
   const size_t tcb = (c->fact_prec == SLR_FP64 || compute64) ? 8 : 4;
+  const int32_t K = c->fact_prec == SLR_FP64 ? D.Bd.pack_K : D.Bf.pack_K;
   const int64_t items = (int64_t)D.nb * a.nrhs;
   const size_t share = items > 2 * (int64_t)c->n_cu ? 4 : (items > (int64_t)c->n_cu ? 2 : 1);
   // few blocks: more groups of columns, as many as run in one round
   const int32_t most = columns_in_one_round(c, D.nb, a.nrhs);
   int32_t R = 0, stage = 0;
-  if (!b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, false, std::min(a.nrhs, most), tcb, R, stage,
+  if (!b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, K, false, std::min(a.nrhs, most), tcb, R, stage,
                      c->lds_limit / share) &&
-      !b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, false, std::min(a.nrhs, most), tcb, R, stage,
+      !b_lds_plan_sz(D.max_m, D.max_lev, D.max_level_bytes, D.data_bytes, K, false, std::min(a.nrhs, most), tcb, R, stage,
                      c->lds_limit))
     return fail(SLR_ERR_ARG, "an interface block does not fit the LDS of one workgroup");
   a.R = R;
   a.stage_bytes = stage;
-  const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)tcb * ((int64_t)D.max_m * R + 1)) +
+  const size_t lds = (size_t)stage + kStageDummyBytes + x_bytes((int64_t)tcb, D.max_m, K, R) +
                      16 * (size_t)(D.max_lev + 1);
   a.shared = shared_cu(c, (int64_t)D.nb * ((a.nrhs + R - 1) / R), lds);
-  const int32_t K = c->fact_prec == SLR_FP64 ? D.Bd.pack_K : D.Bf.pack_K, threads = K > 0 ? 512 : bsolve_threads(0);
+  const int32_t threads = K > 0 ? 512 : bsolve_threads(0);
   if (c->fact_prec == SLR_FP64)
     launch_bsolve<double, double>(D.Bd, D.nb, a, threads, lds, st);
   else if (compute64)
@@ -776,23 +778,24 @@ bool c1_plan(const slr_ctx *c, int32_t nrhs, size_t tcb, int32_t &R, int32_t &st
   const int32_t K = c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K;
   const int32_t share = K > 0 || c1_many(c) ? 4 : 2;
   threads = share == 4 ? 256 : bsolve_threads(0);
-  if (b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, false, nrhs, tcb, R, stage,
+  if (b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, K, false, nrhs, tcb, R, stage,
                     c->lds_limit / share))
     return true;
   if (K == 0) threads = bsolve_threads(0);
-  return b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, K == 0, nrhs, tcb, R, stage, c->lds_limit);
+  return b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, K, true, nrhs, tcb, R, stage, c->lds_limit);
 }
 
 int c1solve(slr_ctx *c, BArgs a, int32_t sweeps, bool compute64, hipStream_t st) {
   const slr_ctx::Inner &I = c->ml;
   a.sweeps = sweeps;
   const size_t tcb = (c->fact_prec == SLR_FP64 || compute64) ? 8 : 4;
+  const int32_t K = c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K;
   int32_t R = 0, stage = 0, threads = 0;
   if (!c1_plan(c, a.nrhs, tcb, R, stage, threads))
     return fail(SLR_ERR_ARG, "a connector does not fit the LDS of one workgroup");
   a.R = R;
   a.stage_bytes = stage;
-  const size_t lds = (size_t)stage + kStageDummyBytes + pad16h((int64_t)tcb * ((int64_t)I.max_m * R + 1)) +
+  const size_t lds = (size_t)stage + kStageDummyBytes + x_bytes((int64_t)tcb, I.max_m, K, R) +
                      16 * (size_t)(I.max_lev + 1);
   a.shared = shared_cu(c, (int64_t)I.nb * ((a.nrhs + R - 1) / R), lds);
   if (c->fact_prec == SLR_FP64)
@@ -1659,7 +1662,7 @@ struct SegPacker {
       for (int64_t v = 0; v < nb * B; ++v) {
         const int64_t e = v * G + g, at = ((v / B) * 64 + l) * B + v % B;
         const bool in = real && e < (int64_t)p.e.size();
-        ci[at] = (uint16_t)(in ? p.e[e].first : row);
+        ci[at] = (uint16_t)(in ? p.e[e].first : sw.nrows);
         w[at] = in ? (TS)sw.w[p.e[e].second] : (TS)0;
         if (map && in) t.map.push_back(rf_weight(sw, p.t, p.e[e].second, o_w + ts * at, ebase));
       }
@@ -2338,7 +2341,8 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
     P.max_level_bytes = sz.max_level_bytes;
     P.data_bytes = sz.data_bytes;
     int32_t R = 0, stage = 0;
-    return ok && b_lds_plan_sz(P.max_m, P.max_lev, P.max_level_bytes, P.data_bytes, false, 1, 8, R, stage, c->lds_limit);
+    return ok && b_lds_plan_sz(P.max_m, P.max_lev, P.max_level_bytes, P.data_bytes,
+                               sizeof(TS) == 8 ? P.Bd.pack_K : P.Bf.pack_K, false, 1, 8, R, stage, c->lds_limit);
   };
   // a task or a table that does not fit leaves the schedule's own launches
   if ((nb > 0 && !pack(lead, D.lead, rm ? &rm->lead : nullptr)) || !pack(rest, D.rest, rm ? &rm->rest : nullptr))
@@ -2976,7 +2980,8 @@ int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out
         return bad("interface factor blocks");
       int32_t R = 0, stage = 0;
       auto fits = [&](const slr_ctx::Deep::Part &q) {
-        return q.nb > 0 && b_lds_plan_sz(q.max_m, q.max_lev, q.max_level_bytes, q.data_bytes, false, 1, 8, R, stage,
+        return q.nb > 0 && b_lds_plan_sz(q.max_m, q.max_lev, q.max_level_bytes, q.data_bytes,
+                                          c->fact_prec == SLR_FP64 ? q.Bd.pack_K : q.Bf.pack_K, false, 1, 8, R, stage,
                                           c->lds_limit);
       };
       if (D.s != c->s || D.t < 0 || D.t > D.s || (D.t > 0 && !fits(D.lead)) || !fits(D.rest))
@@ -3238,7 +3243,7 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
     I.k2 = o->k2 > 0 ? o->k2 : o->k;
     int32_t R1 = 0, st1 = 0;
     const int32_t K1 = c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K;
-    if (!b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, K1 == 0, 1, 8, R1, st1, c->lds_limit))
+    if (!b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, K1, true, 1, 8, R1, st1, c->lds_limit))
       return destroy_fail(fail(SLR_ERR_ARG, "largest connector does not fit one workgroup's LDS"));
   }
   c->cf_lev_h = H.cfwd.levptr;

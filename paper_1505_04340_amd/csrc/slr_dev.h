@@ -38,7 +38,7 @@ namespace slr {
 //     ci    uint16[nb][64][B]  columns; B = 2 (nu <= 2) or 4, nb = ceil(nu / B)
 //     w     TS[nb][64][B]      pre-divided weights
 //     (lane g of a row's G lanes holds its entries g, g + G, ..; padding has
-//     w = 0 and the row itself)
+//     w = 0 and column m, one past the rows, which is zero)
 //   kSegChain  14 with entries to the previous chain, 17-25 R rows
 //     rows  uint16[16]         the chain's rows in solve order (the last repeated)
 //     prev  uint16[16]         the previous chain's
@@ -126,6 +126,13 @@ __host__ __device__ constexpr int rec_passes(int K) { return K <= 2 ? 4 : (K == 
 // that their programs are laid out for and the stagers; with fewer waves each
 // solver wave takes columns of its own.
 __host__ __device__ constexpr int bsolve_threads(int pack_K) { return pack_K > 0 ? 1024 : 64 * (kSegWaves + kSegStagers); }
+
+// A column of x in LDS: m values, and a zero for the padding of sweeps of any
+// width.  Bytes of the R columns of a workgroup (max_m: rows of the largest).
+__host__ __device__ constexpr int x_stride(int m, int pack_K) { return pack_K > 0 ? m : m + 1; }
+__host__ __device__ constexpr int64_t x_bytes(int64_t value, int max_m, int pack_K, int R) {
+  return (value * (pack_K > 0 ? (int64_t)max_m * R + 1 : ((int64_t)max_m + 1) * R) + 15) & ~(int64_t)15;
+}
 
 // Sweeps of any width: slots of a ring of segments in the stage.
 __host__ __device__ constexpr int ring_slots(int stage_bytes, int max_segment) {

@@ -147,7 +147,7 @@ __host__ __device__ constexpr int pad16(int x) { return (x + 15) & ~15; }
 // x lives in LDS column-major: column r of the workgroup's right-hand sides
 // at xs[r * XS + row], XS = the largest subdomain size (a persistent item
 // with its own column count: its subdomain's size), in a region of
-// max_m * R + 1 values.
+// x_bytes bytes.
 //
 // Sum over aligned groups of 1 << lg lanes (lg 0, 2, 3, 4 or 6), valid in each
 // group's first lane, halves first (the order of a butterfly from the widest
@@ -304,6 +304,8 @@ __device__ __forceinline__ void pass_barriers(int n) {
 // single lane, or summed by the lanes of the row first.  What does not depend
 // on x is read before the barriers; up to NB blocks are in flight (a block
 // waits for its columns and then for their values, two LDS latencies).
+// Padding multiplies a zero (past the column's rows), never a row's value, which
+// may not be finite.
 template <typename TS, typename TC, int B, int NB>
 __device__ __forceinline__ void ell_task(uint32_t at, int lg, int nb, int nbar, const SegCols &cols, int lane) {
   constexpr uint32_t es = sizeof(TC), ts = sizeof(TS);
@@ -912,12 +914,12 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
   const BlockDesc d = B.desc[sub];
   const int R = a.R;
   const int m = d.m;
-  // LDS: [stage][dummy slots][x: max_m*R + 1 TC][levptr f, b][lvb f, b]; the
-  // item's Rg columns of XS rows each fit the x region (XS*Rg <= max_m*R)
+  // LDS: [stage][dummy slots][x: x_bytes][levptr f, b][lvb f, b]; the item's Rg
+  // columns of XS values each fit the x region
   uint8_t *stage = smem;
   TC *xs = reinterpret_cast<TC *>(smem + a.stage_bytes + kStageDummyBytes);
   int32_t *levf =
-      reinterpret_cast<int32_t *>(smem + a.stage_bytes + kStageDummyBytes + pad16((int)sizeof(TC) * (B.max_m * R + 1)));
+      reinterpret_cast<int32_t *>(smem + a.stage_bytes + kStageDummyBytes + (int)x_bytes(sizeof(TC), B.max_m, KE, R));
   int32_t *levb = levf + B.max_lev + 1;
   int32_t *lvbf = levb + B.max_lev + 1;
   int32_t *lvbb = lvbf + B.max_lev + 1;
@@ -930,6 +932,8 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
   // level pointers into LDS, then rhs = a_f f_i (loads batched 4 per
   // thread), by the threads gt = 0 .. gn-1
   auto prologue = [&](int gt, int gn) {
+    if constexpr (KE == 0)
+      if (gt < Rg) xs[gt * XS + m] = (TC)0;
     for (int i = gt; i <= d.f_nlev; i += gn) {
       levf[i] = B.lev[d.f_lev + i];
       lvbf[i] = B.lvb[d.f_lvb + i];
@@ -1169,16 +1173,16 @@ __global__ void __launch_bounds__(bsolve_threads(KE), MANY ? 4 : 1) k_bsolve(Blo
       if (a.var_cols) {
         // columns [c0, c0 + Rg) of the subdomain, with its own row stride
         const int c0 = (int)((item >> 16) & 0xFFu), Rg = (int)(item >> 24);
-        bsolve_item<TS, TC, KE, XP, PM, MANY>(B, a, sub, c0, Rg, B.desc[sub].m);
+        bsolve_item<TS, TC, KE, XP, PM, MANY>(B, a, sub, c0, Rg, x_stride(B.desc[sub].m, KE));
       } else {
         const int c0 = (int)(item >> 16) * a.R;
-        bsolve_item<TS, TC, KE, XP, PM, MANY>(B, a, sub, c0, min(a.R, a.nrhs - c0), B.max_m);
+        bsolve_item<TS, TC, KE, XP, PM, MANY>(B, a, sub, c0, min(a.R, a.nrhs - c0), x_stride(B.max_m, KE));
       }
       __syncthreads();
     }
   } else {
     const int c0 = blockIdx.y * a.R;
-    bsolve_item<TS, TC, KE, XP, PM, MANY>(B, a, blockIdx.x, c0, min(a.R, a.nrhs - c0), B.max_m);
+    bsolve_item<TS, TC, KE, XP, PM, MANY>(B, a, blockIdx.x, c0, min(a.R, a.nrhs - c0), x_stride(B.max_m, KE));
   }
 }
 
