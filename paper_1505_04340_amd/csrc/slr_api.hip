@@ -710,8 +710,8 @@ int block_sweep(slr_ctx *c, const slr_ctx::Deep::Part &D, BArgs a, bool compute6
 }
 
 // x <- L^{-1} x (fwd) or L^{-T} x in place through the block form of L
-void deep_sweep(slr_ctx *c, const slr_ctx::Deep &D, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool compute64,
-                hipStream_t st) {
+int deep_sweep(slr_ctx *c, const slr_ctx::Deep &D, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool compute64,
+               hipStream_t st) {
   BArgs lead, rest;
   lead.f = x; lead.u = x;
   rest.f = x + D.t; rest.u = x + D.t;
@@ -721,22 +721,20 @@ void deep_sweep(slr_ctx *c, const slr_ctx::Deep &D, bool fwd, double *x, int64_t
     a->nrhs = nrhs;
     a->sweeps = fwd ? 1 : 2;
   }
+  int rc = SLR_OK;
   if (fwd) {
     if (D.t > 0) {
-      (void)block_sweep(c, D.lead, lead, compute64, st);
+      if ((rc = block_sweep(c, D.lead, lead, compute64, st))) return rc;
       launch_rows_sub(D.s - D.t, D.et_rp, D.et_ci, D.et_v, x, ldx, x + D.t, ldx, nrhs, st);
     }
-    (void)block_sweep(c, D.rest, rest, compute64, st);
-  } else {
-    (void)block_sweep(c, D.rest, rest, compute64, st);
-    if (D.t > 0) {
-      lead.y = x + D.t; lead.ldy = ldx; lead.b_y = -1.0;
-      (void)block_sweep(c, D.lead, lead, compute64, st);
-    }
+    return block_sweep(c, D.rest, rest, compute64, st);
   }
+  if ((rc = block_sweep(c, D.rest, rest, compute64, st)) || D.t == 0) return rc;
+  lead.y = x + D.t; lead.ldy = ldx; lead.b_y = -1.0;
+  return block_sweep(c, D.lead, lead, compute64, st);
 }
 
-void csweep(slr_ctx *c, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool compute64, hipStream_t st) {
+int csweep(slr_ctx *c, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool compute64, hipStream_t st) {
   if (c->cdeep.on) return deep_sweep(c, c->cdeep, fwd, x, ldx, nrhs, compute64, st);
   const int32_t nlev = fwd ? c->cf_nlev : c->cb_nlev;
   const int32_t *lev = fwd ? c->cf_lev_h.data() : c->cb_lev_h.data();
@@ -748,6 +746,7 @@ void csweep(slr_ctx *c, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool com
   } else {
     launch_sweep<float, float>(fwd ? c->Cff : c->Cbf, lev, nlev, (int32_t)c->s, x, ldx, nrhs, c->c_one_wg, st, G);
   }
+  return SLR_OK;
 }
 
 // out-of-place two-level interface sweep (multicolour schedules)
@@ -808,7 +807,7 @@ int c1solve(slr_ctx *c, BArgs a, int32_t sweeps, bool compute64, hipStream_t st)
 }
 
 // x <- L2^{-1} x (fwd) or L2^{-T} x over the inner interface, in place
-void c2sweep(slr_ctx *c, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool compute64, hipStream_t st) {
+int c2sweep(slr_ctx *c, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool compute64, hipStream_t st) {
   const slr_ctx::Inner &I = c->ml;
   if (I.deep.on) return deep_sweep(c, I.deep, fwd, x, ldx, nrhs, compute64, st);
   const int32_t nlev = fwd ? I.f_nlev : I.b_nlev;
@@ -821,6 +820,7 @@ void c2sweep(slr_ctx *c, bool fwd, double *x, int64_t ldx, int32_t nrhs, bool co
     launch_sweep<float, double>(fwd ? I.C2ff : I.C2bf, lev, nlev, s2, x, ldx, nrhs, I.one_wg, st, G);
   else
     launch_sweep<float, float>(fwd ? I.C2ff : I.C2bf, lev, nlev, s2, x, ldx, nrhs, I.one_wg, st, G);
+  return SLR_OK;
 }
 
 // x <- Q2 x = sq x + U2 diag(qd) U2^T x over the inner interface, in place
@@ -845,7 +845,7 @@ int c_lower(slr_ctx *c, double *x, int64_t ldx, int32_t nrhs, bool compute64, do
   a.u = scr; a.ldu = lds;
   if ((rc = c1solve(c, a, 2, compute64, st))) return rc;
   launch_spmv_axpby(I.s2, I.ft_rp, I.ft_ci, I.ft_v, scr, lds, x + I.s1, ldx, nrhs, 1.0, -1.0, st);
-  c2sweep(c, true, x + I.s1, ldx, nrhs, compute64, st);
+  if ((rc = c2sweep(c, true, x + I.s1, ldx, nrhs, compute64, st))) return rc;
   q2(c, x + I.s1, ldx, nrhs, w, st);
   return SLR_OK;
 }
@@ -856,13 +856,13 @@ int c_upper(slr_ctx *c, double *x, int64_t ldx, int32_t nrhs, bool compute64, do
             hipStream_t st) {
   const slr_ctx::Inner &I = c->ml;
   q2(c, x + I.s1, ldx, nrhs, w, st);
-  c2sweep(c, false, x + I.s1, ldx, nrhs, compute64, st);
+  int rc = c2sweep(c, false, x + I.s1, ldx, nrhs, compute64, st);
+  if (rc) return rc;
   BArgs a;
   a.y = x + I.s1; a.ldy = ldx; a.b_y = 1.0;
   a.u = scr; a.ldu = lds;
   a.nrhs = nrhs;
-  int rc = c1solve(c, a, 1, compute64, st);
-  if (rc) return rc;
+  if ((rc = c1solve(c, a, 1, compute64, st))) return rc;
   launch_axpby(I.s1, nrhs, -1.0, scr, lds, 1.0, x, ldx, st);
   BArgs b;
   b.f = x; b.ldf = ldx; b.a_f = 1.0;
@@ -950,9 +950,9 @@ int apply_dd(slr_ctx *c, ApplyWS &w, const double *r, int64_t ldr, double *z, in
       lowrank(c, w, w.W2, s, w.W, s, nrhs, st);
       csweep2(c, false, w.W, s, y, ldy, nrhs, false, st);
     } else {
-      csweep(c, true, w.W, s, nrhs, false, st);
+      if ((rc = csweep(c, true, w.W, s, nrhs, false, st))) return rc;
       lowrank(c, w, w.W, s, y, ldy, nrhs, st);
-      csweep(c, false, y, ldy, nrhs, false, st);
+      if ((rc = csweep(c, false, y, ldy, nrhs, false, st))) return rc;
     }
   }
   if (m > 0) {
@@ -1013,7 +1013,7 @@ int apply_H(slr_ctx *c, const double *v, double *w, double *t, double *t2, hipSt
     if (!t_ready) csweep2(c, false, v, s, t, s, 1, true, st);
   } else {
     launch_axpby(s, 1, 1.0, v, s, 0.0, t, s, st);
-    csweep(c, false, t, s, 1, true, st);
+    if (const int rc = csweep(c, false, t, s, 1, true, st)) return rc;
   }
   int rc = bsolve_et(c, t, c->c_two_level ? t2 : w, st);
   if (rc) return rc;
@@ -1021,7 +1021,7 @@ int apply_H(slr_ctx *c, const double *v, double *w, double *t, double *t2, hipSt
     csweep2(c, true, t2, s, w, s, 1, true, st, dv, dpart);
     if (dv && ndp) *ndp = (int32_t)((s + 255) / 256);
   } else {
-    csweep(c, true, w, s, 1, true, st);
+    return csweep(c, true, w, s, 1, true, st);
   }
   return SLR_OK;
 }
@@ -1342,14 +1342,14 @@ int lanczos_inner(slr_ctx *c, const double *v0_host, hipStream_t st) {
     double *vj = V + (int64_t)j * s2;
     // w = H2 v_j: T = L2^{-T} v_j, Tu = C1^{-1} F T, w = L2^{-1} F^T Tu
     launch_axpby(s2, 1, 1.0, vj, s2, 0.0, T, s2, st);
-    c2sweep(c, false, T, s2, 1, true, st);
+    if ((rc = c2sweep(c, false, T, s2, 1, true, st))) return bail(rc);
     BArgs a;
     a.y = T; a.ldy = s2; a.b_y = 1.0;
     a.u = Tu; a.ldu = s1;
     a.nrhs = 1;
     if ((rc = c1solve(c, a, 3, true, st))) return bail(rc);
     launch_spmv_axpby(s2, I.ft_rp, I.ft_ci, I.ft_v, Tu, s1, Wl, s2, 1, 0.0, 1.0, st);
-    c2sweep(c, true, Wl, s2, 1, true, st);
+    if ((rc = c2sweep(c, true, Wl, s2, 1, true, st))) return bail(rc);
     int32_t rb = 0;
     for (int pass = 0; pass < 2; ++pass) {
       const int32_t rbh = launch_multidot_partial(s2, j + 1, V, s2, Wl, part, RED_NBLK, st);
@@ -3452,7 +3452,7 @@ int slr_time_kernel(slr_ctx *c, int32_t which, int32_t nrhs, int32_t reps, void 
         if (c->c_two_level)
           csweep2(c, true, c->ws.W, s, c->ws.W2, s, nrhs, false, st);
         else
-          csweep(c, true, c->ws.W, s, nrhs, false, st);
+          return csweep(c, true, c->ws.W, s, nrhs, false, st);
         return SLR_OK;
       case 2: lowrank(c, c->ws, c->ws.W2, s, c->ws.W, s, nrhs, st); return SLR_OK;
       case 3:
@@ -3461,7 +3461,7 @@ int slr_time_kernel(slr_ctx *c, int32_t which, int32_t nrhs, int32_t reps, void 
         if (c->c_two_level)
           csweep2(c, false, c->ws.W, s, c->pz + m, n, nrhs, false, st);
         else
-          csweep(c, false, c->pz + m, n, nrhs, false, st);
+          return csweep(c, false, c->pz + m, n, nrhs, false, st);
         return SLR_OK;
       case 4: {
         BArgs a;
