@@ -6,11 +6,12 @@
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <functional>
+#include <new>
 #include <mutex>
 #include <numeric>
 #include <queue>
@@ -19,6 +20,7 @@
 #include <vector>
 
 #include "slr.h"
+#include "slr_threads.h"
 #include "slr_dev.h"
 #include "slr_host.h"
 #include "slr_kern.h"
@@ -1958,26 +1960,20 @@ bool pack_blocks(DevPool &P, const std::vector<Block> &blocks, BlockArrays<TS> &
   };
   std::vector<Packed> packed(Kfix == 0 ? nbk : 0);
   if (Kfix == 0) {
-    std::atomic<int32_t> next{0};
-    auto worker = [&]() {
-      for (int32_t q = next++; q < nbk; q = next++) {
-        const Block &b = blocks[q];
-        Packed &k = packed[q];
-        for (int f = 0; f < 2; ++f) {
-          k.off[f] = (int64_t)k.data.size();
-          SegPacker<TS> pk{f ? b.bwd : b.fwd, k.data, k.lvb[f], k.lev[f], rm ? &k.map : nullptr, b.f_base, k.off[f],
-                           seg_bytes, k.max_bytes};
-          pk.pack(b.lanes, b.runs);
-          k.nseg[f] = pk.nseg;
-          k.ok = k.ok && pk.ok;
-        }
-      }
-    };
     const int32_t nth = (int32_t)std::max(1u, std::min<unsigned>(std::thread::hardware_concurrency(), 16u));
-    std::vector<std::thread> pool;
-    for (int32_t t = 1; t < std::min(nth, nbk); ++t) pool.emplace_back(worker);
-    worker();
-    for (auto &th : pool) th.join();
+    const bool done = run_parallel(nbk, nth, [&](int32_t q) {
+      const Block &b = blocks[q];
+      Packed &k = packed[q];
+      for (int f = 0; f < 2; ++f) {
+        k.off[f] = (int64_t)k.data.size();
+        SegPacker<TS> pk{f ? b.bwd : b.fwd, k.data, k.lvb[f], k.lev[f], rm ? &k.map : nullptr, b.f_base, k.off[f],
+                         seg_bytes, k.max_bytes};
+        pk.pack(b.lanes, b.runs);
+        k.nseg[f] = pk.nseg;
+        k.ok = k.ok && pk.ok;
+      }
+    });
+    if (!done) throw std::bad_alloc();
     size_t total = 0;
     for (const Packed &k : packed) total += k.data.size();
     data.reserve(total);
@@ -2902,7 +2898,8 @@ int export_setup(const slr_ctx *cc, std::vector<uint8_t> &blob) {
   return SLR_OK;
 }
 
-int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out) {
+// (c: the context while it is being made)
+int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx *&c, slr_ctx **out) {
   if (bytes < 24 || std::memcmp(buf, kSetupMagic, 7) != 0 || buf[7] < kSetupOldest || buf[7] > kSetupMagic[7])
     return fail(SLR_ERR_ARG, "not a serialised SLR setup");
   const int version = buf[7] - '0';
@@ -2912,9 +2909,8 @@ int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out
   std::memcpy(&h, buf + 16 + len, 8);
   if (h != fnv1a(buf + 16, len)) return fail(SLR_ERR_ARG, "serialised setup: checksum mismatch");
   Reader r{buf + 16, (size_t)len};
-  slr_ctx *c = new slr_ctx();
+  c = new slr_ctx();
   auto bad = [&](const char *what) {
-    slr_destroy(c);
     return fail(SLR_ERR_ARG, std::string("serialised setup: ") + what);
   };
   (void)hipGetDevice(&c->device);
@@ -3042,24 +3038,31 @@ int import_setup(const uint8_t *buf, size_t bytes, hipStream_t st, slr_ctx **out
     return bad("low-rank part does not match the problem");
   c->info = info;
   c->U64 = c->lrpool.upload(U.empty() ? std::vector<double>{0.0} : U);
-  if (!c->U64) {
-    slr_destroy(c);
-    return fail(SLR_ERR_OOM, "U");
-  }
+  if (!c->U64) return fail(SLR_ERR_OOM, "U");
   int rc = finish_lowrank(c, st);
   if (!rc) rc = ws_ensure(c, c->ws, 1);
-  if (rc) {
-    slr_destroy(c);
-    return rc;
-  }
-  if (hipStreamSynchronize(st) != hipSuccess) {
-    slr_destroy(c);
-    return fail(SLR_ERR_HIP, "hipStreamSynchronize");
-  }
+  if (rc) return rc;
+  if (hipStreamSynchronize(st) != hipSuccess) return fail(SLR_ERR_HIP, "hipStreamSynchronize");
   c->info.k = c->k;
   c->info.theta = c->theta;
   *out = c;
   return SLR_OK;
+}
+
+// make(c) for an entry point that makes a context: a failure or an exception
+// leaves no part of one behind.
+template <class F>
+int guarded(slr_ctx **out, F make) {
+  slr_ctx *c = nullptr;
+  int rc;
+  try {
+    rc = make(c);
+  } catch (const std::exception &e) {
+    rc = fail(SLR_ERR_OOM, std::string("host memory or threads: ") + e.what());
+  }
+  if (rc && c) slr_destroy(c);
+  if (rc) *out = nullptr;
+  return rc;
 }
 
 }  // namespace
@@ -3124,10 +3127,9 @@ int slr_device_lds_bytes(void) {
   return (int)prop.sharedMemPerBlock;
 }
 
-int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *o, void *hip_stream,
-              slr_ctx **out) {
-  if (!A || !part || !o || !out || !A->rowptr || !A->col || !A->val) return fail(SLR_ERR_ARG, "null argument");
-  *out = nullptr;
+// (c: the context while it is being made)
+static int setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *o, void *hip_stream, slr_ctx *&c,
+                 slr_ctx **out) {
   if (o->k < 0 || o->k > 64) return fail(SLR_ERR_ARG, "k must be in [0, 64]");
   if (o->theta_mode < SLR_THETA_LAMBDA_K1 || o->theta_mode > SLR_THETA_LAMBDA_S) return fail(SLR_ERR_ARG, "theta_mode");
   if (o->theta_mode == SLR_THETA_EPS && !(o->eps > 0.0)) return fail(SLR_ERR_ARG, "theta_mode eps needs eps > 0");
@@ -3168,7 +3170,7 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
   std::string err;
   int rc = host_setup(A->n, A->rowptr, A->col, A->val, part, p, prm, H, err);
   if (rc) return fail(rc, err);
-  slr_ctx *c = new slr_ctx();
+  c = new slr_ctx();
   (void)hipGetDevice(&c->device);
   {
     // set-up of slr_apply_dd_noalloc's scratch on this device (a failure
@@ -3186,10 +3188,6 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
   c->lds_limit = (size_t)slr_device_lds_bytes();
   c->n_cu = device_cu_count();
   c->perm_h = H.perm;
-  auto destroy_fail = [&](int code) {
-    slr_destroy(c);
-    return code;
-  };
   c->perm = c->pool.upload(H.perm);
   c->perm32 = c->pool.upload(std::vector<int32_t>(H.perm.begin(), H.perm.end()));
   c->a_rp = c->pool.upload(H.a_rp);
@@ -3207,7 +3205,7 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
   RfMaps rmaps;
   RfMaps *rm = H.have_plan ? &rmaps : nullptr;
   ok = ok && (c->fact_prec == SLR_FP64 ? upload_blocks<double>(c, H, c->Bd, rm) : upload_blocks<float>(c, H, c->Bf, rm));
-  if (!ok) return destroy_fail(fail(SLR_ERR_OOM, "factor upload (or a subdomain above 65535 rows)"));
+  if (!ok) return fail(SLR_ERR_OOM, "factor upload (or a subdomain above 65535 rows)");
   if (H.s1 > 0) {
     slr_ctx::Inner &I = c->ml;
     I.on = true;
@@ -3215,10 +3213,10 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
     I.s2 = H.s - H.s1;
     I.nb = (int32_t)H.c1blocks.size();
     for (const Block &b : H.c1blocks)
-      if (b.m > 65535) return destroy_fail(fail(SLR_ERR_ARG, "a connector above 65535 rows"));
+      if (b.m > 65535) return fail(SLR_ERR_ARG, "a connector above 65535 rows");
     const bool ok2 = c->fact_prec == SLR_FP64 ? upload_inner<double>(c, H, I.Bd, I.C2fd, I.C2bd)
                                               : upload_inner<float>(c, H, I.Bf, I.C2ff, I.C2bf);
-    if (!ok2) return destroy_fail(fail(SLR_ERR_OOM, "inner interface solver upload"));
+    if (!ok2) return fail(SLR_ERR_OOM, "inner interface solver upload");
     I.f_lev_h = H.c2fwd.levptr;
     I.b_lev_h = H.c2bwd.levptr;
     I.f_nlev = H.c2fwd.nlev;
@@ -3235,16 +3233,16 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
     if (lg >= 0 && std::max(I.f_nlev, I.b_nlev) > 2 &&
         !(c->fact_prec == SLR_FP64 ? deep_build<double>(c, H.c2fwd, H.c2bwd, old_us, lg, I.deep)
                                    : deep_build<float>(c, H.c2fwd, H.c2bwd, old_us, lg, I.deep)))
-      return destroy_fail(fail(SLR_ERR_OOM, "inner interface factor blocks"));
+      return fail(SLR_ERR_OOM, "inner interface factor blocks");
     if (I.one_wg && sizeof(int32_t) * (size_t)(std::max(I.f_nlev, I.b_nlev) + 1) > c->lds_limit)
-      return destroy_fail(fail(SLR_ERR_ARG, "inner level schedule too deep for one workgroup"));
+      return fail(SLR_ERR_ARG, "inner level schedule too deep for one workgroup");
     I.nnz_L1 = H.nnz_LC1;
     I.nnz_L2 = H.nnz_LC2;
     I.k2 = o->k2 > 0 ? o->k2 : o->k;
     int32_t R1 = 0, st1 = 0;
     const int32_t K1 = c->fact_prec == SLR_FP64 ? I.Bd.pack_K : I.Bf.pack_K;
     if (!b_lds_plan_sz(I.max_m, I.max_lev, I.max_level_bytes, I.data_bytes, K1, true, 1, 8, R1, st1, c->lds_limit))
-      return destroy_fail(fail(SLR_ERR_ARG, "largest connector does not fit one workgroup's LDS"));
+      return fail(SLR_ERR_ARG, "largest connector does not fit one workgroup's LDS");
   }
   c->cf_lev_h = H.cfwd.levptr;
   c->cb_lev_h = H.cbwd.levptr;
@@ -3264,14 +3262,14 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
   // (the recursive interface solver has no single factor of C)
   if (!c->ml.on && !(c->fact_prec == SLR_FP64 ? upload_c<double>(c, H, c->Cfd, c->Cbd, rm, dm)
                                               : upload_c<float>(c, H, c->Cff, c->Cbf, rm, dm)))
-    return destroy_fail(fail(SLR_ERR_OOM, "interface factor upload"));
-  if (rm && !rf_upload(c, H, *rm, dmaps, A)) return destroy_fail(fail(SLR_ERR_OOM, "refactorisation plan"));
+    return fail(SLR_ERR_OOM, "interface factor upload");
+  if (rm && !rf_upload(c, H, *rm, dmaps, A)) return fail(SLR_ERR_OOM, "refactorisation plan");
   if (c->c_one_wg && sizeof(int32_t) * (size_t)(std::max(c->cf_nlev, c->cb_nlev) + 1) > c->lds_limit)
-    return destroy_fail(fail(SLR_ERR_ARG, "interface level schedule too deep for one workgroup"));
+    return fail(SLR_ERR_ARG, "interface level schedule too deep for one workgroup");
   {
     int32_t R1 = 0, st1 = 0;
     if (!b_lds_plan(c, 1, c->fact_prec == SLR_FP64 ? 8 : 4, R1, st1) || !b_lds_plan(c, 1, 8, R1, st1))
-      return destroy_fail(fail(SLR_ERR_ARG, "largest subdomain does not fit one workgroup's LDS"));
+      return fail(SLR_ERR_ARG, "largest subdomain does not fit one workgroup's LDS");
   }
   // stats
   slr_info &I = c->info;
@@ -3295,10 +3293,10 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
   const double t1 = now_s();
   std::vector<double> v0s;
   const double *v0p = o->lanczos_v0 ? o->lanczos_v0 : seeded_v0(c->n, o->seed, v0s);
-  if ((rc = ws_ensure(c, c->ws, 1))) return destroy_fail(rc);
+  if ((rc = ws_ensure(c, c->ws, 1))) return rc;
   if (c->ml.on) {
-    if ((rc = lanczos_inner(c, v0p, st))) return destroy_fail(rc);
-    if ((rc = ws_ensure(c, c->ws, 1))) return destroy_fail(rc);
+    if ((rc = lanczos_inner(c, v0p, st))) return rc;
+    if ((rc = ws_ensure(c, c->ws, 1))) return rc;
     I.s1 = c->ml.s1;
     I.k2 = c->ml.k2;
     I.lanczos_steps2 = c->ml.steps;
@@ -3310,31 +3308,38 @@ int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *
     I.nnz_F = (int64_t)H.ft_ci.size();
   }
   if (o->U_in && o->k_in > 0) {
-    if (o->k_in > 64 || !o->lambda_in) return destroy_fail(fail(SLR_ERR_ARG, "imported low-rank part"));
+    if (o->k_in > 64 || !o->lambda_in) return fail(SLR_ERR_ARG, "imported low-rank part");
     c->k = o->k_in;
     std::vector<double> Ucm(o->U_in, o->U_in + (size_t)c->s * c->k);   // column-major s x k
     c->U64 = c->lrpool.upload(Ucm);
-    if (!c->U64) return destroy_fail(fail(SLR_ERR_OOM, "U"));
+    if (!c->U64) return fail(SLR_ERR_OOM, "U");
     c->lam_h.assign(o->lambda_in, o->lambda_in + c->k);
     c->ritz_h = c->lam_h;
     c->theta = o->theta_in;
-    if ((rc = finish_lowrank(c, st))) return destroy_fail(rc);
+    if ((rc = finish_lowrank(c, st))) return rc;
   } else if (o->k > 0 && c->s > 0) {
     c->k = o->k;
-    if ((rc = lanczos_build(c, o->k, 0, v0p, st))) return destroy_fail(rc);
+    if ((rc = lanczos_build(c, o->k, 0, v0p, st))) return rc;
   } else {
     c->k = 0;
     c->theta = 0.0;
-    if ((rc = finish_lowrank(c, st))) return destroy_fail(rc);
+    if ((rc = finish_lowrank(c, st))) return rc;
   }
   HIPCHK(hipStreamSynchronize(st));
   I.k = c->k;
   I.theta = c->theta;
   I.setup_lanczos_s = now_s() - t1;
-  if ((rc = ws_ensure(c, c->ws, 1))) return destroy_fail(rc);
+  if ((rc = ws_ensure(c, c->ws, 1))) return rc;
   I.device_bytes = c->pool.bytes + c->lrpool.bytes + c->ws.pool.bytes;
   *out = c;
   return SLR_OK;
+}
+
+int slr_setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *o, void *hip_stream,
+              slr_ctx **out) {
+  if (!A || !part || !o || !out || !A->rowptr || !A->col || !A->val) return fail(SLR_ERR_ARG, "null argument");
+  *out = nullptr;
+  return guarded(out, [&](slr_ctx *&c) { return setup(A, part, p, o, hip_stream, c, out); });
 }
 
 int slr_update_lowrank(slr_ctx *c, int32_t k, int32_t lanczos_steps, const double *lanczos_v0,
@@ -3762,7 +3767,7 @@ int slr_export_setup(const slr_ctx *c, void *buf, size_t cap, size_t *bytes) {
 int slr_import(const void *buf, size_t bytes, void *hip_stream, slr_ctx **out) {
   if (!buf || !out) return fail(SLR_ERR_ARG, "null");
   *out = nullptr;
-  return import_setup((const uint8_t *)buf, bytes, S(hip_stream), out);
+  return guarded(out, [&](slr_ctx *&c) { return import_setup((const uint8_t *)buf, bytes, S(hip_stream), c, out); });
 }
 
 void slr_set_allocator(slr_alloc_fn alloc, slr_free_fn free_, void *user) {
