@@ -1925,6 +1925,44 @@ double block_cost(const Block &b) {
   return (double)(b.fwd.nlev + b.bwd.nlev) + (double)(b.fwd.ci.size() + b.bwd.ci.size()) / 256.0;
 }
 
+// Both sweeps of a block of rows of any width, packed.
+struct PackedStreams {
+  std::vector<uint8_t> data;
+  std::vector<int32_t> lvb[2], lev[2];
+  std::vector<RfMap> map;
+  int64_t off[2] = {0, 0};
+  int32_t nseg[2] = {0, 0}, max_bytes = 0;
+  bool ok = true;
+};
+
+// The sweeps of a block set of any width, block by block on several threads.
+template <typename TS>
+std::vector<PackedStreams> pack_streams(const std::vector<Block> &blocks, bool maps, size_t lds) {
+  int32_t widest_m = 0;
+  int64_t stream = 0;
+  for (const Block &b : blocks) {
+    widest_m = std::max(widest_m, b.m);
+    for (const Sweep *sw : {&b.fwd, &b.bwd}) stream += (2 + (int64_t)sizeof(TS)) * (sw->nrows + (int64_t)sw->ci.size());
+  }
+  const int64_t seg_bytes = segment_bytes(widest_m, lds, stream);
+  std::vector<PackedStreams> packed(blocks.size());
+  const int32_t nth = (int32_t)std::max(1u, std::min<unsigned>(std::thread::hardware_concurrency(), 16u));
+  const bool done = run_parallel((int32_t)blocks.size(), nth, [&](int32_t q) {
+    const Block &b = blocks[q];
+    PackedStreams &k = packed[q];
+    for (int f = 0; f < 2; ++f) {
+      k.off[f] = (int64_t)k.data.size();
+      SegPacker<TS> pk{f ? b.bwd : b.fwd, k.data, k.lvb[f], k.lev[f], maps ? &k.map : nullptr, b.f_base, k.off[f],
+                       seg_bytes, k.max_bytes};
+      pk.pack(b.lanes, b.runs);
+      k.nseg[f] = pk.nseg;
+      k.ok = k.ok && pk.ok;
+    }
+  });
+  if (!done) throw std::bad_alloc();
+  return packed;
+}
+
 // Pack and upload a set of diagonal blocks (factor sweeps, E and E^T rows)
 // for the B kernel (lds: the bytes a workgroup should get by with).  Every
 // local index in the packed data is an LDS position (lds_positions); B.xpos maps a block's rows to them, or is null
@@ -1943,39 +1981,11 @@ bool pack_blocks(DevPool &P, const std::vector<Block> &blocks, BlockArrays<TS> &
   int32_t max_m = 0, max_lev = 0, max_lb = 0, max_K = 0;
   bool ok = true;
   const int32_t Kfix = packed_width(blocks);
-  int32_t widest_m = 0;
-  for (const Block &b : blocks) widest_m = std::max(widest_m, b.m);
-  int64_t stream = 0;
-  for (const Block &b : blocks)
-    for (const Sweep *sw : {&b.fwd, &b.bwd}) stream += (2 + (int64_t)sizeof(TS)) * (sw->nrows + (int64_t)sw->ci.size());
-  const int64_t seg_bytes = segment_bytes(widest_m, lds, stream);
-  // sweeps of any width are packed block by block on several threads
-  struct Packed {
-    std::vector<uint8_t> data;
-    std::vector<int32_t> lvb[2], lev[2];
-    std::vector<RfMap> map;
-    int64_t off[2] = {0, 0};
-    int32_t nseg[2] = {0, 0}, max_bytes = 0;
-    bool ok = true;
-  };
-  std::vector<Packed> packed(Kfix == 0 ? nbk : 0);
+  std::vector<PackedStreams> packed;
   if (Kfix == 0) {
-    const int32_t nth = (int32_t)std::max(1u, std::min<unsigned>(std::thread::hardware_concurrency(), 16u));
-    const bool done = run_parallel(nbk, nth, [&](int32_t q) {
-      const Block &b = blocks[q];
-      Packed &k = packed[q];
-      for (int f = 0; f < 2; ++f) {
-        k.off[f] = (int64_t)k.data.size();
-        SegPacker<TS> pk{f ? b.bwd : b.fwd, k.data, k.lvb[f], k.lev[f], rm ? &k.map : nullptr, b.f_base, k.off[f],
-                         seg_bytes, k.max_bytes};
-        pk.pack(b.lanes, b.runs);
-        k.nseg[f] = pk.nseg;
-        k.ok = k.ok && pk.ok;
-      }
-    });
-    if (!done) throw std::bad_alloc();
+    packed = pack_streams<TS>(blocks, rm != nullptr, lds);
     size_t total = 0;
-    for (const Packed &k : packed) total += k.data.size();
+    for (const PackedStreams &k : packed) total += k.data.size();
     data.reserve(total);
   }
   for (int32_t q = 0; q < nbk; ++q) {
@@ -2010,7 +2020,7 @@ bool pack_blocks(DevPool &P, const std::vector<Block> &blocks, BlockArrays<TS> &
         if (cut.levptr.empty()) lev.push_back(0);
         pack_sweep<TS>(cut, Kfix, data, lvb, max_lb, off, rm ? &rm->bdata : nullptr, b.f_base);
       } else {
-        const Packed &k = packed[q];
+        const PackedStreams &k = packed[q];
         const int w = f ? 0 : 1;
         for (int32_t t = 0; t < sp->nrows; ++t) K = std::max(K, sp->rp[t + 1] - sp->rp[t]);
         if (f) {
@@ -2204,23 +2214,33 @@ double deep_sweep_us(const Sweep &sw, bool runs) {
   return us + 24.0 * (double)sw.ci.size() / 40e3;
 }
 
+struct DeepSplit {
+  struct Ent {
+    int32_t col;
+    double v;
+    int32_t fac, diag;   // where it comes from
+  };
+  bool on = false;
+  int32_t t = 0;
+  std::vector<Block> lead, rest;
+  std::vector<std::vector<Ent>> et;
+};
+
 // The block form of a deep interface factor, where it is modelled to beat
 // the schedule's own launches (old_us for both sweeps): the leading rows up
 // to the t that leaves the smallest largest piece plus remainder.  Connectors
 // (HID order) make the pieces; without them a factor that fits one
 // workgroup's LDS is one block.  lanes >= 0: every row in that many lanes
 // (log2) and no near-chains, which keeps the sums of launch_sweep with the
-// same lanes; only for t == 0.  rm: where the coefficients come from.
-template <typename TS>
-bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32_t lanes, slr_ctx::Deep &D,
-                RfDeepMaps *rm = nullptr) {
+// same lanes; only for t == 0.
+DeepSplit deep_split(const Sweep &f, const Sweep &b, double old_us, int32_t lanes, size_t lds_limit) {
   const int32_t s = f.nrows;
-  D.on = false;
-  if (std::max(f.nlev, b.nlev) <= 8) return true;   // a few wide launches
+  DeepSplit S;
+  if (std::max(f.nlev, b.nlev) <= 8) return S;   // a few wide launches
   for (double x : f.sc)
-    if (x == 0.0) return true;
+    if (x == 0.0) return S;
   // rows that fit a workgroup's LDS beside a stage and its tables
-  const int64_t cap = std::min<int64_t>(65535, ((int64_t)c->lds_limit - 49152) / 8);
+  const int64_t cap = std::min<int64_t>(65535, ((int64_t)lds_limit - 49152) / 8);
   std::vector<int32_t> tof(s), root(s), size(s, 1);
   for (int32_t t = 0; t < s; ++t) tof[f.rows[t]] = t;
   std::iota(root.begin(), root.end(), 0);
@@ -2251,7 +2271,7 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
       M = std::max<int64_t>(M, join(i));
     }
   }
-  if (t < 0) return true;
+  if (t < 0) return S;
   // pieces of the leading rows (each must be a contiguous range), small
   // neighbours joined
   std::iota(root.begin(), root.end(), 0);
@@ -2264,7 +2284,7 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
     const int32_t r = find(i);
     if (i > 0 && find(i - 1) == r) continue;
     if (seen[r]) {
-      if (s > cap) return true;
+      if (s > cap) return S;
       t = 0;   // not contiguous: one block
       starts.clear();
       break;
@@ -2283,13 +2303,11 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
     fs[blk[f.rows[k]]].push_back(k);
     bs[blk[b.rows[k]]].push_back(k);
   }
-  std::vector<Block> lead(nb), rest(1);
-  struct Ent {
-    int32_t col;
-    double v;
-    int32_t fac, diag;
-  };
-  std::vector<std::vector<Ent>> et(s - t);
+  std::vector<Block> &lead = S.lead, &rest = S.rest;
+  std::vector<std::vector<DeepSplit::Ent>> &et = S.et;
+  lead.resize(nb);
+  rest.resize(1);
+  et.resize(s - t);
   double us = 0.0;
   for (int32_t q = 0; q <= nb; ++q) {
     Block &k = q < nb ? lead[q] : rest[0];
@@ -2299,17 +2317,17 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
     k.lanes = lanes;
     k.runs = lanes < 0;
     k.fwd = sub_sweep(f, fs[q], lo, hi, [&](int32_t r, int32_t col, double v, int32_t fac, int32_t diag) {
-      et[r].push_back(Ent{col, v, fac, diag});
+      et[r].push_back(DeepSplit::Ent{col, v, fac, diag});
     });
-    std::vector<std::vector<Ent>> e(q < nb ? k.m : 0);
+    std::vector<std::vector<DeepSplit::Ent>> e(q < nb ? k.m : 0);
     k.bwd = sub_sweep(b, bs[q], lo, hi, [&](int32_t r, int32_t col, double v, int32_t fac, int32_t diag) {
-      e[r].push_back(Ent{col - t, v, fac, diag});
+      e[r].push_back(DeepSplit::Ent{col - t, v, fac, diag});
     });
     for (int32_t r = 0; r < (int32_t)e.size(); ++r) {
       if (e[r].empty()) continue;
       k.e_row.push_back(r);
       k.e_ptr.push_back((int32_t)k.e_q.size());
-      for (const Ent &x : e[r]) {
+      for (const DeepSplit::Ent &x : e[r]) {
         k.e_q.push_back(x.col);
         k.e_val.push_back(x.v);
         k.e_fac.push_back(x.fac);
@@ -2321,7 +2339,20 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
     const double one = deep_sweep_us(k.fwd, k.runs) + deep_sweep_us(k.bwd, k.runs);
     us = q < nb ? std::max(us, one) : us + one;
   }
-  if (us + 20.0 > 0.7 * old_us) return true;
+  if (us + 20.0 > 0.7 * old_us) return S;
+  S.on = true;
+  S.t = t;
+  return S;
+}
+
+// The same packed and uploaded.  rm: where the coefficients come from.
+template <typename TS>
+bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32_t lanes, slr_ctx::Deep &D,
+                RfDeepMaps *rm = nullptr) {
+  D.on = false;
+  const DeepSplit S = deep_split(f, b, old_us, lanes, c->lds_limit);
+  if (!S.on) return true;
+  const int32_t s = f.nrows, t = S.t, nb = (int32_t)S.lead.size();
   D.t = t;
   D.s = s;
   auto pack = [&](const std::vector<Block> &blocks, slr_ctx::Deep::Part &P, RfMaps *pm) {
@@ -2341,14 +2372,14 @@ bool deep_build(slr_ctx *c, const Sweep &f, const Sweep &b, double old_us, int32
                                sizeof(TS) == 8 ? P.Bd.pack_K : P.Bf.pack_K, false, 1, 8, R, stage, c->lds_limit);
   };
   // a task or a table that does not fit leaves the schedule's own launches
-  if ((nb > 0 && !pack(lead, D.lead, rm ? &rm->lead : nullptr)) || !pack(rest, D.rest, rm ? &rm->rest : nullptr))
+  if ((nb > 0 && !pack(S.lead, D.lead, rm ? &rm->lead : nullptr)) || !pack(S.rest, D.rest, rm ? &rm->rest : nullptr))
     return true;
   if (t > 0) {
     std::vector<int64_t> rp(1, 0);
     std::vector<int32_t> ci;
     std::vector<double> v;
-    for (const auto &row : et) {
-      for (const Ent &x : row) {
+    for (const auto &row : S.et) {
+      for (const DeepSplit::Ent &x : row) {
         if (rm) rm->et.push_back(RfMap{(int64_t)sizeof(double) * (int64_t)v.size(), x.fac, x.diag, 0, RF_ENT64});
         ci.push_back(x.col);
         v.push_back(x.v);
@@ -2423,7 +2454,14 @@ bool upload_inner(slr_ctx *c, const HostSetup &H, BlockArrays<TS> &B, SweepArray
   I.max_lev = sz.max_lev;
   I.max_level_bytes = sz.max_level_bytes;
   I.data_bytes = sz.data_bytes;
-  ok = ok && upload_sweep<TS>(c->pool, H.c2fwd, Cf, nullptr) && upload_sweep<TS>(c->pool, H.c2bwd, Cb, nullptr);
+  // C2's sweeps in the lanes of its own launches also by blocks: the inner
+  // spectrum is flat, and its Lanczos vectors follow every rounding
+  const int32_t lg = I.f_group == I.b_group ? __builtin_ctz((unsigned)I.f_group) : -1;
+  const double old_us = schedule_us(H.c2fwd, H.c2bwd, I.one_wg, I.f_group, I.b_group);
+  if (lg >= 0 && std::max(I.f_nlev, I.b_nlev) > 2)
+    ok = ok && deep_build<TS>(c, H.c2fwd, H.c2bwd, old_us, lg, I.deep);
+  if (!I.deep.on)
+    ok = ok && upload_sweep<TS>(c->pool, H.c2fwd, Cf, nullptr) && upload_sweep<TS>(c->pool, H.c2bwd, Cb, nullptr);
   I.ft_rp = c->pool.upload(H.ft_rp);
   I.ft_ci = c->pool.upload(H.ft_ci.empty() ? std::vector<int32_t>{0} : H.ft_ci);
   I.ft_v = c->pool.upload(H.ft_v.empty() ? std::vector<double>{0.0} : H.ft_v);
@@ -3214,9 +3252,6 @@ static int setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opt
     I.nb = (int32_t)H.c1blocks.size();
     for (const Block &b : H.c1blocks)
       if (b.m > 65535) return fail(SLR_ERR_ARG, "a connector above 65535 rows");
-    const bool ok2 = c->fact_prec == SLR_FP64 ? upload_inner<double>(c, H, I.Bd, I.C2fd, I.C2bd)
-                                              : upload_inner<float>(c, H, I.Bf, I.C2ff, I.C2bf);
-    if (!ok2) return fail(SLR_ERR_OOM, "inner interface solver upload");
     I.f_lev_h = H.c2fwd.levptr;
     I.b_lev_h = H.c2bwd.levptr;
     I.f_nlev = H.c2fwd.nlev;
@@ -3226,14 +3261,9 @@ static int setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opt
       I.f_group = sweep_group(H.c2fwd);
       I.b_group = sweep_group(H.c2bwd);
     }
-    // (in the lanes of its own launches: the inner spectrum is flat, and its
-    // Lanczos vectors follow every rounding)
-    const int32_t lg = I.f_group == I.b_group ? __builtin_ctz((unsigned)I.f_group) : -1;
-    const double old_us = schedule_us(H.c2fwd, H.c2bwd, I.one_wg, I.f_group, I.b_group);
-    if (lg >= 0 && std::max(I.f_nlev, I.b_nlev) > 2 &&
-        !(c->fact_prec == SLR_FP64 ? deep_build<double>(c, H.c2fwd, H.c2bwd, old_us, lg, I.deep)
-                                   : deep_build<float>(c, H.c2fwd, H.c2bwd, old_us, lg, I.deep)))
-      return fail(SLR_ERR_OOM, "inner interface factor blocks");
+    const bool ok2 = c->fact_prec == SLR_FP64 ? upload_inner<double>(c, H, I.Bd, I.C2fd, I.C2bd)
+                                              : upload_inner<float>(c, H, I.Bf, I.C2ff, I.C2bf);
+    if (!ok2) return fail(SLR_ERR_OOM, "inner interface solver upload");
     if (I.one_wg && sizeof(int32_t) * (size_t)(std::max(I.f_nlev, I.b_nlev) + 1) > c->lds_limit)
       return fail(SLR_ERR_ARG, "inner level schedule too deep for one workgroup");
     I.nnz_L1 = H.nnz_LC1;
@@ -3605,9 +3635,8 @@ int slr_set_bsolve_plan(slr_ctx *c, int32_t several, int32_t threads, int32_t ld
   return SLR_OK;
 }
 
-int slr_analyze(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *o, slr_info *info,
-                int64_t *perm) {
-  if (!A || !part || !o || !info || !A->rowptr || !A->col || !A->val) return fail(SLR_ERR_ARG, "null argument");
+static int analyze(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *o, slr_info *info,
+                   int64_t *perm) {
   if (A->rowptr[A->n] != A->nnz) return fail(SLR_ERR_ARG, "rowptr[n] != nnz");
   const double t0 = now_s();
   HostSetup H;
@@ -3632,7 +3661,30 @@ int slr_analyze(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts
   info->nnz_A = (int64_t)H.a_ci.size();
   info->m_min = INT64_MAX;
   const int64_t fb = o->fact_prec == SLR_FP32 ? 4 : 8;
-  int64_t bytes = (int64_t)H.a_ci.size() * 12 + (H.n + 1) * 8 + H.n * 8;
+  int64_t bytes = (int64_t)H.a_ci.size() * 12 + (H.n + 1) * 8 + H.n * 12;
+  // the sweeps of a block set and its couplings
+  const size_t lds = (size_t)std::max(slr_device_lds_bytes(), 163840);
+  auto block_bytes = [&](const std::vector<Block> &blocks) {
+    int64_t n = 0;
+    if (packed_width(blocks) == 0) {
+      for (const PackedStreams &k : fb == 8 ? pack_streams<double>(blocks, false, lds) : pack_streams<float>(blocks, false, lds))
+        n += (int64_t)k.data.size();
+    } else {
+      for (const Block &b : blocks)
+        n += (int64_t)(b.fwd.ci.size() + b.bwd.ci.size()) * (4 + fb) + (int64_t)b.m * 2 * (8 + fb);
+    }
+    for (const Block &b : blocks) n += (int64_t)(b.e_q.size() + b.t_j.size()) * (4 + fb) + (int64_t)b.m * 2;
+    return n;
+  };
+  auto sweep_bytes = [&](const Sweep &f, const Sweep &b, bool one_wg, int32_t lanes, bool deep) {
+    if (deep) {
+      const DeepSplit S = deep_split(f, b, schedule_us(f, b, one_wg, sweep_group(f), sweep_group(b)), lanes, lds);
+      int64_t n = 0;
+      for (const auto &row : S.et) n += 8 + 12 * (int64_t)row.size();
+      if (S.on) return n + (S.lead.empty() ? 0 : block_bytes(S.lead)) + block_bytes(S.rest);
+    }
+    return (int64_t)(f.ci.size() + b.ci.size()) * (4 + fb) + f.nrows * 2 * (8 + fb);
+  };
   {
     const int32_t Kfix = packed_width(H.blocks);
     for (const auto &b : H.blocks) {
@@ -3649,10 +3701,12 @@ int slr_analyze(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts
     info->b_levels_max = std::max({info->b_levels_max, b.fwd.nlev, b.bwd.nlev});
     info->m_min = std::min<int64_t>(info->m_min, b.m);
     info->m_max = std::max<int64_t>(info->m_max, b.m);
-    bytes += (int64_t)(b.fwd.ci.size() + b.bwd.ci.size()) * (4 + fb) + (int64_t)b.m * (2 * (8 + fb) + 10) +
-             (int64_t)(b.e_q.size() + b.t_j.size()) * (4 + fb);
   }
-  bytes += (int64_t)(H.cfwd.ci.size() + H.cbwd.ci.size()) * (4 + fb) + H.s * 2 * (8 + fb);
+  bytes += block_bytes(H.blocks) + H.m * 8;
+  if (H.s1 == 0) {
+    const int32_t nlev = std::max(H.cfwd.nlev, H.cbwd.nlev);
+    bytes += sweep_bytes(H.cfwd, H.cbwd, nlev > 8, -1, nlev > 2);
+  }
   if (H.s1 > 0) {
     // the recursive interface solver: C1 blocks, C2 sweeps, F^T and U2
     const int32_t k2 = o->k2 > 0 ? o->k2 : o->k;
@@ -3664,10 +3718,10 @@ int slr_analyze(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts
     info->nnz_F = (int64_t)H.ft_ci.size();
     for (const auto &b : H.c1blocks) {
       info->c1_levels = std::max({info->c1_levels, b.fwd.nlev, b.bwd.nlev});
-      bytes += (int64_t)(b.fwd.ci.size() + b.bwd.ci.size()) * (4 + fb) + (int64_t)b.m * (2 * (8 + fb) + 2) +
-               (int64_t)b.e_q.size() * (4 + fb);
     }
-    bytes += (int64_t)(H.c2fwd.ci.size() + H.c2bwd.ci.size()) * (4 + fb) + (H.s - H.s1) * 2 * (8 + fb) +
+    const int32_t nlev = std::max(H.c2fwd.nlev, H.c2bwd.nlev), g = sweep_group(H.c2fwd);
+    bytes += block_bytes(H.c1blocks);
+    bytes += sweep_bytes(H.c2fwd, H.c2bwd, nlev > 8, __builtin_ctz((unsigned)g), nlev > 2 && g == sweep_group(H.c2bwd)) +
              (int64_t)H.ft_ci.size() * 12 + (H.s - H.s1) * (int64_t)k2 * 16;
   }
   const int64_t ub = o->uk_prec == SLR_FP64 ? 8 : (o->uk_prec == SLR_FP32 ? 4 : 2);
@@ -3676,6 +3730,16 @@ int slr_analyze(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts
   info->setup_host_s = now_s() - t0;
   if (perm) std::copy(H.perm.begin(), H.perm.end(), perm);
   return SLR_OK;
+}
+
+int slr_analyze(const slr_csr *A, const int32_t *part, int32_t p, const slr_opts *o, slr_info *info,
+                int64_t *perm) {
+  if (!A || !part || !o || !info || !A->rowptr || !A->col || !A->val) return fail(SLR_ERR_ARG, "null argument");
+  try {
+    return analyze(A, part, p, o, info, perm);
+  } catch (const std::exception &e) {
+    return fail(SLR_ERR_OOM, std::string("host memory or threads: ") + e.what());
+  }
 }
 
 void slr_destroy(slr_ctx *c) {
