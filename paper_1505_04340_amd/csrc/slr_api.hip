@@ -2437,6 +2437,13 @@ bool upload_c(slr_ctx *c, const HostSetup &H, SweepArrays<TS> &Cf, SweepArrays<T
          upload_sweep<TS>(c->pool, H.cbwd, Cb, rm ? &rm->cb : nullptr);
 }
 
+// Levels of the deepest sweep of a block set.
+int32_t sweep_depth(const std::vector<Block> &blocks) {
+  int32_t n = 0;
+  for (const Block &b : blocks) n = std::max({n, b.fwd.nlev, b.bwd.nlev});
+  return n;
+}
+
 // Lanes per row of an interface sweep launched one level at a time: by the
 // mean row length (entries per row < 8: one lane per row).
 int32_t sweep_group(const Sweep &sw) {
@@ -3304,7 +3311,8 @@ static int setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opt
   // stats
   slr_info &I = c->info;
   I.n = c->n; I.m = c->m; I.s = c->s; I.p = c->p;
-  I.b_levels_max = c->b_max_lev;
+  // (rows of any width: the schedules, which the segments are packed from)
+  I.b_levels_max = (c->fact_prec == SLR_FP64 ? c->Bd.pack_K : c->Bf.pack_K) > 0 ? c->b_max_lev : sweep_depth(H.blocks);
   I.c_levels = H.cfwd.nlev;
   I.c_colors = H.c_colors;
   I.nnz_LB = 0;
@@ -3330,7 +3338,8 @@ static int setup(const slr_csr *A, const int32_t *part, int32_t p, const slr_opt
     I.s1 = c->ml.s1;
     I.k2 = c->ml.k2;
     I.lanczos_steps2 = c->ml.steps;
-    I.c1_levels = c->ml.max_lev;
+    I.c1_levels = (c->fact_prec == SLR_FP64 ? c->ml.Bd.pack_K : c->ml.Bf.pack_K) > 0 ? c->ml.max_lev
+                                                                                     : sweep_depth(H.c1blocks);
     I.c2_levels = c->ml.f_nlev;
     I.theta2 = c->ml.theta2;
     I.nnz_LC1 = H.nnz_LC1;

@@ -51,5 +51,16 @@ def test_form_of_the_refactorisation(name, over, order, blocks):
     assert slr.forms()["refactor_blocks"] == (pr.nparts if blocks else 0)
 
 
+@pytest.mark.parametrize("name,over,kw", [
+    ("lap2d_64", dict(N=40), dict(b_fact="chol", c_fact="chol")),
+    ("lap3d_64", dict(N=20, boxes=2), dict(b_fact="ict", c_fact="ict", b_order="mindeg")),
+    ("lap3d_64", dict(N=24, boxes=3), dict(c_fact="ict", c_order="hid", c_levels=2, k2=4)),
+])
+def test_levels_are_those_of_the_schedules(name, over, kw):
+    pr, slr = _slr(name, over, **kw)
+    info = P.analyze(pr.csr, pr.part, pr.nparts, **dict(dict(k=4, droptol=1e-4), **kw))[0]
+    assert slr.info["b_levels_max"] == info["b_levels_max"] and slr.info["c1_levels"] == info["c1_levels"]
+
+
 def test_layout():
     assert ctypes.sizeof(P.slr_forms) == 48 and P.slr_forms.c_deep.offset == 16
