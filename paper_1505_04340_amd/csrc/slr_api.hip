@@ -2612,12 +2612,12 @@ void rf_pack_all(slr_ctx *c, const BlockArrays<TS> &B, const SweepArrays<TS> &Cf
                  hipStream_t st) {
   auto &R = c->rf;
   RfPack P;
-  int q = 0;
   auto run = [&](const slr_ctx::Refactor::Map &m, const double *V, const void *base) {
-    P.map[q] = m.m;
-    P.n[q] = m.n;
-    P.V[q] = V;
-    P.base[q++] = const_cast<void *>(base);
+    if (m.n == 0) return;
+    P.map[P.maps] = m.m;
+    P.n[P.maps] = m.n;
+    P.V[P.maps] = V;
+    P.base[P.maps++] = const_cast<void *>(base);
   };
   run(R.bdata, R.fb.v, B.data);
   run(R.ev, nullptr, B.e_val);

@@ -188,14 +188,15 @@ struct RfMap {
   int32_t a, b, c, op;
 };
 
-// every map of a refactorisation in one launch; V: the factor of a map's
-// values (RF_SRC reads val)
+// every map of a refactorisation that is not empty in one launch; V: the
+// factor of a map's values (RF_SRC reads val)
 constexpr int kRfMaps = 13;
 struct RfPack {
   const RfMap *map[kRfMaps] = {};
   int64_t n[kRfMaps] = {};
   const double *V[kRfMaps] = {};
   void *base[kRfMaps] = {};
+  int32_t maps = 0;
 };
 template <typename TS>
 void launch_rf_pack(const RfPack &P, const double *val, hipStream_t st);

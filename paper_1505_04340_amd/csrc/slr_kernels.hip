@@ -3828,7 +3828,7 @@ void launch_rf_pack(const RfPack &P, const double *val, hipStream_t st) {
   int64_t n = 0;
   for (int64_t q : P.n) n = std::max(n, q);
   if (n == 0) return;
-  hipLaunchKernelGGL(k_rf_pack<TS>, dim3((unsigned)((n + 255) / 256), kRfMaps), dim3(256), 0, st, P, val);
+  hipLaunchKernelGGL(k_rf_pack<TS>, dim3((unsigned)((n + 255) / 256), P.maps), dim3(256), 0, st, P, val);
 }
 
 // ---------------------------------------------------------------------------
