@@ -328,11 +328,13 @@ int slr_grow_lowrank(slr_ctx *c, int32_t k_add, int32_t lanczos_steps, const dou
  * on_device != 0; the call does not keep the pointer), for a context set up with
  * opts.refactor = 1.  The zero-fill factors of the B_i and of C (Sec. 5.2,
  * IC(0) / ILDL^T(0)) are recomputed on the device, level by level with the
- * schedules of the forward sweeps (a B_i whose rows subtract no products in
- * one workgroup), and every stored coefficient of the
+ * schedules of the forward sweeps (the B_i in one workgroup each, where in all
+ * of them a row has at most 4 entries left of the diagonal and subtracts no
+ * products), and every stored coefficient of the
  * apply (sweep scales and weights, E, E^T, A for the Krylov products) is
  * rewritten in place in the context's storage precision; the results equal
- * those of a fresh slr_setup with the new values.  The low-rank part
+ * those of a fresh slr_setup with the new values, with opts.refactor or
+ * without.  The low-rank part
  * (U_k, Lambda_k, theta) is kept: call slr_update_lowrank to rebuild it for
  * the new H.  Errors: SLR_ERR_NOT_SYMMETRIC (every value must equal its
  * mirror's; checked where the values are),
@@ -455,7 +457,9 @@ int slr_export_setup(const slr_ctx *c, void *buf, size_t cap, size_t *bytes);
 /* slr_import: a new context on the current device from slr_export_setup's
  * bytes (host; not retained), without the host analysis or the Lanczos
  * build.  Its apply and solves equal those of the exported context bit for
- * bit.  The imported context cannot slr_refactor (no refactorisation plan
+ * bit.  Bytes of the library's earlier layouts are taken as well, with their
+ * sweeps packed anew; where C's sweeps run by launches there and by blocks
+ * here (slr_forms.c_deep) the results agree to rounding.  The imported context cannot slr_refactor (no refactorisation plan
  * is serialised).  Errors: SLR_ERR_ARG (wrong magic, length, checksum or
  * inconsistent sizes), SLR_ERR_OOM, SLR_ERR_HIP.  The content beyond its
  * structure is trusted: pass only bytes that slr_export_setup wrote. */

@@ -1491,9 +1491,10 @@ void pack_sweep(const Sweep &sw, int32_t K, std::vector<uint8_t> &data, std::vec
 //
 // A level's rows are cut into pieces of about kPieceBytes of entries; the
 // rows of a piece get the same number of lanes, by the piece's rows and its
-// widest row (or `lanes`, log2, for the whole sweep); 64 lanes make a task.  A run of at least kColRunMin consecutive levels of at most
-// kColRunRows rows each -- typically the long rows at the end of a minimum
-// degree or threshold factor, each waiting for the previous one -- is packed
+// widest row (or `lanes`, log2, for the whole sweep); 64 lanes make a task.
+// A run of at least kColRunMin consecutive levels of at most kColRunRows rows
+// each -- typically the long rows at the end of a minimum degree or threshold
+// factor, each waiting for the previous one -- is packed
 // as (1) such tasks with the entries of its rows to rows before the run
 // (independent rows: those are final), then, chain by chain of kChainRows run
 // rows, (2) a dense chain with the entries to the previous chain and among

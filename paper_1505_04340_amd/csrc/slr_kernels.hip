@@ -1160,7 +1160,7 @@ __device__ __forceinline__ void bsolve_item(const BlockArrays<TS> &B, const BArg
 // MANY (sweeps of any width): at most 128 registers, so that two workgroups of
 // 512 threads or four of 256 share a compute unit (a.shared).  Without the
 // bound the solver loop takes 230 and a compute unit holds one: 512 blocks of
-// 3375 rows (threshold factors) 492 us, with it 378, 400 exact blocks of 361
+// 3375 rows (threshold factors) 492 us, with it 335, 400 exact blocks of 361
 // rows 72 and 45.  Where one workgroup a compute unit is all there is, the
 // registers saved on entry cost 1% (27 blocks of 48^3) to 5% (32 x 32 small
 // blocks, 16 columns), so the unbounded kernel stays for that.
